@@ -3,8 +3,10 @@
 #include "../../include/draftexpert.h"
 #include "de_common.h"
 #include "draft_persistent.h"
+#include "grouped_mfma.h"
 #include "verify_fused.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -90,6 +92,8 @@ int elem_align(int wdtype) { return wdtype == DE_Q4_0 ? 32 : (wdtype == DE_BF16 
 // The shared path's down projection runs as up to this many dense sources
 // (intermediate chunks), each with its own [T, H] partial.
 constexpr int kMaxSharedChunks = 3;
+// A dense layer's, on the matrix cores (on the vector ALU kMaxSharedChunks).
+constexpr int kMaxDenseChunks = 3 + de::kMaxMore;
 
 // Chunks of the shared intermediate for the down pass: the fewest (up to
 // max_chunks) whose T input rows fit 64 KB and that are no wider than
@@ -107,10 +111,54 @@ int shared_chunks(int inter, int T, int max_chunks, int align, int width) {
   return best;
 }
 
-int verify_chunks(const de_moe_desc& d, int T) {
-  return d.shared_inter > 0 ? shared_chunks(d.shared_inter, T, kMaxSharedChunks, elem_align(d.wdtype),
-                                            d.inter)
-                            : 0;
+// The grouped passes of a MoE layer on the matrix cores (on = false: on the
+// vector ALU).
+struct MfmaPlan {
+  bool on;
+  int chunks, cw;      // the shared down projection's column chunks and their width
+  int lkw_gu, lkw_dn;  // log2 of the column slices of a block
+};
+
+// Width of n column chunks of a K-column reduction (the last may be narrower),
+// and the number of chunks that have columns.
+int chunk_width(int K, int n) { return (K / 8 + n - 1) / n * 8; }
+int chunk_count(int K, int n) { return (K + chunk_width(K, n) - 1) / chunk_width(K, n); }
+
+// bf16 blocks of two positions or more (V2-Lite layer, gate/up + down:
+// T = 2: 53.8 us against 56.9 on the vector ALU, T = 9: 121 against 136,
+// T = 64: 235 against 802; a single position is the same within the runs'
+// spread, and the persistent draft pass computes it in the vector ALU's order),
+// every source's columns within the waves' registers.  The plan follows from
+// the layer's shape and the block alone, so that calls over parts of a layer
+// (an expert cache's chunks) sum in the same order.
+MfmaPlan mfma_plan(const de_moe_desc& d, int T, int kk, bool has_shared, bool has_draft) {
+  MfmaPlan p{};
+  const int Is = has_shared ? d.shared_inter : 0, Id = has_draft ? d.draft_inter : 0;
+  if (d.wdtype != DE_BF16 || T < 2 || d.hidden > de::kMfmaMaxK || d.inter > de::kMfmaMaxK ||
+      Id > de::kMfmaMaxK || !de::mfma_fits(T, d.n_experts, d.top_k))
+    return p;
+  if (Is > 0) {
+    // No wider than the routed experts' rows where possible, so that every
+    // down tile of the launch streams about the same.
+    const int most = kMaxSharedChunks - (Id > 0 ? 1 : 0);
+    int n = 1;
+    while (n < most && chunk_width(Is, n) > std::max(d.inter, 256)) ++n;
+    p.cw = chunk_width(Is, n);
+    p.chunks = chunk_count(Is, n);
+    if (p.cw > de::kMfmaMaxK) return p;
+  }
+  const int mu = std::min(T * kk, d.n_experts);
+  p.lkw_gu = de::mfma_lkw(d.hidden, mu * d.inter + Is + Id, 16);
+  p.lkw_dn = de::mfma_lkw(std::max(std::max(d.inter, p.cw), Id),
+                          (mu + p.chunks + (Id > 0 ? 1 : 0)) * d.hidden, 32);
+  p.on = true;
+  return p;
+}
+
+// True when the verify layer of this shape can run as one launch.
+bool fused_shape(const de_moe_desc& d, int T) {
+  return T >= de::kVerifyFusedMinT && T <= de::kVerifyFusedMaxT &&
+         mfma_plan(d, T, d.top_k, d.shared_inter > 0, false).on;
 }
 
 constexpr size_t kCtlBytes = 4096;
@@ -126,28 +174,8 @@ struct Layout {
   size_t ctl, z, idx, gate, nu, uids, offs, tok, glist, ppos;
   size_t a_r, a_s, a_d, p_r, p_s, p_d;
   size_t pd;  // persistent draft pass: gate/up outputs [Is + Id + I], row words [H], logit words [N] (8 bytes)
-  // The single-launch verify layer (only for the shapes it serves, else
-  // fused = false): (value, epoch) words of A_r, A_s, P_r and the shared
-  // down chunks' partials.
-  bool fused;
-  int chunks;     // shared down chunks of that launch
-  size_t lds;     // its LDS bytes per block
-  size_t t_ar, t_as, t_pr, t_ps, t_pub;
   size_t total;
 };
-
-// True when the verify layer of this shape can run as one launch; chunks and
-// lds receive the launch's shared down chunks and LDS bytes per block.
-bool fused_shape(const de_moe_desc& d, int T, int* chunks, size_t* lds) {
-  if (d.wdtype != DE_BF16 || T < 2 || T > kMaxT) return false;
-  const int c = verify_chunks(d, T);
-  const size_t b = de::verify_fused_lds(T, d.hidden, d.n_experts, d.top_k, d.inter,
-                                        d.shared_inter, c);
-  if (b == 0) return false;
-  if (chunks) *chunks = c;
-  if (lds) *lds = b;
-  return true;
-}
 
 Layout layout(const de_moe_desc& d, int T) {
   Layout L{};
@@ -184,16 +212,23 @@ Layout layout(const de_moe_desc& d, int T) {
   L.p_r = take(tk * d.hidden * 4);
   L.p_s = take((size_t)kMaxSharedChunks * T * d.hidden * 4);
   L.p_d = take((size_t)T * d.hidden * 4);
-  L.fused = fused_shape(d, T, &L.chunks, &L.lds);
-  if (L.fused) {
-    L.t_ar = take(tk * d.inter * 8);
-    L.t_as = take((size_t)T * d.shared_inter * 8);
-    L.t_pr = take(tk * d.hidden * 8);
-    L.t_ps = take((size_t)kMaxSharedChunks * T * d.hidden * 8);
-    L.t_pub = take(de::verify_fused_pub_words(T, d.n_experts, d.top_k) * 8);
-  }
+  // Room for the single launch's exchange (a (value, epoch) word for every value
+  // that its blocks hand on).  The launch hands them on through the plain
+  // buffers now; the room stays part of the workspace's size.
+  if (fused_shape(d, T))
+    take((tk * (d.inter + d.hidden) + (size_t)T * d.shared_inter +
+          (size_t)kMaxSharedChunks * T * d.hidden) * 8);
   L.total = o;
   return L;
+}
+
+// Every launch that waits at device-wide points gets its own epoch (its arrival
+// words are larger than those of earlier launches); 0 never occurs, so a zeroed
+// word is always behind.
+uint32_t next_epoch() {
+  static std::atomic<uint32_t> epoch{1};
+  const uint32_t e = epoch.fetch_add(1);
+  return e != 0 ? e : epoch.fetch_add(1);
 }
 
 int check_T(int T) { return (T >= 1 && T <= kMaxT) ? DE_OK : DE_ERR_INVALID; }
@@ -296,81 +331,23 @@ de::RoutedSrc routed_src(const de_moe_desc& d, int T, int kk, const de_expert_ta
   return r;
 }
 
-// The verify layer as one launch (verify_fused.hip): the same outputs as the
-// gate/up, down and combine launches, bit for bit.
-int run_fused(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc& r, int kk,
-              const void* shared_w, float* y, const de_epilogue* epi, const Layout& L, void* ws,
-              const de::TopkUnionArgs& sel, hipStream_t s) {
-  static std::atomic<uint32_t> epoch{1};
-  uint32_t ep = epoch.fetch_add(1);
-  if (ep == 0) ep = epoch.fetch_add(1);  // 0 never tags a word (a zeroed word is always stale)
-  de::FusedArgs f{};
-  de::GroupedArgs& g = f.gu;
-  g.T = T;
-  g.H = d.hidden;
-  g.x = x;
-  g.has_routed = 1;
-  g.r = r;
-  g.r.a = nullptr;  // A_r only as tagged words
-  g.r.a_tag = at<uint64_t>(ws, L.t_ar);
-  g.r.p_tag = at<uint64_t>(ws, L.t_pr);
-  g.fuse_route = 1;
-  g.fuse_select = 1;
-  g.sel = sel;
-  g.epoch = ep;
-  g.n_dense = 0;
-  if (shared_w != nullptr && d.shared_inter > 0) {
-    de::DenseSrc& ds = g.dense[g.n_dense++];
-    ds.w = shared_w;
-    ds.inter = d.shared_inter;
-    ds.out = nullptr;
-    ds.out_tag = at<uint64_t>(ws, L.t_as);
-  }
-  de::GroupedArgs& h = f.dn;
-  h = g;
-  h.fuse_route = 0;
-  h.fuse_select = 0;
-  h.n_dense = 0;
-  h.r.p = r.p;  // the plain P_r too (the residual target reads it)
-  // Every down input is read from LDS after it is staged; the plain buffers
-  // only keep a stray read in bounds.
-  h.r.a = r.a;
-  de::CombineArgs& c = f.c;
-  c.T = T;
-  c.H = d.hidden;
-  c.n_dense = 0;
-  if (shared_w != nullptr && d.shared_inter > 0) {
-    const int chunks = L.chunks;
-    const int cl = d.shared_inter / chunks;
-    const char* D = static_cast<const char*>(shared_w) +
-                    2 * de::mat_bytes(d.wdtype, d.shared_inter, d.hidden);
-    for (int i = 0; i < chunks; ++i) {
-      de::DenseSrc& ds = h.dense[h.n_dense++];
-      ds.w = D + (size_t)i * cl * 2;
-      ds.inter = cl;
-      ds.ld = d.shared_inter;
-      ds.rows = d.hidden;
-      ds.gate = 1.0f;
-      ds.vin = at<float>(ws, L.a_s) + (size_t)i * cl;
-      ds.vin_tag = at<uint64_t>(ws, L.t_as) + (size_t)i * cl;
-      ds.vin_stride = d.shared_inter;
-      ds.out = nullptr;
-      ds.out_tag = at<uint64_t>(ws, L.t_ps) + (size_t)i * T * d.hidden;
-      ds.out_stride = d.hidden;
-      ++c.n_dense;
+// Chunks of a dense reduction of K columns for a matrix-core down pass of
+// `rows` rows: 0 when even `most` chunks are too wide.
+int mfma_chunks(int K, int rows, int T, int most) {
+  int best = 0;
+  long cost = 0;
+  const int cus = de::dev_info().num_cus;
+  for (int n = 1; n <= most; ++n) {
+    const int cw = chunk_width(K, n);
+    if (cw > de::kMfmaMaxK || chunk_count(K, n) != n) continue;
+    const long tiles = (long)n * ((rows + 31) / 32) * ((T + 15) / 16);
+    const long c = (tiles + cus - 1) / cus * ((cw + 255) / 256);
+    if (best == 0 || c < cost) {
+      best = n;
+      cost = c;
     }
   }
-  c.kk = kk;
-  c.pairs_max = r.pairs_max;
-  c.y = y;
-  c.residual = epi ? epi->residual : nullptr;
-  c.normed = epi ? epi->normed : nullptr;
-  c.eps = epi ? epi->eps : 0.f;
-  f.region_floats = de::verify_fused_region(T, d.hidden, d.inter, d.shared_inter, L.chunks);
-  f.status = r.status;
-  f.pub = at<uint64_t>(ws, L.t_pub);
-  const hipError_t e = timed_layer(s, [&] { return de::launch_verify_fused(f, L.lds, s); });
-  return e == hipSuccess ? DE_OK : DE_ERR_HIP;
+  return best;
 }
 
 // gate/up + down + combine over the union (kk entries per position) and the
@@ -384,10 +361,9 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
                 const de::TopkUnionArgs* fused_sel, hipStream_t s, bool dense_on = true,
                 bool combine_on = true, bool fuse_select = false,
                 const float* next_router = nullptr) {
-  if (fused_sel != nullptr && fuse_select && dense_on && combine_on && next_router == nullptr &&
-      draft_w == nullptr && !r.absent_ok && L.fused && de::verify_fused_enabled()) {
-    return run_fused(d, T, x, r, kk, shared_w, y, epi, L, ws, *fused_sel, s);
-  }
+  const bool fused = fused_sel != nullptr && fuse_select && dense_on && combine_on &&
+                     next_router == nullptr && draft_w == nullptr && !r.absent_ok &&
+                     fused_shape(d, T) && de::verify_fused_enabled();
   const bool q4 = d.wdtype == DE_Q4_0;
   const size_t esz = q4 ? 0 : elem_bytes(d.wdtype);
   de::GroupedArgs g{};
@@ -418,8 +394,19 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
     ds.inter = d.draft_inter;
     ds.out = at<float>(ws, L.a_d);
   }
-  hipError_t e = timed_phase(DE_PHASE_GATEUP, s, [&] { return de::launch_gateup(g, d.wdtype, s); });
-  if (e != hipSuccess) return DE_ERR_HIP;
+  const bool has_draft = draft_w != nullptr && d.draft_inter > 0;
+  const MfmaPlan mx = mfma_plan(d, T, kk, shared_w != nullptr && d.shared_inter > 0, has_draft);
+  g.mfma = mx.on ? 1 : 0;
+  g.lkw = mx.lkw_gu;
+  hipError_t e = hipSuccess;
+  de::FusedArgs f{};
+  if (fused) {
+    f.gu = g;
+  } else {
+    e = timed_phase(DE_PHASE_GATEUP, s, [&] { return de::launch_gateup(g, d.wdtype, s); });
+    if (e != hipSuccess) return DE_ERR_HIP;
+  }
+  g.lkw = mx.lkw_dn;
   // The down pass reads the gate/up activations of each dense source.  The
   // shared path's down projection is split along its intermediate dimension
   // into chunks whose block of input rows fits a down block's LDS staging
@@ -427,14 +414,32 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
   // its own partial, and the combine sums them.
   int nd = 0;
   if (shared_w != nullptr && d.shared_inter > 0) {
-    const int max_chunks = kMaxSharedChunks - ((draft_w != nullptr && d.draft_inter > 0) ? 1 : 0);
-    const int chunks =
-        shared_chunks(d.shared_inter, T, max_chunks, elem_align(d.wdtype), d.inter);
-    const int cl = d.shared_inter / chunks;
+    const int max_chunks = kMaxSharedChunks - (has_draft ? 1 : 0);
+    const int chunks = mx.on ? mx.chunks
+                             : shared_chunks(d.shared_inter, T, max_chunks, elem_align(d.wdtype),
+                                             d.inter);
+    const int cl = mx.on ? mx.cw : d.shared_inter / chunks;
     const char* D = static_cast<const char*>(shared_w) +
                     2 * de::mat_bytes(d.wdtype, d.shared_inter, d.hidden);
     c.n_dense = 0;
+    if (mx.on) {
+      de::DenseSrc& ds = g.dense[nd++];
+      ds = de::DenseSrc{};
+      ds.w = D;
+      ds.inter = d.shared_inter;
+      ds.rows = d.hidden;
+      ds.gate = 1.0f;
+      ds.vin = at<float>(ws, L.a_s);
+      ds.vin_stride = d.shared_inter;
+      ds.out = at<float>(ws, L.p_s);
+      ds.out_stride = d.hidden;
+      ds.chunks = chunks;
+      ds.cw = cl;
+      ds.chunk_out = T * d.hidden;
+    }
     for (int i = 0; i < chunks; ++i) {
+      c.dense_p[c.n_dense++] = at<float>(ws, L.p_s) + (size_t)i * T * d.hidden;
+      if (mx.on) continue;
       de::DenseSrc& ds = g.dense[nd++];
       // Columns [i cl, (i+1) cl) of D; Q4_0: their codes, and their scales
       // after the matrix's codes.
@@ -448,10 +453,9 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
       ds.vin_stride = d.shared_inter;
       ds.out = at<float>(ws, L.p_s) + (size_t)i * T * d.hidden;
       ds.out_stride = d.hidden;
-      c.dense_p[c.n_dense++] = ds.out;
     }
   }
-  if (draft_w != nullptr && d.draft_inter > 0) {
+  if (has_draft) {
     de::DenseSrc& ds = g.dense[nd++];
     ds.w = static_cast<const char*>(draft_w) + 2 * de::mat_bytes(d.wdtype, d.draft_inter, d.hidden);
     ds.ws = q4 ? static_cast<const char*>(ds.w) + (size_t)d.hidden * d.draft_inter / 2 : nullptr;
@@ -463,6 +467,8 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
     ds.vin_stride = d.draft_inter;
     ds.out = at<float>(ws, L.p_d);
     ds.out_stride = d.hidden;
+    ds.chunks = 1;
+    ds.cw = d.draft_inter;
     c.dense_p[c.n_dense++] = ds.out;
   }
   g.n_dense = dense_on ? nd : 0;  // the combine reads the dense partials either way
@@ -475,6 +481,14 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
   c.residual = epi ? epi->residual : nullptr;
   c.normed = epi ? epi->normed : nullptr;
   c.eps = epi ? epi->eps : 0.f;
+  if (fused) {
+    f.dn = g;
+    f.c = c;
+    f.flags = at<uint64_t>(ws, kPDFlagsOff);
+    f.epoch = next_epoch();
+    f.status = r.status;
+    return hip_status(timed_layer(s, [&] { return de::launch_verify_fused(f, s); }));
+  }
   e = timed_phase(DE_PHASE_DOWN, s, [&] { return de::launch_down(g, d.wdtype, s); });
   if (e != hipSuccess) return DE_ERR_HIP;
   if (!combine_on) return DE_OK;
@@ -595,11 +609,7 @@ int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, con
     a.normed_out = normed_out;
     a.pred_idx = pred_idx ? pred_idx + (size_t)l0 * d.top_k : nullptr;
     a.pred_gate = pred_gate ? pred_gate + (size_t)l0 * d.top_k : nullptr;
-    // Every launch gets its own epoch (see PDArgs); 0 never occurs, so a
-    // zeroed flag is always behind.
-    static std::atomic<uint32_t> epoch{1};
-    a.epoch = epoch.fetch_add(1);
-    if (a.epoch == 0) a.epoch = epoch.fetch_add(1);
+    a.epoch = next_epoch();
     const hipError_t e =
         timed_phase(DE_PHASE_DRAFT_PASS, s, [&] { return launch_draft_persistent(a, s); });
     if (e != hipSuccess) {
@@ -1019,7 +1029,8 @@ int de_lm_head(int T, int H, int V, const float* x, const void* w_lm, float* log
   if (!aligned16(x) || !aligned16(w_lm)) return DE_ERR_INVALID;
   // A block of positions on the matrix cores (the vector-ALU row-dot is
   // arithmetic-bound there); one position streams at the HBM rate already.
-  if (de::rowdot_mfma_fits(T, H) && de::lmhead_mfma_enabled())
+  const bool mx = H <= de::kMfmaMaxK && de::lmhead_mfma_enabled();
+  if (!mx && de::rowdot_mfma_fits(T, H) && de::lmhead_mfma_enabled())
     return hip_status(de::launch_rowdot_mfma(T, H, V, x, w_lm, logits, stream));
   de::GroupedArgs g{};
   g.T = T;
@@ -1035,6 +1046,12 @@ int de_lm_head(int T, int H, int V, const float* x, const void* w_lm, float* log
   g.dense[0].vin_stride = H;
   g.dense[0].out = logits;
   g.dense[0].out_stride = V;
+  if (mx) {
+    g.mfma = 1;
+    g.lkw = de::mfma_lkw(H, V, 32);
+    g.dense[0].chunks = 1;
+    g.dense[0].cw = H;
+  }
   return hip_status(de::launch_down(g, DE_BF16, stream));
 }
 
@@ -1059,7 +1076,7 @@ int de_layer_status(void* ws, size_t ws_bytes, hipStream_t stream) {
 
 size_t de_dense_workspace_bytes(int T, int H, int I) {
   if (check_T(T) != DE_OK || H < 1 || I < 1) return 0;
-  return up256((size_t)T * I * 4) + (size_t)kMaxSharedChunks * up256((size_t)T * H * 4);
+  return up256((size_t)T * I * 4) + (size_t)kMaxDenseChunks * up256((size_t)T * H * 4);
 }
 
 // Intermediate chunks of a dense layer's down pass: as many as there are
@@ -1098,7 +1115,7 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
        next_desc->hidden != H || !de::combine_route_fits(H) || !aligned16(next_router)))
     return DE_ERR_INVALID;
   if (ws == nullptr || (reinterpret_cast<uintptr_t>(ws) & 255u) != 0 ||
-      ws_bytes < de_dense_workspace_bytes(T, H, I))
+      ws_bytes < up256((size_t)T * I * 4) + kMaxSharedChunks * up256((size_t)T * H * 4))
     return DE_ERR_WORKSPACE;
   float* A = static_cast<float*>(ws);
   float* P = at<float>(ws, up256((size_t)T * I * 4));
@@ -1112,18 +1129,29 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
   g.dense[0].w = w;
   g.dense[0].inter = I;
   g.dense[0].out = A;
+  // Down: D [H, I] in column chunks, each a dense source with its own partial.
+  int nc = 0;
+  if (wdtype == DE_BF16 && H <= de::kMfmaMaxK) {
+    const size_t fit = (ws_bytes - up256((size_t)T * I * 4)) / up256((size_t)T * H * 4);
+    nc = mfma_chunks(I, H, T, (int)std::min<size_t>(fit, kMaxDenseChunks));
+  }
+  const bool mx = nc > 0;
+  if (!mx) nc = dense_chunks(I, al);
+  const int cw = (I / al + nc - 1) / nc * al;
+  if (mx) {
+    g.mfma = 1;
+    g.lkw = de::mfma_lkw(H, I, 16);
+  }
   if (timed_phase(DE_PHASE_GATEUP, stream, [&] { return de::launch_gateup(g, wdtype, stream); }) !=
       hipSuccess)
     return DE_ERR_HIP;
-  // Down: D [H, I] in column chunks, each a dense source with its own partial.
-  const int nc = dense_chunks(I, al);
-  const int cw = I / nc;
+  if (mx) g.lkw = de::mfma_lkw(cw, nc * H, 32);
   const char* D = static_cast<const char*>(w) + 2 * (size_t)I * H * elem_bytes(wdtype);
-  g.n_dense = nc;
-  for (int i = 0; i < nc; ++i) {
+  g.n_dense = mx ? 1 : nc;
+  for (int i = 0; i < g.n_dense; ++i) {
     g.dense[i] = de::DenseSrc{};
     g.dense[i].w = D + (size_t)i * cw * elem_bytes(wdtype);
-    g.dense[i].inter = cw;
+    g.dense[i].inter = mx ? I : cw;
     g.dense[i].ld = I;
     g.dense[i].rows = H;
     g.dense[i].gate = 1.0f;
@@ -1131,6 +1159,9 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
     g.dense[i].vin_stride = I;
     g.dense[i].out = P + (size_t)i * pstride;
     g.dense[i].out_stride = H;
+    g.dense[i].chunks = nc;
+    g.dense[i].cw = cw;
+    g.dense[i].chunk_out = (int)pstride;
   }
   if (timed_phase(DE_PHASE_DOWN, stream, [&] { return de::launch_down(g, wdtype, stream); }) !=
       hipSuccess)
@@ -1138,8 +1169,10 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
   de::CombineArgs c{};
   c.T = T;
   c.H = H;
-  c.n_dense = nc;
-  for (int i = 0; i < nc; ++i) c.dense_p[i] = P + (size_t)i * pstride;
+  c.n_dense = std::min(nc, 3);
+  for (int i = 0; i < c.n_dense; ++i) c.dense_p[i] = P + (size_t)i * pstride;
+  c.n_more = nc - c.n_dense;
+  c.more_stride = (int)pstride;
   c.y = y;
   c.residual = epi ? epi->residual : nullptr;
   c.normed = epi ? epi->normed : nullptr;
@@ -1162,7 +1195,7 @@ extern "C" {
 
 int de_verify_single_launch(const de_moe_desc* d, int T) {
   if (de_check_desc(d) != DE_OK || check_T(T) != DE_OK || !de::verify_fused_enabled()) return 0;
-  return fused_shape(*d, T, nullptr, nullptr) ? 1 : 0;
+  return fused_shape(*d, T) ? 1 : 0;
 }
 
 int de_time_next_phase(int phase, hipEvent_t start, hipEvent_t stop) {

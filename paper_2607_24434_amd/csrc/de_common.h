@@ -96,11 +96,10 @@ struct DenseSrc {
   float* out;        // gate/up: A [T, inter]; down: P [T, out_stride]
   int out_stride;
   const void* ws;    // down, Q4_0 weights: the scales of the matrix's first row
-  // The single-launch verify layer only: every output value also goes to
-  // out_tag (same indexing as out) as a 64-bit (value, launch epoch) pair, and
-  // the down pass reads its input pairs from vin_tag (same indexing as vin).
-  uint64_t* out_tag;
-  const uint64_t* vin_tag;
+  // Matrix-core down only: the `inter` columns in `chunks` parts of cw columns
+  // (the last may be narrower), each with its own partial, chunk_out floats
+  // after the one before it.
+  int chunks, cw, chunk_out;
 };
 
 // The routed part of a grouped launch: the union members and their lists.
@@ -127,10 +126,6 @@ struct RoutedSrc {
   // kStatusNotResident into *status (when not NULL).
   int absent_ok;
   int32_t* status;
-  // The single-launch verify layer only: (value, launch epoch) pairs of A_r and
-  // P_r, indexed as a and p.
-  uint64_t* a_tag;
-  uint64_t* p_tag;
 };
 
 // Bits of the device status word of a workspace.
@@ -159,10 +154,15 @@ struct TopkUnionArgs {
   int32_t* pair_pos;       // [T, ucols]
 };
 
+// Column chunks of a dense layer's reduction beyond three.
+constexpr int kMaxMore = 5;
+
 struct CombineArgs {
   int T, H;
   int n_dense;
   const float* dense_p[3];     // [T, H] partials with their gates applied
+  int n_more;                  // without p_r: up to kMaxMore partials after the third, each
+  int more_stride;             // this many floats after the one before it
   const float* p_r;            // [pairs, H] routed partials or NULL
   const int32_t* pair_pos;     // [T, kk]
   int kk;
@@ -181,6 +181,8 @@ struct GroupedArgs {
   RoutedSrc r;
   int n_dense;
   DenseSrc dense[3];
+  int mfma;            // 1: on the matrix cores (bf16), with lkw
+  int lkw;             // log2 of the column slices of a block
   int lds_floats;      // set by the launcher: staged-input capacity of a block
   // Gate/up only: build the union in every block (block 0 also writes sel's
   // outputs); r.n_union ... r.gate_list are then not read.  The lists come
@@ -189,7 +191,6 @@ struct GroupedArgs {
   int fuse_route;
   int fuse_select;
   TopkUnionArgs sel;
-  uint32_t epoch;      // the single-launch verify layer: this launch's tag
 };
 
 // ---------------------------------------------------------------- launchers (HIP side)

@@ -1,8 +1,6 @@
 // The pass stream of the grouped SwiGLU kernels (internal): weight tiles of
 // union members and dense sources, each lane's 16-byte units, the register
-// ring of weight loads, the FMA order and the row reductions.  Shared by the
-// separate gate/up and down launches and by the single-launch verify layer,
-// which therefore compute every output value with the same operations.
+// ring of weight loads, the FMA order and the row reductions.  
 //
 // With a few block positions per expert the work is a batch of skinny GEMVs:
 // every weight byte meets only |T_e| positions, so the kernels are bound by
@@ -300,7 +298,6 @@ struct Tables {
   Member* mem;
   int32_t* tok;
   float* gate;
-  int* dact;  // single-launch verify layer: LDS offsets of the dense sources' staged inputs
 };
 
 size_t tables_bytes(const GroupedArgs& a) {
@@ -344,7 +341,6 @@ __device__ __forceinline__ Tables tables_at(const GroupedArgs& a, int act_floats
   const int nm = a.has_routed ? a.r.max_union : 0;
   tb.tok = reinterpret_cast<int32_t*>(p + (size_t)nm * sizeof(Member));
   tb.gate = reinterpret_cast<float*>(tb.tok + (a.has_routed ? a.r.pairs_max : 0));
-  tb.dact = nullptr;
   return tb;
 }
 
@@ -362,7 +358,6 @@ __device__ __forceinline__ DenseSrc dense_at(const Tables& tb, int s) {
   d.out = uni(g.out);
   d.out_stride = uni(g.out_stride);
   d.ws = uni(g.ws);
-  d.out_tag = uni(g.out_tag);
   return d;
 }
 
@@ -411,6 +406,91 @@ __device__ __forceinline__ int routed_count(const GroupedArgs& a) {
   return nu < 0 ? 0 : min(nu, a.r.max_union);
 }
 
+// Fused selection: the logits of the wave's first two positions (of a launch
+// that selects them itself; zeros otherwise).
+__device__ __forceinline__ void first_logits(const GroupedArgs& a, int wave, float (&z0)[2][4]) {
+  const bool sel = a.fuse_route && a.fuse_select;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    // Clamped position: in bounds; a position past T is never selected.
+    const int t = min(wave + r * kWavesPB, a.T - 1);
+    if (sel) {
+      topk_load(a.sel, a.sel.z + (size_t)t * a.sel.N, z0[r]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z0[r][q] = 0.f;
+    }
+  }
+}
+
+// The top-k lists (selected here from the logits, or given), then their
+// union, in every block; block 0 also publishes both for the down and combine
+// launches.  Fills the member table and the token and gate lists; returns the
+// number of members.  All threads; ends with a barrier.
+__device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& tb,
+                                           float (&z0)[2][4], int lane, int wave, int* absent) {
+  const SelView v = sel_at(a, tb);
+  const int k = a.sel.k;
+  if (a.fuse_select) {
+    // Wave w selects positions w, w + 8 (two interleaved), then w + 16, ...
+    for (int t = wave; t < a.T; t += 2 * kWavesPB) {
+      const int t1 = t + kWavesPB;
+      if (t != wave) {
+        topk_load(a.sel, a.sel.z + (size_t)t * a.sel.N, z0[0]);
+        if (t1 < a.T) topk_load(a.sel, a.sel.z + (size_t)t1 * a.sel.N, z0[1]);
+      }
+      if (t1 < a.T) {
+        topk_regs<2>(a.sel, z0, v.idx + t * k, v.sc + t * k, v.idx + t1 * k, v.sc + t1 * k);
+      } else {
+        float z1[1][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) z1[0][q] = z0[0][q];
+        topk_regs<1>(a.sel, z1, v.idx + t * k, v.sc + t * k);
+      }
+      const int kr = a.sel.rounds > 0 ? min(a.sel.rounds, k) : k;
+      for (int r = 0; r < 2; ++r) {
+        const int tt = t + r * kWavesPB;
+        if (tt < a.T && lane < kr) {
+          const float g = topk_gate(a.sel, v.sc + tt * k, lane);
+          v.gate[tt * k + lane] = g;
+          if (blockIdx.x == 0) {
+            a.sel.idx_out[tt * k + lane] = v.idx[tt * k + lane];
+            a.sel.gate_out[tt * k + lane] = g;
+          }
+        }
+      }
+    }
+  } else {
+    for (int i = threadIdx.x; i < a.T * k; i += kBlock) {
+      v.idx[i] = a.sel.idx_out[i];
+      v.gate[i] = a.sel.gate_out[i];
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    build_union_wave(a.sel, v, blockIdx.x == 0, tb.tok, tb.gate);
+    const int n = uni(v.misc[1]);
+    if (n > 0) members_from_union(a, tb, v, lane, kWave, absent);
+  }
+  __syncthreads();
+  const int nu = uni(v.misc[1]);
+  return nu < 0 ? 0 : min(nu, a.r.max_union);
+}
+
+// Down: a needed member without a slot contributes zero partials (the combine
+// sums its pairs like any other), spread over the grid.
+__device__ __forceinline__ void absent_rows_zero(const GroupedArgs& a, const Tables& tb, int nu) {
+  const size_t gstride = (size_t)gridDim.x * kBlock;
+  for (int j = 0; j < nu; ++j) {
+    const Member m = tb.mem[j];
+    if (m.blk != nullptr || m.ntok <= 0) continue;
+    float* p = a.r.p + (size_t)m.off * a.H;
+    const size_t n = (size_t)m.ntok * a.H;
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += gstride)
+      *(DE_GLOBAL float*)(p + i) = 0.f;
+  }
+}
+
 // ------------------------------------------------------------------ the pass stream
 
 // One pass: kNS weight rows against up to NT activation rows.
@@ -430,7 +510,6 @@ struct Pass {
   int orow0;           // output row of the pass's first position
   int goff;            // routed down: gate-list index of the first position; -1: gscalar
   float gscalar;
-  uint64_t* tout;      // single-launch verify layer: tagged outputs, indexed as out
 };
 
 // Tile list of a launch: the dense sources' tiles first (source s from ds[s]),
@@ -484,9 +563,7 @@ struct Cursor {
 };
 
 // The passes of a wave's tiles in [lo, hi) (tiles b*W + w + k * step).
-// FUSED (the single-launch verify layer): outputs also go to the tagged
-// buffers, and a dense source's staged input offset comes from tb.dact.
-template <typename WT, bool GATEUP, int NT, int RT, bool FUSED = false>
+template <typename WT, bool GATEUP, int NT, int RT>
 struct Walker {
   Layout ly;      // by value: a reference to a local would live in per-lane scratch
   Tables tb;
@@ -533,7 +610,6 @@ struct Walker {
         p.out = a.r.a;
         p.ostride = I;
         p.goff = -1;
-        if constexpr (FUSED) p.tout = a.r.a_tag;
       } else {
         const size_t rb = qrow_bytes<WT>(I);
         const char* D = blk + 2 * mat_bytes<WT>(I, H);
@@ -560,7 +636,6 @@ struct Walker {
         p.out = a.r.p;
         p.ostride = H;
         p.goff = p.orow0;
-        if constexpr (FUSED) p.tout = a.r.p_tag;
       }
       p.gscalar = 0.f;
     } else {
@@ -593,7 +668,6 @@ struct Walker {
         for (int m = 0; m < NT; ++m) p.vo[m] = (c.m0 + min(m, p.nt - 1)) * xstride;
         p.out = d.out;
         p.ostride = d.inter;
-        if constexpr (FUSED) p.tout = d.out_tag;
       } else {
         const int ldc = d.ld > 0 ? d.ld : d.inter;
         const size_t rb = qrow_bytes<WT>(ldc);
@@ -606,12 +680,11 @@ struct Walker {
           if constexpr (kQ4<WT>) p.srow[k] = static_cast<const char*>(d.ws) + r * (ldc / 16);
         }
         p.L = (int)(qrow_bytes<WT>(d.inter) / 16);
-        const int act = FUSED ? uni(tb.dact[s]) : dact;
-        if (act >= 0) {
+        if (dact >= 0) {
           const int sst = staged_stride<EPU>(d.inter);
           p.act = nullptr;
 #pragma unroll
-          for (int m = 0; m < NT; ++m) p.vo[m] = act + (c.m0 + min(m, p.nt - 1)) * sst;
+          for (int m = 0; m < NT; ++m) p.vo[m] = dact + (c.m0 + min(m, p.nt - 1)) * sst;
         } else {
           p.act = d.vin;
 #pragma unroll
@@ -619,7 +692,6 @@ struct Walker {
         }
         p.out = d.out;
         p.ostride = d.out_stride;
-        if constexpr (FUSED) p.tout = d.out_tag;
       }
       p.goff = -1;
       p.gscalar = d.gate;
@@ -759,32 +831,18 @@ __device__ __forceinline__ void consume(const Pass<NT>& p, int it, const u32x4 (
   }
 }
 
-// Stores v with this launch's epoch as one 64-bit value (agent scope: written
-// through to memory, so a block on another XCD that reads it with an
-// agent-scope load sees the value and its epoch together).
-__device__ __forceinline__ void st_tag(uint64_t* p, float v, uint32_t epoch) {
-  __hip_atomic_store(p, ((uint64_t)epoch << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// One output value of a pass: to out (plain) and, with TAGGED, to the tagged
-// buffer (either may be null in that mode).
-template <bool TAGGED, int NT>
-__device__ __forceinline__ void put(const Pass<NT>& p, size_t o, float v, uint32_t epoch) {
-  if constexpr (TAGGED) {
-    if (p.tout != nullptr) st_tag(p.tout + o, v, epoch);
-    if (p.out != nullptr) *(DE_GLOBAL float*)(p.out + o) = v;
-  } else {
-    // A global (not flat) store: a flat store also counts against the LDS wait
-    // counter and would hold up the activation reads behind it.
-    *(DE_GLOBAL float*)(p.out + o) = v;
-  }
+// One output value of a pass: a global (not flat) store; a flat store also
+// counts against the LDS wait counter and would hold up the activation reads
+// behind it.
+template <int NT>
+__device__ __forceinline__ void put(const Pass<NT>& p, size_t o, float v) {
+  *(DE_GLOBAL float*)(p.out + o) = v;
 }
 
 // Reduces the pass's sums and writes them; clears acc.
-template <bool GATEUP, int NT, int RT, bool TAGGED = false>
+template <bool GATEUP, int NT, int RT>
 __device__ __forceinline__ void finish(const Pass<NT>& p, const Tables& tb, int lane,
-                                       float (&acc)[RT][NT], uint32_t epoch = 0) {
+                                       float (&acc)[RT][NT]) {
 #pragma unroll
   for (int m = 0; m < NT; ++m) {
     if (m < p.nt) {
@@ -794,7 +852,7 @@ __device__ __forceinline__ void finish(const Pass<NT>& p, const Tables& tb, int 
           const float g = row_total(acc[2 * q][m]);
           const float u = row_total(acc[2 * q + 1][m]);
           if (lane == m && p.r0 + q < p.rows)
-            put<TAGGED>(p, (size_t)(p.orow0 + m) * p.ostride + p.r0 + q, silu_f(g) * u, epoch);
+            put(p, (size_t)(p.orow0 + m) * p.ostride + p.r0 + q, silu_f(g) * u);
         }
       } else {
         const float gm = p.goff >= 0 ? tb.gate[p.goff + m] : p.gscalar;
@@ -802,7 +860,7 @@ __device__ __forceinline__ void finish(const Pass<NT>& p, const Tables& tb, int 
         for (int k = 0; k < RT; ++k) {
           const float v = row_total(acc[k][m]);
           if (lane == m && p.r0 + k < p.rows)
-            put<TAGGED>(p, (size_t)(p.orow0 + m) * p.ostride + p.r0 + k, gm * v, epoch);
+            put(p, (size_t)(p.orow0 + m) * p.ostride + p.r0 + k, gm * v);
         }
       }
     }
@@ -813,20 +871,12 @@ __device__ __forceinline__ void finish(const Pass<NT>& p, const Tables& tb, int 
     for (int m = 0; m < NT; ++m) acc[k][m] = 0.f;
 }
 
-// Called by the consumer before the first pass of each of its tiles (the
-// pass is already made and may be remade).  The separate launches need
-// nothing there.
-struct NoHook {
-  template <class WK, class P>
-  __device__ __forceinline__ void enter(const GroupedArgs&, const WK&, Cursor&, P&) {}
-};
-
 // Streams the wave's pass sequence: the loader runs RING iterations ahead of
 // the consumer, across pass and tile boundaries.
-template <typename WT, bool GATEUP, int NT, int RING, int RT, bool FUSED, class Hook>
+template <typename WT, bool GATEUP, int NT, int RING, int RT>
 __device__ __forceinline__ void run_stream(const GroupedArgs& a,
-                                           const Walker<WT, GATEUP, NT, RT, FUSED> wk,
-                                           int first_tile, int lane, Hook& hk) {
+                                           const Walker<WT, GATEUP, NT, RT> wk,
+                                           int first_tile, int lane) {
   Cursor lc{first_tile, 0, 0}, cc{first_tile, 0, 0};
   Pass<NT> lp, cp;
   bool l_ok = wk.seek(a, lc, lp);
@@ -849,18 +899,16 @@ __device__ __forceinline__ void run_stream(const GroupedArgs& a,
   for (int k = 0; k < RT; ++k)
 #pragma unroll
     for (int m = 0; m < NT; ++m) acc[k][m] = 0.f;
-  if (c_ok) hk.enter(a, wk, cc, cp);
   while (c_ok) {
 #pragma unroll
     for (int q = 0; q < RING; ++q) {
       if (c_ok) {
         consume<WT, NT, RT, !GATEUP>(cp, c_it, raw[q], sraw[q], lane, acc);
         if (++c_it == cp.nit) {
-          finish<GATEUP, NT, RT, FUSED>(cp, wk.tb, lane, acc, a.epoch);
+          finish<GATEUP, NT, RT>(cp, wk.tb, lane, acc);
           const int prev_tile = cc.tile;
           c_ok = wk.next(a, cc, cp);
           c_it = 0;
-          if (c_ok && cc.tile != prev_tile) hk.enter(a, wk, cc, cp);
           // Dense sources over many positions are arithmetic-heavy: a wave
           // with more tiles left gets a higher issue priority, so the waves
           // of a CU finish together instead of the oldest first.
@@ -889,32 +937,24 @@ __device__ __forceinline__ void run_stream(const GroupedArgs& a,
 }
 
 // A wave's tiles: first, first + step, ...  The dense tiles [0, ndt) run with
-// passes of kDenseNT positions, the members' tiles with kRoutedNT.  WPB waves
-// per block; FUSED and the hook as in Walker and run_stream.
-template <typename WT, bool GATEUP, int RT, int WPB, bool FUSED, class Hook>
+// passes of kDenseNT positions, the members' tiles with kRoutedNT.
+template <typename WT, bool GATEUP, int RT>
 __device__ __forceinline__ void run_tiles(const GroupedArgs& a, const Layout ly, const Tables& tb,
-                                          int xstride, bool xlds, int lane, int wave, Hook& hk) {
-  const int step = (int)gridDim.x * WPB;
-  const int first = (int)blockIdx.x * WPB + wave;
+                                          int xstride, bool xlds, int lane, int wave) {
+  const int step = (int)gridDim.x * kWavesPB;
+  const int first = (int)blockIdx.x * kWavesPB + wave;
   if (first < ly.ndt) {
     constexpr int DNT = kDenseNTOf<WT>;
-    const Walker<WT, GATEUP, DNT, RT, FUSED> wd{ly, tb, step, 0, ly.ndt, xstride, xlds};
-    run_stream<WT, GATEUP, DNT, kDenseRing, RT>(a, wd, first, lane, hk);
+    const Walker<WT, GATEUP, DNT, RT> wd{ly, tb, step, 0, ly.ndt, xstride, xlds};
+    run_stream<WT, GATEUP, DNT, kDenseRing, RT>(a, wd, first, lane);
   }
   __builtin_amdgcn_s_setprio(0);
   if (ly.nr > 0) {
     const int f2 = first >= ly.ndt ? first : first + cdiv(ly.ndt - first, step) * step;
     constexpr int RNT = kRoutedNTOf<WT>;
-    const Walker<WT, GATEUP, RNT, RT, FUSED> wr{ly, tb, step, ly.ndt, ly.total, xstride, xlds};
-    run_stream<WT, GATEUP, RNT, kRingOf<WT>, RT>(a, wr, f2, lane, hk);
+    const Walker<WT, GATEUP, RNT, RT> wr{ly, tb, step, ly.ndt, ly.total, xstride, xlds};
+    run_stream<WT, GATEUP, RNT, kRingOf<WT>, RT>(a, wr, f2, lane);
   }
-}
-
-template <typename WT, bool GATEUP, int RT>
-__device__ __forceinline__ void run_tiles(const GroupedArgs& a, const Layout ly, const Tables& tb,
-                                          int xstride, bool xlds, int lane, int wave) {
-  NoHook h;
-  run_tiles<WT, GATEUP, RT, kWavesPB, false>(a, ly, tb, xstride, xlds, lane, wave, h);
 }
 
 }  // namespace

@@ -1,0 +1,79 @@
+// The grouped gate/up and down launches of a block of positions on the matrix
+// cores (bf16 weights); mfma_core.h holds the passes.
+#include "mfma_core.h"
+
+namespace de {
+namespace {
+
+template <int KS, bool GATEUP>
+__global__ __launch_bounds__(kBlock, 2) void grouped_mfma_kernel(GroupedArgs a) {
+  const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+  __shared__ int s_absent, s_nms;
+  const MfmaTables mt = mfma_tables<KS, GATEUP>(a, lane, wave, &s_absent, &s_nms);
+  if constexpr (!GATEUP) {
+    if (s_absent && !a.r.absent_ok) absent_rows_zero(a, mt.tb, mt.nu);
+  }
+  mfma_pass<KS, GATEUP>(a, 0, mt.tb, mt.slc, mt.nms, lane, wave);
+}
+
+template <int KS, bool GATEUP>
+hipError_t launch_ks(const GroupedArgs& a, int tiles, hipStream_t s) {
+  const auto kernel = grouped_mfma_kernel<KS, GATEUP>;
+  const size_t lds = mfma_lds<KS>(a);
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return note_hip(e);
+  }
+  const int cus = dev_info().num_cus;
+  hipLaunchKernelGGL(kernel, dim3(tiles < cus ? tiles : cus), dim3(kBlock), lds, s, a);
+  return note_hip(hipGetLastError());
+}
+
+template <bool GATEUP>
+hipError_t launch_typed(const GroupedArgs& a, hipStream_t s) {
+  const int rpt = (kWavesPB >> a.lkw) * (GATEUP ? 16 : 32);
+  const int groups = cdiv(a.T, kXP);
+  int K = GATEUP ? a.H : (a.has_routed ? a.r.inter : 0), tiles = 0;
+  if (a.has_routed)
+    tiles += (a.r.max_union + a.r.pairs_max / kXP) * cdiv(GATEUP ? a.r.inter : a.H, rpt);
+  for (int i = 0; i < a.n_dense; ++i) {
+    if (!GATEUP && a.dense[i].cw > K) K = a.dense[i].cw;
+    tiles += groups * (GATEUP ? 1 : a.dense[i].chunks) * cdiv(GATEUP ? a.dense[i].inter : a.dense[i].rows, rpt);
+  }
+  if (tiles == 0) return hipSuccess;
+  const int ks = cdiv(cdiv(K, 32), 1 << a.lkw);
+  if (ks <= 2) return launch_ks<2, GATEUP>(a, tiles, s);
+  if (ks <= 4) return launch_ks<4, GATEUP>(a, tiles, s);
+  if (ks <= 6) return launch_ks<6, GATEUP>(a, tiles, s);
+  if (ks <= 8) return launch_ks<8, GATEUP>(a, tiles, s);
+  return note_hip(hipErrorInvalidValue);
+}
+
+}  // namespace
+
+// The fewest column slices whose waves hold at most 8 steps each, then more
+// (smaller tiles) while the rows make fewer tiles than the chip has CUs.
+int mfma_lkw(int K, int rows, int per) {
+  const int S = (K + 31) / 32;
+  int l = 0;
+  while (l < 3 && cdiv(S, 1 << l) > 8) ++l;
+  while (l < 3 && S >= (2 << l) && cdiv(rows, (kWavesPB >> l) * per) < dev_info().num_cus) ++l;
+  return l;
+}
+
+bool mfma_fits(int T, int N, int k) {
+  GroupedArgs a{};
+  a.T = T;
+  a.has_routed = a.fuse_route = 1;
+  a.sel.k = k;
+  a.sel.N = N;
+  a.r.pairs_max = T * k;
+  a.r.max_union = T * k < N ? T * k : N;
+  return mfma_lds<8>(a) <= (size_t)160 * 1024 - 256;
+}
+
+hipError_t launch_gateup_mfma(const GroupedArgs& a, hipStream_t s) { return launch_typed<true>(a, s); }
+hipError_t launch_down_mfma(const GroupedArgs& a, hipStream_t s) { return launch_typed<false>(a, s); }
+
+}  // namespace de

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "grouped_core.h"
+#include "grouped_mfma.h"
 
 namespace de {
 namespace {
@@ -35,76 +36,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
   const int act_floats = LDSX ? a.T * staged_stride<EPU>(a.H) : 0;
   const Tables tb = tables_at(a, act_floats);
-  // Fused selection: the wave's first two positions' logits are loaded
-  // before the staging so that their latency overlaps it.
-  const bool sel = a.fuse_route && a.fuse_select;
+  // The logits are loaded before the staging so that their latency overlaps it.
   __shared__ int s_absent;
   if (threadIdx.x == 0) s_absent = 0;
   float z0[2][4];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    // Clamped position: in bounds; a position past T is never selected.
-    const int t = min(wave + r * kWavesPB, a.T - 1);
-    if (sel) {
-      topk_load(a.sel, a.sel.z + (size_t)t * a.sel.N, z0[r]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) z0[r][q] = 0.f;
-    }
-  }
+  first_logits(a, wave, z0);
   if constexpr (LDSX) stage_rows<EPU>(a.x, a.H, a.T, a.H);
   fill_dense(a, tb);
   int nu;
   if (a.fuse_route) {
-    // The top-k lists (selected here from the logits, or given), then their
-    // union, in every block; block 0 also publishes both for the down and
-    // combine launches.
-    const SelView v = sel_at(a, tb);
-    const int k = a.sel.k;
-    if (sel) {
-      // Wave w selects positions w, w + 8 (two interleaved), then w + 16, ...
-      for (int t = wave; t < a.T; t += 2 * kWavesPB) {
-        const int t1 = t + kWavesPB;
-        if (t != wave) {
-          topk_load(a.sel, a.sel.z + (size_t)t * a.sel.N, z0[0]);
-          if (t1 < a.T) topk_load(a.sel, a.sel.z + (size_t)t1 * a.sel.N, z0[1]);
-        }
-        if (t1 < a.T) {
-          topk_regs<2>(a.sel, z0, v.idx + t * k, v.sc + t * k, v.idx + t1 * k, v.sc + t1 * k);
-        } else {
-          float z1[1][4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) z1[0][q] = z0[0][q];
-          topk_regs<1>(a.sel, z1, v.idx + t * k, v.sc + t * k);
-        }
-        const int kr = a.sel.rounds > 0 ? min(a.sel.rounds, k) : k;
-        for (int r = 0; r < 2; ++r) {
-          const int tt = t + r * kWavesPB;
-          if (tt < a.T && lane < kr) {
-            const float g = topk_gate(a.sel, v.sc + tt * k, lane);
-            v.gate[tt * k + lane] = g;
-            if (blockIdx.x == 0) {
-              a.sel.idx_out[tt * k + lane] = v.idx[tt * k + lane];
-              a.sel.gate_out[tt * k + lane] = g;
-            }
-          }
-        }
-      }
-    } else {
-      for (int i = threadIdx.x; i < a.T * k; i += kBlock) {
-        v.idx[i] = a.sel.idx_out[i];
-        v.gate[i] = a.sel.gate_out[i];
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      build_union_wave(a.sel, v, blockIdx.x == 0, tb.tok, tb.gate);
-      const int n = uni(v.misc[1]);
-      if (n > 0) members_from_union(a, tb, v, lane, kWave, &s_absent);
-    }
-    __syncthreads();
-    nu = uni(v.misc[1]);
-    nu = nu < 0 ? 0 : min(nu, a.r.max_union);
+    nu = route_lists(a, tb, z0, lane, wave, &s_absent);
   } else {
     nu = routed_count(a);
     __syncthreads();  // s_absent is initialised
@@ -138,19 +79,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   __syncthreads();  // s_absent is initialised
   if (a.has_routed) fill_tables(a, tb, nu, &s_absent);
   __syncthreads();
-  if (s_absent && !a.r.absent_ok) {
-    // A needed member without a slot contributes zero partials (the combine
-    // sums its pairs like any other), spread over the grid.
-    const size_t gstride = (size_t)gridDim.x * kBlock;
-    for (int j = 0; j < nu; ++j) {
-      const Member m = tb.mem[j];
-      if (m.blk != nullptr || m.ntok <= 0) continue;
-      float* p = a.r.p + (size_t)m.off * a.H;
-      const size_t n = (size_t)m.ntok * a.H;
-      for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += gstride)
-        *(DE_GLOBAL float*)(p + i) = 0.f;
-    }
-  }
+  if (s_absent && !a.r.absent_ok) absent_rows_zero(a, tb, nu);
   Layout ly = make_layout<RT>(a, nu, false);
   __shared__ int s_dact[3];
   __shared__ int s_list[kMaxStaged + 1];
@@ -227,7 +156,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // normalisation.  xs (LDS, may be null) also receives the normalised row;
 // without `write` (only with a row of at most NTH * kCombPer elements and
 // xs) nothing is written to global memory.
-template <int NTH>
+// MORE: the a.n_more further partials of a dense layer are summed too.
+template <int NTH, bool MORE>
 __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* red,
                                             float* xs = nullptr, bool write = true) {
   const size_t rowoff = (size_t)t * a.H;
@@ -251,6 +181,12 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         rv[i][j] = (j < kk && pp[j] >= 0) ? a.p_r[(size_t)pp[j] * a.H + h] : 0.f;
+      if constexpr (MORE) {  // a dense layer: no routed partials
+#pragma unroll
+        for (int s = 0; s < kMaxMore; ++s)
+          if (s < a.n_more)
+            rv[i][s] = a.dense_p[2][(size_t)(s + 1) * a.more_stride + rowoff + h];
+      }
       res[i] = a.residual ? a.residual[rowoff + h] : 0.f;
     }
 #pragma unroll
@@ -261,6 +197,11 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
 #pragma unroll
         for (int s = 0; s < 3; ++s)
           if (s < a.n_dense) x += dv[i][s];
+        if constexpr (MORE) {
+#pragma unroll
+          for (int s = 0; s < kMaxMore; ++s)
+            if (s < a.n_more) x += rv[i][s];
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
           if (j < kk && pp[j] >= 0) x += rv[i][j];
@@ -305,9 +246,10 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
   }
 }
 
+template <bool MORE>
 __global__ __launch_bounds__(kCombThreads) void combine_kernel(CombineArgs a) {
   __shared__ float red[kCombThreads / 64];
-  combine_row<kCombThreads>(a, blockIdx.x, red);
+  combine_row<kCombThreads, MORE>(a, blockIdx.x, red);
 }
 
 // The combine of one layer and the router logits of the next (Eq. 1) in one
@@ -317,6 +259,7 @@ __global__ __launch_bounds__(kCombThreads) void combine_kernel(CombineArgs a) {
 // same arithmetic as the routing launch.  (The expert group varies fastest:
 // workgroups go to the XCDs round-robin, so one group's router rows are read
 // from memory by a few XCDs' L2 caches instead of one per position.)
+template <bool MORE>
 __global__ __launch_bounds__(kCombThreads) void combine_route_kernel(CombineArgs a, RouteArgs r) {
   __shared__ float red[kCombThreads / 64];
   const int G = (r.sel.N + kCombThreads / kWave - 1) / (kCombThreads / kWave);
@@ -331,7 +274,7 @@ __global__ __launch_bounds__(kCombThreads) void combine_route_kernel(CombineArgs
   float4 wp[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) wp[j] = pre ? w4[min(lane + j * kWave, H4 - 1)] : float4{};
-  combine_row<kCombThreads>(a, t, red, s_dyn, grp == 0);
+  combine_row<kCombThreads, MORE>(a, t, red, s_dyn, grp == 0);
   __syncthreads();
   if (e < r.sel.N) {
     const float4* xs4 = reinterpret_cast<const float4*>(s_dyn);
@@ -448,11 +391,13 @@ hipError_t allow_lds(const void* fn, size_t lds) {
 }
 
 hipError_t launch_gateup(const GroupedArgs& a, int wdtype, hipStream_t s) {
+  if (a.mfma) return launch_gateup_mfma(a, s);
   if (wdtype == DE_Q4_0) return gateup_typed<q4_t>(a, s);
   return wdtype == DE_BF16 ? gateup_typed<uint16_t>(a, s) : gateup_typed<float>(a, s);
 }
 
 hipError_t launch_down(const GroupedArgs& a, int wdtype, hipStream_t s) {
+  if (a.mfma) return launch_down_mfma(a, s);
   if (wdtype == DE_Q4_0) return down_typed<q4_t>(a, s);
   return wdtype == DE_BF16 ? down_typed<uint16_t>(a, s) : down_typed<float>(a, s);
 }
@@ -476,13 +421,14 @@ hipError_t launch_combine_route(const CombineArgs& a, const RouteArgs& r, hipStr
       rows_overlap(a.y, a.normed, a.T, a.H))
     return note_hip(hipErrorInvalidValue);
   const int G = (r.sel.N + kCombThreads / kWave - 1) / (kCombThreads / kWave);
-  hipLaunchKernelGGL(combine_route_kernel, dim3(a.T * G), dim3(kCombThreads), (size_t)a.H * 4, s,
-                     a, r);
+  hipLaunchKernelGGL(a.n_more > 0 ? combine_route_kernel<true> : combine_route_kernel<false>,
+                     dim3(a.T * G), dim3(kCombThreads), (size_t)a.H * 4, s, a, r);
   return note_hip(hipGetLastError());
 }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(combine_kernel, dim3(a.T), dim3(kCombThreads), 0, s, a);
+  hipLaunchKernelGGL(a.n_more > 0 ? combine_kernel<true> : combine_kernel<false>, dim3(a.T),
+                     dim3(kCombThreads), 0, s, a);
   return note_hip(hipGetLastError());
 }
 
