@@ -121,43 +121,47 @@ struct MfmaPlan {
 
 // Width of n column chunks of a K-column reduction (the last may be narrower),
 // and the number of chunks that have columns.
-int chunk_width(int K, int n) { return (K / 8 + n - 1) / n * 8; }
-int chunk_count(int K, int n) { return (K + chunk_width(K, n) - 1) / chunk_width(K, n); }
+int chunk_width(int K, int n, int align) { return (K / align + n - 1) / n * align; }
+int chunk_count(int K, int n, int align) {
+  return (K + chunk_width(K, n, align) - 1) / chunk_width(K, n, align);
+}
 
-// bf16 blocks of two positions or more (V2-Lite layer, gate/up + down:
-// T = 2: 53.8 us against 56.9 on the vector ALU, T = 9: 121 against 136,
-// T = 64: 235 against 802; a single position is the same within the runs'
-// spread, and the persistent draft pass computes it in the vector ALU's order),
-// every source's columns within the waves' registers.  The plan follows from
-// the layer's shape and the block alone, so that calls over parts of a layer
-// (an expert cache's chunks) sum in the same order.
+// Blocks of two positions or more whose sources' columns fit the waves'
+// registers.  V2-Lite layer, gate/up + down, us on the matrix cores against
+// the vector ALU: bf16 T = 2 54 against 57, T = 9 120 against 136, T = 64 234
+// against 802; Q4_0 T = 9 81 against 113, T = 1 31 against 26.  (One bf16
+// position is the same within the runs' spread, and the persistent draft pass
+// computes it in the vector ALU's order.)  The plan follows from the layer's
+// shape and the block alone, so that calls over parts of a layer (an expert
+// cache's chunks) sum in the same order.
 MfmaPlan mfma_plan(const de_moe_desc& d, int T, int kk, bool has_shared, bool has_draft) {
   MfmaPlan p{};
   const int Is = has_shared ? d.shared_inter : 0, Id = has_draft ? d.draft_inter : 0;
-  if (d.wdtype != DE_BF16 || T < 2 || d.hidden > de::kMfmaMaxK || d.inter > de::kMfmaMaxK ||
-      Id > de::kMfmaMaxK || !de::mfma_fits(T, d.n_experts, d.top_k))
+  if (d.wdtype == DE_F32 || T < 2 || d.hidden > de::kMfmaMaxK || d.inter > de::kMfmaMaxK ||
+      Id > de::kMfmaMaxK || !de::mfma_fits(d.wdtype, T, d.n_experts, d.top_k))
     return p;
   if (Is > 0) {
     // No wider than the routed experts' rows where possible, so that every
     // down tile of the launch streams about the same.
     const int most = kMaxSharedChunks - (Id > 0 ? 1 : 0);
+    const int al = elem_align(d.wdtype);
     int n = 1;
-    while (n < most && chunk_width(Is, n) > std::max(d.inter, 256)) ++n;
-    p.cw = chunk_width(Is, n);
-    p.chunks = chunk_count(Is, n);
+    while (n < most && chunk_width(Is, n, al) > std::max(d.inter, 256)) ++n;
+    p.cw = chunk_width(Is, n, al);
+    p.chunks = chunk_count(Is, n, al);
     if (p.cw > de::kMfmaMaxK) return p;
   }
   const int mu = std::min(T * kk, d.n_experts);
-  p.lkw_gu = de::mfma_lkw(d.hidden, mu * d.inter + Is + Id, 16);
-  p.lkw_dn = de::mfma_lkw(std::max(std::max(d.inter, p.cw), Id),
-                          (mu + p.chunks + (Id > 0 ? 1 : 0)) * d.hidden, 32);
+  p.lkw_gu = de::mfma_lkw(d.wdtype, true, d.hidden, mu * d.inter + Is + Id);
+  p.lkw_dn = de::mfma_lkw(d.wdtype, false, std::max(std::max(d.inter, p.cw), Id),
+                          (mu + p.chunks + (Id > 0 ? 1 : 0)) * d.hidden);
   p.on = true;
   return p;
 }
 
 // True when the verify layer of this shape can run as one launch.
 bool fused_shape(const de_moe_desc& d, int T) {
-  return T >= de::kVerifyFusedMinT && T <= de::kVerifyFusedMaxT &&
+  return d.wdtype == DE_BF16 && T >= de::kVerifyFusedMinT && T <= de::kVerifyFusedMaxT &&
          mfma_plan(d, T, d.top_k, d.shared_inter > 0, false).on;
 }
 
@@ -338,8 +342,8 @@ int mfma_chunks(int K, int rows, int T, int most) {
   long cost = 0;
   const int cus = de::dev_info().num_cus;
   for (int n = 1; n <= most; ++n) {
-    const int cw = chunk_width(K, n);
-    if (cw > de::kMfmaMaxK || chunk_count(K, n) != n) continue;
+    const int cw = chunk_width(K, n, 8);
+    if (cw > de::kMfmaMaxK || chunk_count(K, n, 8) != n) continue;
     const long tiles = (long)n * ((rows + 31) / 32) * ((T + 15) / 16);
     const long c = (tiles + cus - 1) / cus * ((cw + 255) / 256);
     if (best == 0 || c < cost) {
@@ -426,6 +430,7 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
       de::DenseSrc& ds = g.dense[nd++];
       ds = de::DenseSrc{};
       ds.w = D;
+      ds.ws = q4 ? D + (size_t)d.hidden * d.shared_inter / 2 : nullptr;
       ds.inter = d.shared_inter;
       ds.rows = d.hidden;
       ds.gate = 1.0f;
@@ -1048,7 +1053,7 @@ int de_lm_head(int T, int H, int V, const float* x, const void* w_lm, float* log
   g.dense[0].out_stride = V;
   if (mx) {
     g.mfma = 1;
-    g.lkw = de::mfma_lkw(H, V, 32);
+    g.lkw = de::mfma_lkw(DE_BF16, false, H, V);
     g.dense[0].chunks = 1;
     g.dense[0].cw = H;
   }
@@ -1140,12 +1145,12 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
   const int cw = (I / al + nc - 1) / nc * al;
   if (mx) {
     g.mfma = 1;
-    g.lkw = de::mfma_lkw(H, I, 16);
+    g.lkw = de::mfma_lkw(wdtype, true, H, I);
   }
   if (timed_phase(DE_PHASE_GATEUP, stream, [&] { return de::launch_gateup(g, wdtype, stream); }) !=
       hipSuccess)
     return DE_ERR_HIP;
-  if (mx) g.lkw = de::mfma_lkw(cw, nc * H, 32);
+  if (mx) g.lkw = de::mfma_lkw(wdtype, false, cw, nc * H);
   const char* D = static_cast<const char*>(w) + 2 * (size_t)I * H * elem_bytes(wdtype);
   g.n_dense = mx ? 1 : nc;
   for (int i = 0; i < g.n_dense; ++i) {

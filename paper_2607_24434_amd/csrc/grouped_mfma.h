@@ -9,17 +9,16 @@ namespace de {
 constexpr int kMfmaMaxK = 2048;
 
 // log2 of the column slices of a pass over sources of at most K columns and
-// `rows` rows in all (gate/up: (G, U) row pairs), `per` rows per row group
-// of a tile (16 gate/up pairs, 32 down rows).
-int mfma_lkw(int K, int rows, int per);
+// `rows` rows in all (gate/up: (G, U) row pairs).
+int mfma_lkw(int wdtype, bool gateup, int K, int rows);
 
 // True when a layer's tables (T positions, top k of N experts) fit a block's
 // LDS beside the staged weights and the partials.
-bool mfma_fits(int T, int N, int k);
+bool mfma_fits(int wdtype, int T, int N, int k);
 
-// GroupedArgs::lkw set, every source's columns a multiple of 8 and at most
-// kMfmaMaxK.
-hipError_t launch_gateup_mfma(const GroupedArgs& a, hipStream_t s);
-hipError_t launch_down_mfma(const GroupedArgs& a, hipStream_t s);
+// DE_BF16 or DE_Q4_0 weights; GroupedArgs::lkw set, every source's columns (a
+// down source's: cw) a multiple of 8 (32) and at most kMfmaMaxK.
+hipError_t launch_gateup_mfma(const GroupedArgs& a, int wdtype, hipStream_t s);
+hipError_t launch_down_mfma(const GroupedArgs& a, int wdtype, hipStream_t s);
 
 }  // namespace de

@@ -1,25 +1,25 @@
 // The grouped gate/up and down launches of a block of positions on the matrix
-// cores (bf16 weights); mfma_core.h holds the passes.
+// cores (bf16 and Q4_0 weights); mfma_core.h holds the passes.
 #include "mfma_core.h"
 
 namespace de {
 namespace {
 
-template <int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP>
 __global__ __launch_bounds__(kBlock, 2) void grouped_mfma_kernel(GroupedArgs a) {
   const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
   __shared__ int s_absent, s_nms;
-  const MfmaTables mt = mfma_tables<KS, GATEUP>(a, lane, wave, &s_absent, &s_nms);
+  const MfmaTables mt = mfma_tables<WT, KS, GATEUP>(a, lane, wave, &s_absent, &s_nms);
   if constexpr (!GATEUP) {
     if (s_absent && !a.r.absent_ok) absent_rows_zero(a, mt.tb, mt.nu);
   }
-  mfma_pass<KS, GATEUP>(a, 0, mt.tb, mt.slc, mt.nms, lane, wave);
+  mfma_pass<WT, KS, GATEUP>(a, 0, mt.tb, mt.slc, mt.nms, lane, wave);
 }
 
-template <int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP>
 hipError_t launch_ks(const GroupedArgs& a, int tiles, hipStream_t s) {
-  const auto kernel = grouped_mfma_kernel<KS, GATEUP>;
-  const size_t lds = mfma_lds<KS>(a);
+  const auto kernel = grouped_mfma_kernel<WT, KS, GATEUP>;
+  const size_t lds = mfma_lds<WT, KS>(a);
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -30,23 +30,31 @@ hipError_t launch_ks(const GroupedArgs& a, int tiles, hipStream_t s) {
   return note_hip(hipGetLastError());
 }
 
-template <bool GATEUP>
+template <typename WT, bool GATEUP>
 hipError_t launch_typed(const GroupedArgs& a, hipStream_t s) {
-  const int rpt = (kWavesPB >> a.lkw) * (GATEUP ? 16 : 32);
+  const int rpt = (kWavesPB >> a.lkw) * group_rows<WT, GATEUP>();
   const int groups = cdiv(a.T, kXP);
   int K = GATEUP ? a.H : (a.has_routed ? a.r.inter : 0), tiles = 0;
   if (a.has_routed)
     tiles += (a.r.max_union + a.r.pairs_max / kXP) * cdiv(GATEUP ? a.r.inter : a.H, rpt);
   for (int i = 0; i < a.n_dense; ++i) {
-    if (!GATEUP && a.dense[i].cw > K) K = a.dense[i].cw;
-    tiles += groups * (GATEUP ? 1 : a.dense[i].chunks) * cdiv(GATEUP ? a.dense[i].inter : a.dense[i].rows, rpt);
+    const DenseSrc& d = a.dense[i];
+    if (!GATEUP && d.cw > K) K = d.cw;
+    tiles += groups * (GATEUP ? cdiv(d.inter, rpt) : d.chunks * cdiv(d.rows, rpt));
   }
   if (tiles == 0) return hipSuccess;
   const int ks = cdiv(cdiv(K, 32), 1 << a.lkw);
-  if (ks <= 2) return launch_ks<2, GATEUP>(a, tiles, s);
-  if (ks <= 4) return launch_ks<4, GATEUP>(a, tiles, s);
-  if (ks <= 6) return launch_ks<6, GATEUP>(a, tiles, s);
-  if (ks <= 8) return launch_ks<8, GATEUP>(a, tiles, s);
+  if (ks <= 2) return launch_ks<WT, 2, GATEUP>(a, tiles, s);
+  if (ks <= 4) return launch_ks<WT, 4, GATEUP>(a, tiles, s);
+  if (ks <= 6) return launch_ks<WT, 6, GATEUP>(a, tiles, s);
+  if (ks <= 8) return launch_ks<WT, 8, GATEUP>(a, tiles, s);
+  return note_hip(hipErrorInvalidValue);
+}
+
+template <bool GATEUP>
+hipError_t launch_pass(const GroupedArgs& a, int wdtype, hipStream_t s) {
+  if (wdtype == DE_Q4_0) return launch_typed<q4_t, GATEUP>(a, s);
+  if (wdtype == DE_BF16) return launch_typed<uint16_t, GATEUP>(a, s);
   return note_hip(hipErrorInvalidValue);
 }
 
@@ -54,7 +62,10 @@ hipError_t launch_typed(const GroupedArgs& a, hipStream_t s) {
 
 // The fewest column slices whose waves hold at most 8 steps each, then more
 // (smaller tiles) while the rows make fewer tiles than the chip has CUs.
-int mfma_lkw(int K, int rows, int per) {
+int mfma_lkw(int wdtype, bool gateup, int K, int rows) {
+  const int per = wdtype == DE_Q4_0
+                      ? (gateup ? group_rows<q4_t, true>() : group_rows<q4_t, false>())
+                      : (gateup ? group_rows<uint16_t, true>() : group_rows<uint16_t, false>());
   const int S = (K + 31) / 32;
   int l = 0;
   while (l < 3 && cdiv(S, 1 << l) > 8) ++l;
@@ -62,7 +73,7 @@ int mfma_lkw(int K, int rows, int per) {
   return l;
 }
 
-bool mfma_fits(int T, int N, int k) {
+bool mfma_fits(int wdtype, int T, int N, int k) {
   GroupedArgs a{};
   a.T = T;
   a.has_routed = a.fuse_route = 1;
@@ -70,10 +81,15 @@ bool mfma_fits(int T, int N, int k) {
   a.sel.N = N;
   a.r.pairs_max = T * k;
   a.r.max_union = T * k < N ? T * k : N;
-  return mfma_lds<8>(a) <= (size_t)160 * 1024 - 256;
+  const size_t lds = wdtype == DE_Q4_0 ? mfma_lds<q4_t, 8>(a) : mfma_lds<uint16_t, 8>(a);
+  return lds <= (size_t)160 * 1024 - 256;
 }
 
-hipError_t launch_gateup_mfma(const GroupedArgs& a, hipStream_t s) { return launch_typed<true>(a, s); }
-hipError_t launch_down_mfma(const GroupedArgs& a, hipStream_t s) { return launch_typed<false>(a, s); }
+hipError_t launch_gateup_mfma(const GroupedArgs& a, int wdtype, hipStream_t s) {
+  return launch_pass<true>(a, wdtype, s);
+}
+hipError_t launch_down_mfma(const GroupedArgs& a, int wdtype, hipStream_t s) {
+  return launch_pass<false>(a, wdtype, s);
+}
 
 }  // namespace de

@@ -391,13 +391,13 @@ hipError_t allow_lds(const void* fn, size_t lds) {
 }
 
 hipError_t launch_gateup(const GroupedArgs& a, int wdtype, hipStream_t s) {
-  if (a.mfma) return launch_gateup_mfma(a, s);
+  if (a.mfma) return launch_gateup_mfma(a, wdtype, s);
   if (wdtype == DE_Q4_0) return gateup_typed<q4_t>(a, s);
   return wdtype == DE_BF16 ? gateup_typed<uint16_t>(a, s) : gateup_typed<float>(a, s);
 }
 
 hipError_t launch_down(const GroupedArgs& a, int wdtype, hipStream_t s) {
-  if (a.mfma) return launch_down_mfma(a, s);
+  if (a.mfma) return launch_down_mfma(a, wdtype, s);
   if (wdtype == DE_Q4_0) return down_typed<q4_t>(a, s);
   return wdtype == DE_BF16 ? down_typed<uint16_t>(a, s) : down_typed<float>(a, s);
 }

@@ -1,6 +1,6 @@
 // The grouped gate/up and down passes of a block of positions on the matrix
-// cores, for bf16 weights (the LM head's row-dot is a down pass of one
-// source): the device functions of the separate launches and of the
+// cores, for bf16 and Q4_0 weights (the LM head's row-dot is a down pass of
+// one source): the device functions of the separate launches and of the
 // single-launch verify layer, which therefore write the same bits.
 //
 // Every weight byte meets |T_e| positions, so the passes should be bound by
@@ -35,9 +35,15 @@
 // one fragment per wave (64 KB in flight per CU; two measured no faster) and
 // each is refilled from the next fragment as soon as it is stored, across
 // tiles and experts.  A block owns a contiguous range of the launch's tiles
-// and meets one or two experts; the activations of the next expert are loaded
-// the same way, into the registers of the step just finished, and are split
-// when the step is used.
+// and meets one or two experts.  In the steady state a bf16 gate/up tile
+// (128 KB) takes 4.5 us, 7.4 TB/s over the chip.
+//
+// Q4_0: a fragment is a quarter of the bytes, so a tile is four fragments and
+// all four are in flight.  The codes become bf16 operands with one conversion
+// per two (the vector ALU needed one conversion and one FMA per weight and
+// position); V2-Lite layer at T = 9: gate/up 48 us (vector ALU 63), down 33
+// (51), bound by the latency of a fragment's way through LDS, conversion and
+// matrix cores.
 //
 // Measured (rocprofv3, V2-Lite layer): T = 9 gate/up 82 us (vector ALU 88),
 // down 42 (47); T = 17 99 (131) and 50 (80); T = 64 163 (554) and 79 (248);
@@ -59,15 +65,36 @@ namespace {
 constexpr int kXP = 16;                       // positions per slice
 constexpr int kRedLd = 20;                    // LDS partials: row stride (4 extra: no bank conflicts)
 constexpr int kRedTile = kXP * kRedLd;        // one 16 x 16 tile of partials
-constexpr int kRedBuf = kWavesPB * 2 * kRedTile;
-constexpr int kRedFloats = 2 * kRedBuf;       // double buffered: one barrier per tile
+template <typename WT>
+constexpr int kFrags = kQ4<WT> ? 4 : 2;       // 16-row fragments of a wave's tile
+template <typename WT>
+constexpr int kRedBuf = kWavesPB * kFrags<WT> * kRedTile;
+template <typename WT>
+constexpr int kRedFloats = 2 * kRedBuf<WT>;   // double buffered: one barrier per tile
 
-// LDS of a wave's staged weight fragment: 16 rows of 4 KS units of 16 bytes,
-// one unit of padding per row (no bank conflicts in the fragment reads).
+// 16-byte units of a row per step of 32 columns (Q4_0: one unit is one block).
+template <typename WT>
+constexpr int kStepUnits = kQ4<WT> ? 1 : 4;
+// Load instructions of a fragment of KS steps.
+template <typename WT, int KS>
+constexpr int kLoads = (16 * KS * kStepUnits<WT> + kWave - 1) / kWave;
 template <int KS>
-constexpr int kRowUnits = 4 * KS + 1;
-template <int KS>
-constexpr int kStageFloats = kWavesPB * 16 * kRowUnits<KS> * 4;
+constexpr int kQ4Loads = kLoads<q4_t, KS>;
+// LDS of a wave's staged fragment: 16 rows of units with one unit of padding
+// per row (no bank conflicts in the fragment reads), then (Q4_0) 16 rows of 8
+// scales.
+template <typename WT, int KS>
+constexpr int kRowUnits = kStepUnits<WT> * KS + 1;
+template <typename WT, int KS>
+constexpr int kWaveStage = 16 * kRowUnits<WT, KS> * 16 + (kQ4<WT> ? 16 * 16 : 0);
+template <typename WT, int KS>
+constexpr int kStageFloats = kWavesPB * kWaveStage<WT, KS> / 4;
+
+// Rows (gate/up: pairs) of a row group of waves in a tile.
+template <typename WT, bool GATEUP>
+__host__ __device__ constexpr int group_rows() {
+  return GATEUP ? 8 * kFrags<WT> : 16 * kFrags<WT>;
+}
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -75,9 +102,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // every lane).
 struct Slice {
   const char* w;      // gate/up: G; down: the matrix
-  int64_t w2;         // gate/up: bytes from a G row to its U row
+  const char* sc;     // Q4_0: the scales of the first row
+  int64_t w2;         // gate/up: bytes from a G row (and its scales) to its U row
   int rows, K;        // rows (gate/up: pairs), columns
-  uint32_t rb;        // bytes per row
+  uint32_t rb, srb;   // bytes per row of weights (codes) and of scales
   const float* act;   // activations, row stride astride
   int astride;
   int nt, p0;         // positions, first output row
@@ -99,6 +127,7 @@ __device__ __forceinline__ DenseSrc dense_arg(int arg, int s) {
   DenseSrc d{};
 #define DE_KARG(f) d.f = *(__attribute__((address_space(4))) const decltype(d.f)*)(p + offsetof(DenseSrc, f))
   DE_KARG(w);
+  DE_KARG(ws);
   DE_KARG(inter);
   DE_KARG(ld);
   DE_KARG(rows);
@@ -116,7 +145,7 @@ __device__ __forceinline__ DenseSrc dense_arg(int arg, int s) {
 
 // Tiles of a launch: each dense source's slices (position groups of 16), then
 // the members' slices, every slice's tiles in row order.
-template <bool GATEUP>
+template <typename WT, bool GATEUP>
 struct Tiles {
   const GroupedArgs& a;
   int arg;              // where the kernel arguments hold a
@@ -187,18 +216,18 @@ struct Tiles {
       if constexpr (GATEUP) {
         c.rows = d.inter;
         c.K = a.H;
-        c.rb = (uint32_t)a.H * 2u;
-        c.w2 = (int64_t)d.inter * c.rb;
+        c.rb = (uint32_t)qrow_bytes<WT>(a.H);
+        c.w2 = (int64_t)mat_bytes<WT>(d.inter, a.H);
         c.act = a.x;
         c.astride = a.H;
         c.out = d.out;
         c.ostride = d.inter;
         c.gscalar = 0.f;
       } else {
-        c.w += (size_t)ch * d.cw * 2;
+        c.w += qrow_bytes<WT>(ch * d.cw);
         c.rows = d.rows;
         c.K = min(d.cw, d.inter - ch * d.cw);
-        c.rb = (uint32_t)(d.ld > 0 ? d.ld : d.inter) * 2u;
+        c.rb = (uint32_t)qrow_bytes<WT>(d.ld > 0 ? d.ld : d.inter);
         c.w2 = 0;
         c.act = d.vin + (size_t)ch * d.cw;
         c.astride = d.vin_stride;
@@ -206,6 +235,10 @@ struct Tiles {
         c.ostride = d.out_stride;
         c.gscalar = d.gate;
       }
+      // Q4_0: a matrix's scales follow its codes (a column chunk's are given).
+      c.srb = c.rb >> 3;
+      c.sc = GATEUP ? c.w + (size_t)c.rows * c.rb
+                    : static_cast<const char*>(d.ws) + (size_t)ch * (d.cw >> 4);
       c.tiles = uni(cdiv(c.rows, rpt));
     } else {
       const int e = uni(slc[v - nds]);
@@ -220,8 +253,8 @@ struct Tiles {
         c.w = blk;
         c.rows = I;
         c.K = a.H;
-        c.rb = (uint32_t)a.H * 2u;
-        c.w2 = (int64_t)I * c.rb;
+        c.rb = (uint32_t)qrow_bytes<WT>(a.H);
+        c.w2 = (int64_t)mat_bytes<WT>(I, a.H);
         c.act = a.x;
         c.astride = a.H;
         c.listed = 1;
@@ -229,10 +262,10 @@ struct Tiles {
         c.ostride = I;
         c.goff = -1;
       } else {
-        c.w = blk + 2 * mat_bytes<uint16_t>(I, a.H);
+        c.w = blk + 2 * mat_bytes<WT>(I, a.H);
         c.rows = a.H;
         c.K = I;
-        c.rb = (uint32_t)I * 2u;
+        c.rb = (uint32_t)qrow_bytes<WT>(I);
         c.w2 = 0;
         c.act = a.r.a;
         c.astride = I;
@@ -241,6 +274,8 @@ struct Tiles {
         c.ostride = a.H;
         c.goff = c.p0;
       }
+      c.srb = c.rb >> 3;
+      c.sc = c.w + (size_t)c.rows * c.rb;
       c.tiles = tr;
     }
     return c;
@@ -251,15 +286,15 @@ struct Tiles {
 // 16 bytes in every row; its fragment (16 rows of them) is loaded as one list
 // of units in row order, 64 per load, so that a load reads whole runs of a
 // row (512 bytes of two rows for 2048 columns over 8 waves).
-template <int KS>
+template <typename WT, int KS>
 struct Lanes {
-  uint32_t w[KS];     // load j: byte offset from the fragment's first row
   uint32_t row;       // load j: the unit's row in bits 4 j .. 4 j + 3
   int upw;            // the wave's units per row
+  int last;           // last row that a fragment may read
+  uint32_t rb, srb;   // bytes per row of weights and of scales
   uint32_t xo;        // activations: byte offset of the lane's position
   int u0, ulast;      // first unit, last unit of the row
-  uint32_t ok;        // bit q: the lane's unit of step q exists
-  int ragged;         // some lane's unit of some step does not (uniform)
+  uint32_t ok;        // bit q: the lane's columns of step q exist
 };
 
 __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
@@ -270,49 +305,79 @@ __device__ __forceinline__ u32x4 ldx(const float* base, uint32_t off) {
 }
 
 // Slice c for column slice ks of 2^lkw.  As matrix operands lane l holds row
-// (position) l % 16 and columns 8 (l / 16) .. + 7 of each 32-column step; a
-// unit that does not exist is read as the last one and zeroed.
-template <int KS>
-__device__ __forceinline__ Lanes<KS> lanes_of(const Slice& c, const Tables& tb, int ks, int lkw,
-                                              int lane) {
-  Lanes<KS> L;
+// (position) l % 16 and 8 columns of each 32-column step: bf16 weights 8 g ..
+// 8 g + 7 with g = l / 16; Q4_0 4 g .. 4 g + 3 and 16 + 4 g .. (the low and
+// high nibbles of 4 bytes of the block).  A unit that does not exist is never
+// staged: its LDS words and its activations are zero.
+template <typename WT, int KS>
+__device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& tb, int ks, int lkw,
+                                                  int lane) {
+  Lanes<WT, KS> L;
+  constexpr int SU = kStepUnits<WT>;
   const int n = lane & 15, g = lane >> 4;
-  const int S = (c.K + 31) >> 5, U = c.K >> 3;  // steps, units per row
+  const int S = (c.K + 31) >> 5, U = (int)(qrow_bytes<WT>(c.K) >> 4);  // steps, units per row
   const int s0 = (ks * S) >> lkw, s1 = ((ks + 1) * S) >> lkw;
   L.ulast = U - 1;
-  L.u0 = min(s0 * 4, L.ulast);
-  const int upw = max(min(s1 * 4, U) - L.u0, 1);
+  L.u0 = min(s0 * SU, L.ulast);
+  const int upw = max(min(s1 * SU, U) - L.u0, 1);
   L.upw = upw;
+  L.last = min(c.rows, 16) - 1;
+  L.rb = c.rb;
+  L.srb = c.srb;
   L.row = 0;
   const uint32_t inv = (65536u + upw - 1) / (uint32_t)upw;  // f / upw = f inv >> 16 for f < 512
 #pragma unroll
-  for (int j = 0; j < KS; ++j) {
+  for (int j = 0; j < kLoads<WT, KS>; ++j) {
     const uint32_t f = (uint32_t)min(j * kWave + lane, 16 * upw - 1);
-    const uint32_t row = (f * inv) >> 16, u = f - row * upw;
-    L.w[j] = (uint32_t)min((int)row, c.rows - 1) * c.rb + (L.u0 + u) * 16u;
-    L.row |= row << (4 * j);
+    L.row |= ((f * inv) >> 16) << (4 * j);
   }
   L.ok = 0;
 #pragma unroll
-  for (int q = 0; q < KS; ++q) L.ok |= (s0 + q < s1 && (s0 + q) * 4 + g < U) ? 1u << q : 0u;
+  for (int q = 0; q < KS; ++q)
+    L.ok |= (s0 + q < s1 && (kQ4<WT> || (s0 + q) * SU + g < U)) ? 1u << q : 0u;
   const int m = min(n, c.nt - 1);
   const int pos = c.listed ? tb.tok[c.p0 + m] : c.p0 + m;
   L.xo = (uint32_t)pos * (uint32_t)c.astride * 4u;
-  L.ragged = __builtin_amdgcn_ballot_w64(L.ok != (1u << KS) - 1u) != 0ull;
   return L;
 }
 
-// Where the unit of load j goes in the wave's LDS rows (bytes).
-template <int KS>
-__device__ __forceinline__ uint32_t stage_off(uint32_t rows, int upw, int j, int lane) {
-  const uint32_t f = (uint32_t)min(j * kWave + lane, 16 * upw - 1);
-  return (f + ((rows >> (4 * j)) & 15u) * (uint32_t)(kRowUnits<KS> - upw)) * 16u;
+// The lane's unit of load j: its place in the wave's list, and its row.
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t unit_of(const Lanes<WT, KS>& L, int j, int lane, uint32_t& row) {
+  row = (L.row >> (4 * j)) & 15u;
+  return (uint32_t)min(j * kWave + lane, 16 * L.upw - 1);
 }
 
-// Byte offset of the lane's 8 activations of step q.
-template <int KS>
-__device__ __forceinline__ uint32_t x_off(const Lanes<KS>& L, int q, int g) {
-  return L.xo + (uint32_t)min(L.u0 + 4 * q + g, L.ulast) * 32u;
+// Where that unit goes in the wave's LDS rows of `pitch` units.
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t stage_unit(const Lanes<WT, KS>& L, int j, int lane, int pitch) {
+  uint32_t row;
+  const uint32_t f = unit_of(L, j, lane, row);
+  return f + row * (uint32_t)(pitch - L.upw);
+}
+
+// Its byte offset from the fragment's first row, and (Q4_0) its scale's.
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t load_off(const Lanes<WT, KS>& L, int j, int lane, bool scale) {
+  uint32_t row;
+  const uint32_t u = unit_of(L, j, lane, row) - row * (uint32_t)L.upw + (uint32_t)L.u0;
+  row = min(row, (uint32_t)L.last);
+  return scale ? row * L.srb + u * 2u : row * L.rb + u * 16u;
+}
+
+// The lane's 8 activations of step q (fp32).
+template <typename WT, int KS>
+__device__ __forceinline__ void load_x(u32x4 (&f)[3], const float* x, const Lanes<WT, KS>& L, int q,
+                                       int g) {
+  if constexpr (kQ4<WT>) {
+    const uint32_t o = L.xo + (uint32_t)min(L.u0 + q, L.ulast) * 128u + g * 16u;
+    f[0] = ldx(x, o);
+    f[1] = ldx(x, o + 64u);
+  } else {
+    const uint32_t o = L.xo + (uint32_t)min(L.u0 + 4 * q + g, L.ulast) * 32u;
+    f[0] = ldx(x, o);
+    f[1] = ldx(x, o + 16u);
+  }
 }
 
 // f[0], f[1]: 8 fp32 values -> f[0], f[1], f[2]: their hi, mid and lo bf16
@@ -347,59 +412,105 @@ __device__ __forceinline__ void split8(u32x4 (&f)[3], bool ok) {
   }
 }
 
-// One fragment of the wave: 16 weight rows against the activations, sums to
-// acc.  The fragment goes from the load registers through the wave's LDS rows
-// (st; loads in memory order, reads in operand order) and each load register
-// is refilled at once from the next fragment (first row nw, lane offsets of
-// nl; LOADS).  conv: the activations are fp32 values to be split first.
-// fresh: each step's activation registers are refilled with nl's (of nx).
-// The wave's LDS accesses execute in order, so only the compiler has to be
-// kept from moving them.
-template <int KS, bool LOADS>
-__device__ __forceinline__ void fragment(u32x4 (&act)[KS][3], u32x4 (&w)[KS], f32x4& acc, char* st,
-                                         uint32_t rows, int upw, bool conv, uint32_t ok,
-                                         int ragged, const char* nw, const Lanes<KS>& nl,
-                                         bool fresh, const float* nx, int lane) {
-  // Opaque to the compiler: the offsets below are computed again for every
-  // fragment instead of being kept in registers across them.
-  asm volatile("" : "+v"(lane));
-  const int n = lane & 15, g = lane >> 4;
+// Steps whose products are in flight together: independent chains of three
+// matrix instructions.
+template <int KS>
+constexpr int kStepGroup = KS < 4 ? KS : (KS % 4 == 0 ? 4 : 3);
+
+// acc of the steps' three products each, summed from zero, smallest part
+// first: a chain through all steps would round every part at the full sum's
+// magnitude.
+template <int N>
+__device__ __forceinline__ void products(const u32x4 (*act)[3], const u32x4 (&b)[N],
+                                         f32x4 (&c)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 2; p >= 0; --p)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, act[i][p]),
+                                                     __builtin_bit_cast(bf16x8, b[i]), c[i], 0, 0,
+                                                     0);
+}
+
+// Puts a bf16 fragment's load registers into the wave's LDS rows (loads in
+// memory order, reads in operand order) and refills each at once from the next
+// fragment (first row nw, lane offsets of nl; with mask 0 every lane re-reads
+// nw).  The wave's LDS accesses execute in order, so only the compiler has to
+// be kept from moving them.
+template <int KS>
+__device__ __forceinline__ void stage(u32x4 (&w)[KS], char* st, const Lanes<uint16_t, KS>& L,
+                                      const char* nw, const Lanes<uint16_t, KS>& nl, uint32_t mask,
+                                      int lane) {
 #pragma unroll
   for (int j = 0; j < KS; ++j) {
-    *reinterpret_cast<u32x4*>(st + stage_off<KS>(rows, upw, j, lane)) = w[j];
-    if constexpr (LOADS) w[j] = ldw(nw, nl.w[j]);
+    reinterpret_cast<u32x4*>(st)[stage_unit(L, j, lane, kRowUnits<uint16_t, KS>)] = w[j];
+    w[j] = ldw(nw, load_off(nl, j, lane, false) & mask);
   }
-  asm volatile("" ::: "memory");
-  acc = f32x4{0.f, 0.f, 0.f, 0.f};
-  const u32x4* rd = reinterpret_cast<const u32x4*>(st) + n * kRowUnits<KS> + g;
+}
+
+// The sums of the staged bf16 fragment: 16 weight rows against the
+// activations.  Nothing branches between the matrix instructions.
+template <int KS>
+__device__ __forceinline__ f32x4 fragment_sums(const u32x4 (&act)[KS][3], const char* st,
+                                               int lane) {
+  constexpr int N = kStepGroup<KS>;
+  const u32x4* rd = reinterpret_cast<const u32x4*>(st) +
+                    (lane & 15) * kRowUnits<uint16_t, KS> + (lane >> 4);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int q = 0; q < KS; ++q) {
-    const bool okq = !ragged || ((ok >> q) & 1u);
-    if (conv) split8(act[q], okq);
-    u32x4 b = rd[4 * q];
-    if (ragged) {
+  for (int q0 = 0; q0 < KS; q0 += N) {
+    u32x4 b[N];
+    f32x4 c[N];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) b[i] = okq ? b[i] : 0u;
-    }
-    // The step's three products are summed from zero, smallest part first, and
-    // added to the fragment's sums: a chain through all steps would round
-    // every part at the full sum's magnitude.
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < N; ++i) b[i] = rd[4 * (q0 + i)];
+    products<N>(act + q0, b, c);
 #pragma unroll
-    for (int p = 2; p >= 0; --p)
-      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, act[q][p]),
-                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-    acc += c;
-    if constexpr (LOADS) {
-      if (fresh) {
-        const uint32_t o = x_off(nl, q, g);
-        act[q][0] = ldx(nx, o);
-        act[q][1] = ldx(nx, o + 16u);
-      }
-    }
-    if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // bounds the operands read ahead
+    for (int i = 0; i < N; ++i) acc += c[i];
+    __builtin_amdgcn_sched_barrier(0);  // bounds the operands read ahead
   }
-  asm volatile("" ::: "memory");
+  return acc;
+}
+
+// The sums of the staged Q4_0 fragment.  A step is one block of 32 weights per
+// row, d (q - 8): the codes q become bf16 operands (a byte 0 .. 15 read as
+// e4m3 is q / 512, denormal or not, so one conversion with scale 512 makes two
+// of them), the products q x are summed by the matrix cores, and -8 times the
+// block's activation sum (xm) and the scale, which lane l holds for its own
+// row l % 16, are applied to the block's sums.
+template <int KS>
+__device__ __forceinline__ f32x4 fragment_sums_q4(const u32x4 (&act)[KS][3], const f32x4 (&xm)[KS],
+                                                  const char* st, int lane) {
+  constexpr int N = kStepGroup<KS>, RU = kRowUnits<q4_t, KS>;
+  const uint32_t* rd = reinterpret_cast<const uint32_t*>(st) + (lane & 15) * RU * 4 + (lane >> 4);
+  const u32x4 dv = reinterpret_cast<const u32x4*>(st + 16 * RU * 16)[lane & 15];
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q0 = 0; q0 < KS; q0 += N) {
+    u32x4 b[N];
+    f32x4 c[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t v = rd[4 * (q0 + i)];
+      const uint32_t lo = v & 0x0f0f0f0fu, hi = (v >> 4) & 0x0f0f0f0fu;
+#define DE_CODES(x, h) \
+  __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x, 512.f, h))
+      b[i] = u32x4{DE_CODES(lo, false), DE_CODES(lo, true), DE_CODES(hi, false),
+                   DE_CODES(hi, true)};
+#undef DE_CODES
+    }
+    products<N>(act + q0, b, c);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int q = q0 + i;
+      const float d = half_bits_to_float((dv[q >> 1] >> (16 * (q & 1))) & 0xffffu);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = fmaf(d, c[i][j] + xm[q][j], acc[j]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return acc;
 }
 
 // Waits for the wave's LDS accesses and the block's other waves; loads in
@@ -410,117 +521,210 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// First row of row group rw's 16-row fragment i of tile r (the last one is
-// moved up to end with the matrix; rows computed twice get the same value).
-template <bool GATEUP>
+// First row of 16-row group i of row group rw of tile r (the last one is moved
+// up to end with the matrix; rows computed twice get the same value).
+template <typename WT, bool GATEUP>
 __device__ __forceinline__ int frag_row(const Slice& c, int rpt, int r, int rw, int i) {
-  const int lim = max(c.rows - 16, 0);
-  return min(r * rpt + (GATEUP ? rw * 16 : rw * 32 + i * 16), lim);
+  return min(r * rpt + rw * group_rows<WT, GATEUP>() + i * 16, max(c.rows - 16, 0));
 }
 
-// The block's tiles.
-template <int KS, bool GATEUP>
-__device__ __forceinline__ void stream(const GroupedArgs& a, Tiles<GATEUP>& tl, int lkw,
-                                       float* red, int lane, int wave) {
-  const int total = tl.count();
-  const int lo = (int)((int64_t)total * blockIdx.x / gridDim.x);
-  const int hi = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
-  if (lo >= hi) return;
-  const int kw = 1 << lkw, nrw = kWavesPB >> lkw;
-  const int ks = wave & (kw - 1), rw = wave >> lkw;
+// Fragment f of tile r: gate/up G and U of row group f / 2, down row group f.
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ const char* frag_base(const Slice& c, int rpt, int r, int rw, int f) {
+  const size_t row = (size_t)frag_row<WT, GATEUP>(c, rpt, r, rw, GATEUP ? f >> 1 : f);
+  return uni(c.w + row * c.rb + (GATEUP && (f & 1) ? c.w2 : 0));
+}
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ const char* scale_base(const Slice& c, int rpt, int r, int rw, int f) {
+  const size_t row = (size_t)frag_row<WT, GATEUP>(c, rpt, r, rw, GATEUP ? f >> 1 : f);
+  return uni(c.sc + row * c.srb + (GATEUP && (f & 1) ? c.w2 : 0));
+}
+
+// A wave's sums of fragment f: position 4 g + i, row n.
+template <typename WT>
+__device__ __forceinline__ void put_partial(float* buf, const f32x4& acc, int f, int nt, int wave,
+                                            int lane) {
   const int g = lane >> 4, n = lane & 15;
+  float* p = buf + (wave * kFrags<WT> + f) * kRedTile + 4 * g * kRedLd + n;
+  if (4 * g < nt) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i * kRedLd] = acc[i];
+  }
+}
+
+// The tile's outputs from the waves' sums (after the barrier).
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
+                                             int lkw, const float* buf) {
+  const int kw = 1 << lkw, nrw = kWavesPB >> lkw;
+  constexpr int kG = GATEUP ? kFrags<WT> / 2 : kFrags<WT>;  // 16-row groups of a row group
+  constexpr int kWaveRed = kFrags<WT> * kRedTile;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // addresses are computed again for every tile
+#pragma unroll 1
+  for (int o = tid; o < 256 * kG * nrw; o += kBlock) {
+    // Row within 16, 16-row group, position, row group.
+    const int rr = o & 15, i = (o >> 4) & (kG - 1), pos = (o / (16 * kG)) & 15, rg = o / (256 * kG);
+    const int row = frag_row<WT, GATEUP>(c, rpt, r, rg, i) + rr;
+    if (pos < c.nt && row < c.rows) {
+      const float* q = buf + (rg << lkw) * kWaveRed + (GATEUP ? 2 * i : i) * kRedTile +
+                       pos * kRedLd + rr;
+      float s = 0.f, u = 0.f;
+      for (int k = 0; k < kw; ++k) {
+        s += q[k * kWaveRed];
+        if constexpr (GATEUP) u += q[k * kWaveRed + kRedTile];
+      }
+      float val;
+      if constexpr (GATEUP)
+        val = silu_f(s) * u;
+      else
+        val = (c.goff >= 0 ? tb.gate[c.goff + pos] : c.gscalar) * s;
+      *(DE_GLOBAL float*)(c.out + (size_t)(c.p0 + pos) * c.ostride + row) = val;
+    }
+  }
+}
+
+// What a wave holds: the activation fragments of its slice and the weights in
+// flight.  bf16: one fragment, refilled from the next one.  Q4_0 (a fragment
+// is a quarter of the bytes): the tile's four fragments with their units'
+// scales, each refilled from the same fragment of the next tile, and -8 times
+// the activation sum of every block.
+template <typename WT, int KS>
+struct Regs {
+  static constexpr int kDepth = kQ4<WT> ? kFrags<WT> : 1;
+  u32x4 act[KS][3];
+  u32x4 w[kDepth][kLoads<WT, KS>];
+  uint32_t sc[kQ4<WT> ? kDepth : 1][kQ4<WT> ? kLoads<WT, KS> : 1];
+  f32x4 xm[kQ4<WT> ? KS : 1];
+};
+
+__device__ __forceinline__ uint32_t ldh(const char* base, uint32_t off) {
+  return *(const DE_GLOBAL uint16_t*)((const DE_GLOBAL char*)base + off);
+}
+
+// The loads of the wave's fragment f of tile r into ring slot d.
+template <typename WT, int KS, bool GATEUP>
+__device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
+                                               const Lanes<WT, KS>& L, int rpt, int r, int rw,
+                                               int f, int d, uint32_t mask, int lane) {
+  const char* p = frag_base<WT, GATEUP>(c, rpt, r, rw, f);
+#pragma unroll
+  for (int j = 0; j < kLoads<WT, KS>; ++j) R.w[d][j] = ldw(p, load_off(L, j, lane, false) & mask);
+  if constexpr (kQ4<WT>) {
+    const char* ps = scale_base<WT, GATEUP>(c, rpt, r, rw, f);
+#pragma unroll
+    for (int j = 0; j < kLoads<WT, KS>; ++j) R.sc[d][j] = ldh(ps, load_off(L, j, lane, true) & mask);
+  }
+}
+
+// Loads a slice's activations and makes operands of them; the wave's LDS rows
+// are cleared (units past the wave's columns stay zero).  The loads are used
+// at once: left in flight into the next tile, where they may or may not be,
+// they would make every tile wait for all loads but its newest.
+template <typename WT, int KS>
+__device__ __forceinline__ void enter_slice(Regs<WT, KS>& R, const Slice& c,
+                                            const Lanes<WT, KS>& L, char* st, int lane) {
+#pragma unroll
+  for (int q = 0; q < KS; ++q) load_x<WT, KS>(R.act[q], c.act, L, q, lane >> 4);
+  const u32x4 z = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int i = 0; i < kWaveStage<WT, KS>; i += kWave * 16)
+    if (i + lane * 16 < kWaveStage<WT, KS>) *reinterpret_cast<u32x4*>(st + i + lane * 16) = z;
+#pragma unroll
+  for (int q = 0; q < KS; ++q) {
+    split8(R.act[q], (L.ok >> q) & 1u);
+    if constexpr (kQ4<WT>) {
+      const uint32_t m8 = 0xc100c100u;  // two bf16 -8
+      const u32x4 m[1] = {u32x4{m8, m8, m8, m8}};
+      f32x4 c[1];
+      products<1>(&R.act[q], m, c);
+      R.xm[q] = c[0];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("" ::: "memory");
+}
+
+// One tile of the wave: its fragments' sums to buf.  The registers are
+// refilled from tile nr of slice nc (lanes N; mask 0: nothing follows, the
+// loads all read one word).
+template <typename WT, int KS, bool GATEUP>
+__device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lanes<WT, KS>& L, int r,
+                                     const Slice& nc, const Lanes<WT, KS>& N, int nr, uint32_t mask,
+                                     int rpt, int rw, char* st, float* buf, int wave,
+                                     int lane_in) {
+  constexpr int NF = kFrags<WT>, D = Regs<WT, KS>::kDepth;
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    // Opaque to the compiler: the LDS offsets are computed again for every
+    // fragment instead of being kept in registers across them.
+    int lane = lane_in;
+    asm volatile("" : "+v"(lane));
+    f32x4 acc;
+    if constexpr (kQ4<WT>) {
+      constexpr int RU = kRowUnits<WT, KS>;
+      uint16_t* sst = reinterpret_cast<uint16_t*>(st + 16 * RU * 16);
+#pragma unroll
+      for (int j = 0; j < kLoads<WT, KS>; ++j) {
+        reinterpret_cast<u32x4*>(st)[stage_unit(L, j, lane, RU)] = R.w[f][j];
+        sst[stage_unit(L, j, lane, 8)] = (uint16_t)R.sc[f][j];
+      }
+      issue_fragment<WT, KS, GATEUP>(R, nc, N, rpt, nr, rw, f, f, mask, lane);
+      asm volatile("" ::: "memory");
+      acc = fragment_sums_q4<KS>(R.act, R.xm, st, lane);
+    } else {
+      if (f + D < NF)
+        stage<KS>(R.w[0], st, L, frag_base<WT, GATEUP>(c, rpt, r, rw, f + D), L, ~0u,
+                  lane);
+      else
+        stage<KS>(R.w[0], st, L, frag_base<WT, GATEUP>(nc, rpt, nr, rw, f + D - NF), N,
+                  mask, lane);
+      asm volatile("" ::: "memory");
+      acc = fragment_sums<KS>(R.act, st, lane);
+    }
+    asm volatile("" ::: "memory");
+    put_partial<WT>(buf, acc, f, c.nt, wave, lane);
+  }
+}
+
+// The block's tiles [lo, hi), hi > lo.
+template <typename WT, int KS, bool GATEUP>
+__device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int hi, int lkw,
+                                       float* red, int lane, int wave) {
+  const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.rpt;
   int v, r;
   tl.locate(lo, v, r);
   Slice c = tl.slice(v);
-  Lanes<KS> L = lanes_of<KS>(c, tl.tb, ks, lkw, lane);
-  u32x4 act[KS][3], w[KS];
-  f32x4 acc[2];
-  char* st = reinterpret_cast<char*>(red + kRedFloats) + wave * 16 * kRowUnits<KS> * 16;
-  const auto base = [&](const Slice& s, int tr, int i) {
-    if (GATEUP) return uni(s.w + (size_t)frag_row<true>(s, tl.rpt, tr, rw, 0) * s.rb + i * s.w2);
-    return uni(s.w + (size_t)frag_row<false>(s, tl.rpt, tr, rw, i) * s.rb);
-  };
-  {
-    const char* p0 = base(c, r, 0);
+  Lanes<WT, KS> L = lanes_of<WT, KS>(c, tl.tb, ks, lkw, lane);
+  Regs<WT, KS> R;
+  char* st = reinterpret_cast<char*>(red + kRedFloats<WT>) + wave * kWaveStage<WT, KS>;
 #pragma unroll
-    for (int q = 0; q < KS; ++q) {
-      act[q][0] = ldx(c.act, x_off(L, q, g));
-      act[q][1] = ldx(c.act, x_off(L, q, g) + 16u);
-    }
-#pragma unroll
-    for (int j = 0; j < KS; ++j) w[j] = ldw(p0, L.w[j]);
-  }
-  // The tile's output rows from the waves' partials.
+  for (int f = 0; f < Regs<WT, KS>::kDepth; ++f)
+    issue_fragment<WT, KS, GATEUP>(R, c, L, rpt, r, rw, f, f, ~0u, lane);
   float* buf = red;
-  const auto finish = [&]() {
-    // Partials of the wave: position 4 g + i, row n of both fragments.
-    float* p = buf + wave * 2 * kRedTile + 4 * g * kRedLd + n;
-    if (4 * g < c.nt) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        p[i * kRedLd] = acc[0][i];
-        p[kRedTile + i * kRedLd] = acc[1][i];
-      }
-    }
-    lds_barrier();
-    constexpr int kOut = GATEUP ? 256 : 512;  // outputs of a row group
-    for (int o = threadIdx.x; o < kOut * nrw; o += kBlock) {
-      const int rg = o / kOut, pos = (o / (kOut / 16)) & 15, rr = o & 15;
-      const int i = GATEUP ? 0 : (o >> 4) & 1;
-      const int row = frag_row<GATEUP>(c, tl.rpt, r, rg, i) + rr;
-      if (pos < c.nt && row < c.rows) {
-        const float* q = buf + ((rg << lkw) * 2 + i) * kRedTile + pos * kRedLd + rr;
-        float s = 0.f, u = 0.f;
-        for (int k = 0; k < kw; ++k) {
-          s += q[k * 2 * kRedTile];
-          if constexpr (GATEUP) u += q[k * 2 * kRedTile + kRedTile];
-        }
-        float val;
-        if constexpr (GATEUP)
-          val = silu_f(s) * u;
-        else
-          val = (c.goff >= 0 ? tl.tb.gate[c.goff + pos] : c.gscalar) * s;
-        *(DE_GLOBAL float*)(c.out + (size_t)(c.p0 + pos) * c.ostride + row) = val;
-      }
-    }
-    buf = buf == red ? red + kRedBuf : red;
-  };
-  bool conv = true;
+  bool enter = true;
 #pragma unroll 1
-  for (int left = hi - lo; left > 1; --left) {
-    const bool same = r + 1 < c.tiles;
-    fragment<KS, true>(act, w, acc[0], st, L.row, L.upw, conv, L.ok, L.ragged, base(c, r, 1), L, false,
-                       nullptr, lane);
-    const uint32_t ok = L.ok;
-    const int ragged = L.ragged;
-    const float* nx = nullptr;
-    const char* np;
-    const uint32_t rows = L.row;
-    const int upw = L.upw;
-    if (same) {
-      np = base(c, r + 1, 0);
-    } else {
-      const Slice ns = tl.slice(v + 1);
-      L = lanes_of<KS>(ns, tl.tb, ks, lkw, lane);
-      np = base(ns, 0, 0);
-      nx = ns.act;
+  for (int left = hi - lo; left > 0; --left) {
+    if (enter) enter_slice<WT, KS>(R, c, L, st, lane);
+    // The tile after this one.
+    Slice nc = c;
+    Lanes<WT, KS> N = L;
+    int nr = r + 1;
+    const bool more = left > 1, fresh = more && nr >= c.tiles;
+    if (fresh) {
+      nc = tl.slice(++v);
+      N = lanes_of<WT, KS>(nc, tl.tb, ks, lkw, lane);
     }
-    fragment<KS, true>(act, w, acc[1], st, rows, upw, false, ok, ragged, np, L, !same, nx, lane);
-    finish();
-    conv = !same;
-    if (same) {
-      ++r;
-    } else {
-      ++v;
-      r = 0;
-      c = tl.slice(v);
-    }
+    if (!more || fresh) nr = more ? 0 : r;
+    tile<WT, KS, GATEUP>(R, c, L, r, nc, N, nr, more ? ~0u : 0u, rpt, rw, st, buf, wave, lane);
+    lds_barrier();
+    tile_outputs<WT, GATEUP>(c, tl.tb, rpt, r, lkw, buf);
+    buf = buf == red ? red + kRedBuf<WT> : red;
+    enter = fresh;
+    c = nc;
+    L = N;
+    r = nr;
   }
-  fragment<KS, true>(act, w, acc[0], st, L.row, L.upw, conv, L.ok, L.ragged, base(c, r, 1), L, false,
-                     nullptr, lane);
-  fragment<KS, false>(act, w, acc[1], st, L.row, L.upw, false, L.ok, L.ragged, nullptr, L, false, nullptr,
-                      lane);
-  finish();
 }
 
 // The member slices: every resident member's positions in groups of 16, in
@@ -551,7 +755,6 @@ __device__ __forceinline__ int32_t* slices_at(const GroupedArgs& a, const Tables
   return reinterpret_cast<int32_t*>(p);
 }
 
-
 // What a block knows of the routed part.
 struct MfmaTables {
   Tables tb;
@@ -562,11 +765,11 @@ struct MfmaTables {
 // The block's tables: the lists (selected and united here in a gate/up launch
 // with fused routing, else read), the members and their slices.  absent and
 // nms are shared words.  Ends with a barrier.
-template <int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP>
 __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane, int wave,
                                                   int* absent, int* nms) {
   MfmaTables mt;
-  mt.tb = tables_at(a, kRedFloats + kStageFloats<KS>);
+  mt.tb = tables_at(a, kRedFloats<WT> + kStageFloats<WT, KS>);
   if (threadIdx.x == 0) {
     *absent = 0;
     *nms = 0;
@@ -601,18 +804,21 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
 }
 
 // One pass over the tables of a block: the slices are known (slc, nms).
-template <int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP>
 __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const Tables& tb,
                                           const int32_t* slc, int nms, int lane, int wave) {
-  Tiles<GATEUP> tl{a, arg, tb, slc, cdiv(a.T, kXP), 0, nms, 0, 0};
-  tl.rpt = (kWavesPB >> a.lkw) * (GATEUP ? 16 : 32);
+  Tiles<WT, GATEUP> tl{a, arg, tb, slc, cdiv(a.T, kXP), 0, nms, 0, 0};
+  tl.rpt = (kWavesPB >> a.lkw) * group_rows<WT, GATEUP>();
   tl.tr = a.has_routed ? uni(cdiv(GATEUP ? a.r.inter : a.H, tl.rpt)) : 1;
-  stream<KS, GATEUP>(a, tl, a.lkw, s_dyn, lane, wave);
+  const int total = tl.count();
+  const int lo = (int)((int64_t)total * blockIdx.x / gridDim.x);
+  const int hi = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
+  if (lo < hi) stream<WT, KS, GATEUP>(tl, lo, hi, a.lkw, s_dyn, lane, wave);
 }
 
-template <int KS>
+template <typename WT, int KS>
 size_t mfma_lds(const GroupedArgs& a) {
-  size_t b = (size_t)(kRedFloats + kStageFloats<KS>)*4 + tables_bytes(a);
+  size_t b = (size_t)(kRedFloats<WT> + kStageFloats<WT, KS>)*4 + tables_bytes(a);
   if (a.has_routed) b += ((size_t)a.r.max_union + a.r.pairs_max / kXP + 1) * 4;
   return b;
 }

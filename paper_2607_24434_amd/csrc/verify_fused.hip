@@ -106,11 +106,11 @@ __global__ __launch_bounds__(kBlock, 2) void verify_fused_kernel(FusedArgs f) {
   __shared__ int s_abort, s_absent, s_nms;
   __shared__ float s_red[kCombThreads / kWave];
   if (threadIdx.x == 0) s_abort = 0;
-  const MfmaTables mt = mfma_tables<kFKS, true>(f.gu, lane, wave, &s_absent, &s_nms);
-  mfma_pass<kFKS, true>(f.gu, offsetof(FusedArgs, gu), mt.tb, mt.slc, mt.nms, lane, wave);
+  const MfmaTables mt = mfma_tables<uint16_t, kFKS, true>(f.gu, lane, wave, &s_absent, &s_nms);
+  mfma_pass<uint16_t, kFKS, true>(f.gu, offsetof(FusedArgs, gu), mt.tb, mt.slc, mt.nms, lane, wave);
   grid_point(f, 1, &s_abort);
   if (s_absent) absent_rows_zero(f.dn, mt.tb, mt.nu);
-  mfma_pass<kFKS, false>(f.dn, offsetof(FusedArgs, dn), mt.tb, mt.slc, mt.nms, lane, wave);
+  mfma_pass<uint16_t, kFKS, false>(f.dn, offsetof(FusedArgs, dn), mt.tb, mt.slc, mt.nms, lane, wave);
   grid_point(f, 2, &s_abort);
   for (int t = blockIdx.x; t < f.c.T; t += gridDim.x) {
     combine_position(f.c, t, s_red);
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kBlock, 2) void verify_fused_kernel(FusedArgs f) {
 }  // namespace
 
 hipError_t launch_verify_fused(const FusedArgs& f, hipStream_t s) {
-  const size_t lds = std::max(mfma_lds<kFKS>(f.gu), (size_t)84 * 1024);
+  const size_t lds = std::max(mfma_lds<uint16_t, kFKS>(f.gu), (size_t)84 * 1024);
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(verify_fused_kernel), lds);
   if (e != hipSuccess) {
     (void)hipGetLastError();

@@ -1,9 +1,10 @@
-"""The grouped passes on the matrix cores (bf16 weights) against the vector-ALU
-passes of the same layer with the same weights held as fp32, on the GPU.
+"""The grouped passes on the matrix cores (bf16 and Q4_0 weights) against the
+vector-ALU passes of the same layer with the same weights held as fp32, on the
+GPU.
 
-The bf16 layer splits each fp32 activation exactly into three bf16 parts, so
-both layers form the same exact products and differ only in the order of fp32
-sums: a 2-norm error of sqrt(terms) 2^-24 per pass, 2.7e-6 at 2048 terms.
+The matrix-core layer splits each fp32 activation exactly into three bf16
+parts, so both layers form the same exact products (Q4_0: of codes, scaled once
+per block) and differ only in the order of fp32 sums: a 2-norm error of sqrt(terms) 2^-24 per pass, 2.7e-6 at 2048 terms.
 Sizes: the edges of the 16-position slices and of the 16-row tiles, columns
 that are not whole steps of 32, fewer rows than a tile, shared and dense
 reductions whose last chunk is narrower, a single column unit.
@@ -29,13 +30,12 @@ def rel(a, b):
     return ((a.double() - b.double()).norm() / b.double().norm()).item()
 
 
-def layer(T, H, N, k, I, Is, x, w, router, f32, kind="verify", slots=None):
-    """One layer call; w: (routed [N, 3 I H], shared, draft) in bf16."""
-    wt = torch.float32 if f32 else torch.bfloat16
-    d = de.make_desc(H, N, k, I, Is, I, de.DE_SOFTMAX, True, 1.0,
-                     de.DE_F32 if f32 else de.DE_BF16)
-    routed, shared, draft = [t.to(wt) if t is not None else None for t in w]
-    tab = de.make_table(routed, de.expert_bytes(de.DE_F32 if f32 else de.DE_BF16, I, H), slots, N)
+def layer(T, H, N, k, I, Is, x, w, router, dt, kind="verify", slots=None):
+    """One layer call; w: (routed [N, 3 I H], shared, draft) in bf16, or their
+    Q4_0 blocks."""
+    d = de.make_desc(H, N, k, I, Is, I, de.DE_SOFTMAX, True, 1.0, dt)
+    routed, shared, draft = [t.float() if t is not None and dt == de.DE_F32 else t for t in w]
+    tab = de.make_table(routed, de.expert_bytes(dt, I, H), slots, N)
     y, normed = torch.empty_like(x), torch.empty_like(x)
     epi = de.make_epilogue(x, normed, 1e-6)
     idx = torch.empty(T, k, dtype=torch.int32, device="cuda")
@@ -69,8 +69,41 @@ def inputs(T, H, N, I, Is, seed):
 def test_layer_matches_the_vector_alu_path(T, H, N, k, I, Is, kind):
     x, w, router = inputs(T, H, N, I, Is, T + H)
     print(kind, T, H, N, k, I, Is, flush=True)
-    a = layer(T, H, N, k, I, Is, x, w, router, False, kind)
-    b = layer(T, H, N, k, I, Is, x, w, router, True, kind)
+    a = layer(T, H, N, k, I, Is, x, w, router, de.DE_BF16, kind)
+    b = layer(T, H, N, k, I, Is, x, w, router, de.DE_F32, kind)
+    assert torch.equal(a[2], b[2]) and a[3] == b[3] == 0
+    assert rel(a[0], b[0]) < TOL and rel(a[1], b[1]) < TOL
+
+
+def q4_blocks(w, n, inter, hidden):
+    """The Q4_0 block [G|U|D] of each of the n experts in w, and the same weights
+    as fp32."""
+    out, back = [], []
+    for m in w.float().view(n, 3, inter * hidden).unbind(1):
+        b = m.view(n, -1, 32)
+        d = (b.gather(2, b.abs().argmax(dim=2, keepdim=True)) / -8.0).half()
+        q = (b / d.float() + 8.5).floor().clamp(0, 15)
+        c = q.to(torch.uint8)
+        codes = (c[:, :, :16] | (c[:, :, 16:] << 4)).reshape(n, -1)
+        out += [codes, d.reshape(n, -1).view(torch.uint8)]
+        back.append(((q - 8.0) * d.float()).view(n, -1))
+    return torch.cat(out, 1).contiguous(), torch.cat(back, 1).contiguous()
+
+
+@pytest.mark.parametrize("T,H,N,k,I,Is", [
+    (2, 32, 4, 2, 32, 32), (16, 96, 5, 3, 64, 160), (17, 288, 6, 6, 160, 0), (5, 544, 8, 2, 32, 608),
+    (64, 512, 4, 4, 128, 256), (9, 2048, 16, 6, 1408, 2816), (33, 1024, 3, 2, 64, 2048 + 1056)])
+@pytest.mark.parametrize("kind", ["verify", "draft"])
+def test_q4_layer_matches_the_vector_alu_path(T, H, N, k, I, Is, kind):
+    x, w, router = inputs(T, H, N, I, Is, T + H)
+    print(kind, T, H, N, k, I, Is, flush=True)
+    q, f = [], []
+    for t, n, i in ((w[0], N, I), (w[1], 1, Is), (w[2], 1, I)):
+        b = q4_blocks(t.view(n, -1), n, i, H) if t is not None else (None, None)
+        q.append(b[0])
+        f.append(b[1])
+    a = layer(T, H, N, k, I, Is, x, q, router, de.DE_Q4_0, kind)
+    b = layer(T, H, N, k, I, Is, x, f, router, de.DE_F32, kind)
     assert torch.equal(a[2], b[2]) and a[3] == b[3] == 0
     assert rel(a[0], b[0]) < TOL and rel(a[1], b[1]) < TOL
 
@@ -78,11 +111,11 @@ def test_layer_matches_the_vector_alu_path(T, H, N, k, I, Is, kind):
 def test_a_position_that_is_not_finite_stays_alone():
     T, H, N, k, I = 18, 136, 4, 4, 40
     x, w, router = inputs(T, H, N, I, I, 3)
-    clean = layer(T, H, N, k, I, I, x, w, router, False)[0]
+    clean = layer(T, H, N, k, I, I, x, w, router, de.DE_BF16)[0]
     x2 = x.clone()
     x2[1, 5] = float("inf")
     x2[17, 100] = float("nan")
-    got = layer(T, H, N, k, I, I, x2, w, router, False)[0]
+    got = layer(T, H, N, k, I, I, x2, w, router, de.DE_BF16)[0]
     rest = [t for t in range(T) if t not in (1, 17)]
     assert torch.equal(got[rest], clean[rest])
     assert not torch.isfinite(got[[1, 17]]).any()
@@ -92,8 +125,8 @@ def test_missing_expert_drops_out_and_is_reported():
     T, H, N, k, I = 20, 264, 4, 4, 40
     x, w, router = inputs(T, H, N, I, I, 4)
     slots = torch.tensor([0, 1, -1, 3], dtype=torch.int32, device="cuda")
-    a = layer(T, H, N, k, I, I, x, w, router, False, slots=slots)
-    b = layer(T, H, N, k, I, I, x, w, router, True, slots=slots)
+    a = layer(T, H, N, k, I, I, x, w, router, de.DE_BF16, slots=slots)
+    b = layer(T, H, N, k, I, I, x, w, router, de.DE_F32, slots=slots)
     assert a[3] == b[3] == -5
     assert rel(a[0], b[0]) < TOL
 
