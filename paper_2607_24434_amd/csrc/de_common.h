@@ -173,6 +173,18 @@ struct CombineArgs {
   float eps;
 };
 
+// Geometry of a matrix-core pass (set by its launcher): the dense sources'
+// slices (column chunks x position groups) and tiles come first, then the
+// members'.
+struct MfmaGeom {
+  int rpt;              // rows (gate/up: pairs) per tile
+  int groups;           // position groups of a dense source
+  int tr;               // tiles per member slice
+  int nds, ndt;         // dense slices, their tiles
+  int v0[3], t0[3];     // first slice and tile of each dense source
+  int tiles[3];         // tiles per slice of each dense source
+};
+
 struct GroupedArgs {
   int T;
   int H;
@@ -183,6 +195,7 @@ struct GroupedArgs {
   DenseSrc dense[3];
   int mfma;            // 1: on the matrix cores (bf16), with lkw
   int lkw;             // log2 of the column slices of a block
+  MfmaGeom geo;
   int lds_floats;      // set by the launcher: staged-input capacity of a block
   // Gate/up only: build the union in every block (block 0 also writes sel's
   // outputs); r.n_union ... r.gate_list are then not read.  The lists come

@@ -365,8 +365,6 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
   __shared__ float s_h[kPDMaxH];                // residual stream
   __shared__ float s_red[kCombVW];
   __shared__ float s_part[kMaxRows * kMaxSrc];
-  __shared__ int32_t s_idx[32];
-  __shared__ float s_sc[32];
   __shared__ int s_e1;
   __shared__ float s_g1;
   __shared__ int s_sel_layer;
@@ -496,36 +494,19 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
             if (lane + q * kWave < a.N) a.z_plain[lane + q * kWave] = z[0][q];
         }
       }
-      // The top-1 expert first, published at once so that its rows load while
-      // the rest of the selection runs: the first round of topk_regs (the
-      // largest key, ties to the lower id), computed the same way, so it is
-      // the list's first entry.
-      {
-        float bk = -INFINITY;
-        int bid = INT_MAX;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int e = lane + q * kWave;
-          if (e >= a.N) continue;
-          const float bias = sel.bias != nullptr ? sel.bias[e] : 0.f;
-          float kk = sel.score_func == 0 ? z[0][q] + bias : 1.0f / (1.0f + expf(-z[0][q])) + bias;
-          if (!(kk == kk)) kk = -INFINITY;
-          if (kk > bk || (kk == bk && e < bid)) {
-            bk = kk;
-            bid = e;
-          }
-        }
-        const float m = wave_max(bk);
-        const int win = wave_min_i32(bk == m ? bid : INT_MAX);
+      // The top-1 expert (the list's first entry) is published as soon as it
+      // is known, so that its rows load while the rest of the selection runs.
+      int id[1];
+      float sv[1];
+      topk_regs<1>(sel, z, id, sv, [&](int win) {
         if (lane == 0) s_e1 = win;
         __hip_atomic_store(&s_sel_layer, l + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+      });
       // The whole list and the gates (g1 is read after the S2 barrier).
-      topk_regs<1>(sel, z, s_idx, s_sc);
+      const float g = topk_gate(sel, sv[0]);
       if (lane < a.k) {
-        const float g = topk_gate(sel, s_sc, lane);
         if (lane == 0) s_g1 = g;
-        if (b == 0 && a.pred_idx != nullptr) a.pred_idx[(size_t)l * a.k + lane] = s_idx[lane];
+        if (b == 0 && a.pred_idx != nullptr) a.pred_idx[(size_t)l * a.k + lane] = id[0];
         if (b == 0 && a.pred_gate != nullptr) a.pred_gate[(size_t)l * a.k + lane] = g;
       }
     };

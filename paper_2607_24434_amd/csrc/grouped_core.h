@@ -313,25 +313,6 @@ __device__ __forceinline__ SelView sel_at(const GroupedArgs& a, const Tables& tb
   return sel_view_at(p, a.T, a.sel.k, a.sel.N);
 }
 
-// The member table from a union built in LDS: member j = the expert with
-// union index j.  All threads; the caller synchronises.
-__device__ __forceinline__ void members_from_union(const GroupedArgs& a, const Tables& tb,
-                                                   const SelView& v, int first, int stride,
-                                                   int* absent) {
-  const RoutedSrc& r = a.r;
-  for (int e = first; e < a.sel.N; e += stride) {
-    const unsigned long long m = v.mask[e];
-    if (m == 0ull) continue;
-    const int slot = e < r.n_experts ? (r.slot_of_expert ? r.slot_of_expert[e] : e) : -1;
-    Member mb{nullptr, v.off[e], (int)__popcll(m), -1, 0};
-    if (slot >= 0 && slot < r.n_slots)
-      mb.blk = r.base + (size_t)slot * r.stride;
-    else
-      *absent = 1;
-    tb.mem[v.upos[e]] = mb;
-  }
-}
-
 __device__ __forceinline__ Tables tables_at(const GroupedArgs& a, int act_floats) {
   Tables tb;
   char* p = reinterpret_cast<char*>(s_dyn + act_floats);
@@ -369,20 +350,40 @@ __device__ __forceinline__ void fill_dense(const GroupedArgs& a, const Tables& t
   if (threadIdx.x == 2 && a.n_dense > 2) tb.dense[2] = a.dense[2];
 }
 
-// Resolves the union members into LDS.  Lists built by the union kernel always
-// pass; caller-supplied ones are checked so that a bad list can only drop
-// work, never read or write out of bounds.  A member with a valid list and no
-// valid slot keeps its list (blk NULL) and sets *absent.  All threads; the
-// caller synchronises.
-__device__ __forceinline__ void fill_tables(const GroupedArgs& a, const Tables& tb, int nu,
-                                            int* absent) {
+__device__ __forceinline__ int routed_count(const GroupedArgs& a) {
+  if (!a.has_routed) return 0;
+  const int nu = uni(*a.r.n_union);
+  return nu < 0 ? 0 : min(nu, a.r.max_union);
+}
+
+// Resolves the union members into LDS; returns their number.  Lists built by
+// the union kernel always pass; caller-supplied ones are checked so that a bad
+// list can only drop work, never read or write out of bounds.  A member with a
+// valid list and no valid slot keeps its list (blk NULL) and sets *absent.
+// Every list entry is loaded whether or not the union reaches it (their
+// capacities are fixed), so that one memory latency covers them and the
+// union's size.  All threads; the caller synchronises.
+__device__ __forceinline__ int fill_tables(const GroupedArgs& a, const Tables& tb, int* absent) {
   const RoutedSrc& r = a.r;
-  for (int j = threadIdx.x; j < nu; j += kBlock) {
+  if (!a.has_routed) return 0;
+  const int j = threadIdx.x;
+  static_assert(kBlock >= 256, "a thread per expert");
+  int e = -1, off = 0, end = 0;
+  if (j < r.max_union) {
+    e = r.union_ids[j];
+    off = r.offsets[j];
+    end = r.offsets[j + 1];
+  }
+  for (int i = threadIdx.x; i < r.pairs_max; i += kBlock) {
+    const int t = r.tok_list[i];
+    tb.tok[i] = t < 0 ? 0 : (t >= a.T ? a.T - 1 : t);  // a position outside the block never indexes x
+    tb.gate[i] = r.gate_list[i];
+  }
+  const int nu = routed_count(a);
+  if (j < nu) {
     Member m{nullptr, 0, 0, -1, 0};
-    const int e = r.union_ids[j];
     const int slot =
         (e >= 0 && e < r.n_experts) ? (r.slot_of_expert ? r.slot_of_expert[e] : e) : -1;
-    const int off = r.offsets[j], end = r.offsets[j + 1];
     if (off >= 0 && end >= off && end <= r.pairs_max) {
       m.off = off;
       m.ntok = end - off;
@@ -393,17 +394,7 @@ __device__ __forceinline__ void fill_tables(const GroupedArgs& a, const Tables& 
     }
     tb.mem[j] = m;
   }
-  for (int i = threadIdx.x; i < r.pairs_max; i += kBlock) {
-    const int t = r.tok_list[i];
-    tb.tok[i] = t < 0 ? 0 : (t >= a.T ? a.T - 1 : t);  // a position outside the block never indexes x
-    tb.gate[i] = r.gate_list[i];
-  }
-}
-
-__device__ __forceinline__ int routed_count(const GroupedArgs& a) {
-  if (!a.has_routed) return 0;
-  const int nu = uni(*a.r.n_union);
-  return nu < 0 ? 0 : min(nu, a.r.max_union);
+  return nu;
 }
 
 // Fused selection: the logits of the wave's first two positions (of a launch
@@ -423,58 +414,142 @@ __device__ __forceinline__ void first_logits(const GroupedArgs& a, int wave, flo
   }
 }
 
+// Positions per matrix-core slice.
+constexpr int kXP = 16;
+
 // The top-k lists (selected here from the logits, or given), then their
 // union, in every block; block 0 also publishes both for the down and combine
-// launches.  Fills the member table and the token and gate lists; returns the
-// number of members.  All threads; ends with a barrier.
+// launches.  Fills the member table, the token and gate lists and (slc not
+// NULL) the resident members' slices of kXP positions, (member << 8) | group,
+// their number to *nms; returns the number of members.  All threads; ends
+// with a barrier.
 __device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& tb,
-                                           float (&z0)[2][4], int lane, int wave, int* absent) {
+                                           float (&z0)[2][4], int lane, int wave, int* absent,
+                                           int32_t* slc = nullptr, int* nms = nullptr) {
   const SelView v = sel_at(a, tb);
-  const int k = a.sel.k;
+  const RoutedSrc& rs = a.r;
+  const int T = a.T, N = a.sel.N, k = a.sel.k, uc = a.sel.ucols;
+  const bool out = blockIdx.x == 0;
+  for (int e = threadIdx.x; e < N; e += kBlock) v.mask[e] = 0ull;
+  if (threadIdx.x == 0) v.misc[0] = 0;
+  __syncthreads();
   if (a.fuse_select) {
     // Wave w selects positions w, w + 8 (two interleaved), then w + 16, ...
-    for (int t = wave; t < a.T; t += 2 * kWavesPB) {
+    for (int t = wave; t < T; t += 2 * kWavesPB) {
       const int t1 = t + kWavesPB;
       if (t != wave) {
-        topk_load(a.sel, a.sel.z + (size_t)t * a.sel.N, z0[0]);
-        if (t1 < a.T) topk_load(a.sel, a.sel.z + (size_t)t1 * a.sel.N, z0[1]);
+        topk_load(a.sel, a.sel.z + (size_t)t * N, z0[0]);
+        if (t1 < T) topk_load(a.sel, a.sel.z + (size_t)t1 * N, z0[1]);
       }
-      if (t1 < a.T) {
-        topk_regs<2>(a.sel, z0, v.idx + t * k, v.sc + t * k, v.idx + t1 * k, v.sc + t1 * k);
+      int id[2];
+      float sv[2];
+      if (t1 < T) {
+        topk_regs<2>(a.sel, z0, id, sv);
       } else {
-        float z1[1][4];
+        float z1[1][4], s1[1];
+        int i1[1];
 #pragma unroll
         for (int q = 0; q < 4; ++q) z1[0][q] = z0[0][q];
-        topk_regs<1>(a.sel, z1, v.idx + t * k, v.sc + t * k);
+        topk_regs<1>(a.sel, z1, i1, s1);
+        id[0] = i1[0];
+        sv[0] = s1[0];
+        id[1] = 0;
+        sv[1] = 0.f;
       }
       const int kr = a.sel.rounds > 0 ? min(a.sel.rounds, k) : k;
+#pragma unroll
       for (int r = 0; r < 2; ++r) {
         const int tt = t + r * kWavesPB;
-        if (tt < a.T && lane < kr) {
-          const float g = topk_gate(a.sel, v.sc + tt * k, lane);
+        if (tt >= T) continue;
+        const float g = topk_gate(a.sel, sv[r]);
+        if (lane < kr) {
+          v.idx[tt * k + lane] = id[r];
           v.gate[tt * k + lane] = g;
-          if (blockIdx.x == 0) {
-            a.sel.idx_out[tt * k + lane] = v.idx[tt * k + lane];
+          if (lane < uc) atomicOr(&v.mask[id[r]], 1ull << tt);
+          if (out) {
+            a.sel.idx_out[tt * k + lane] = id[r];
             a.sel.gate_out[tt * k + lane] = g;
           }
         }
       }
     }
   } else {
-    for (int i = threadIdx.x; i < a.T * k; i += kBlock) {
-      v.idx[i] = a.sel.idx_out[i];
+    // Given lists: an id outside [0, N) or repeated within a position makes
+    // the union invalid.
+    for (int i = threadIdx.x; i < T * k; i += kBlock) {
+      const int e = a.sel.idx_out[i], t = i / k;
+      v.idx[i] = e;
       v.gate[i] = a.sel.gate_out[i];
+      if (i - t * k >= uc) continue;
+      const unsigned long long bit = 1ull << t;
+      if (e < 0 || e >= N || (atomicOr(&v.mask[e], bit) & bit)) v.misc[0] = 1;
     }
   }
   __syncthreads();
+  // The members in ascending id: list offsets and union indices by wave scans.
   if (wave == 0) {
-    build_union_wave(a.sel, v, blockIdx.x == 0, tb.tok, tb.gate);
-    const int n = uni(v.misc[1]);
-    if (n > 0) members_from_union(a, tb, v, lane, kWave, absent);
+    const bool bad = v.misc[0] != 0;
+    int pairs = 0, members = 0, slices = 0;
+    for (int e0 = 0; e0 < N && !bad; e0 += kWave) {
+      const int e = e0 + lane;
+      const unsigned long long m = e < N ? v.mask[e] : 0ull;
+      const int cnt = (int)__popcll(m);
+      const int slot =
+          m != 0ull && e < rs.n_experts ? (rs.slot_of_expert ? rs.slot_of_expert[e] : e) : -1;
+      const int inc = wave_scan_i32(cnt);
+      const unsigned long long in = __builtin_amdgcn_ballot_w64(m != 0ull);
+      const int off = pairs + inc - cnt, up = members + lanes_below(in);
+      const bool here = slot >= 0 && slot < rs.n_slots;
+      if (e < N) v.off[e] = off;
+      if (m != 0ull) {
+        v.upos[e] = up;
+        if (!here) *absent = 1;
+        tb.mem[up] = Member{here ? rs.base + (size_t)slot * rs.stride : nullptr, off, cnt, -1, 0};
+        if (out) {
+          a.sel.union_ids[up] = e;
+          a.sel.offsets[up] = off;
+        }
+      }
+      if (slc != nullptr) {
+        const int ng = here ? (cnt + kXP - 1) / kXP : 0;
+        const int ni = wave_scan_i32(ng);
+        for (int i = 0; i < ng; ++i) slc[slices + ni - ng + i] = (up << 8) | i;
+        slices += __builtin_amdgcn_readlane(ni, 63);
+      }
+      pairs += __builtin_amdgcn_readlane(inc, 63);
+      members += (int)__popcll(in);
+    }
+    if (lane == 0) {
+      v.misc[1] = bad ? -1 : members;
+      v.misc[2] = pairs;
+      if (nms != nullptr) *nms = slices;
+      if (out) *a.sel.n_union = bad ? -1 : members;
+    }
   }
   __syncthreads();
   const int nu = uni(v.misc[1]);
-  return nu < 0 ? 0 : min(nu, a.r.max_union);
+  if (nu < 0) return 0;
+  const int total = uni(v.misc[2]);
+  for (int i = threadIdx.x; i < T * uc; i += kBlock) {
+    const int t = i / uc, j = i - t * uc;
+    const int e = v.idx[t * k + j];
+    const unsigned long long below = t == 0 ? 0ull : (v.mask[e] & (~0ull >> (64 - t)));
+    const int p = v.off[e] + (int)__popcll(below);
+    const float g = v.gate[t * k + j];
+    tb.tok[p] = t;
+    tb.gate[p] = g;
+    if (out) {
+      a.sel.tok_list[p] = t;
+      a.sel.gate_list[p] = g;
+      a.sel.pair_pos[i] = p;
+    }
+  }
+  if (out) {
+    for (int u = nu + threadIdx.x; u < N; u += kBlock) a.sel.union_ids[u] = -1;
+    for (int u = nu + threadIdx.x; u <= N; u += kBlock) a.sel.offsets[u] = total;
+  }
+  __syncthreads();
+  return min(nu, rs.max_union);
 }
 
 // Down: a needed member without a slot contributes zero partials (the combine

@@ -31,17 +31,13 @@ hipError_t launch_ks(const GroupedArgs& a, int tiles, hipStream_t s) {
 }
 
 template <typename WT, bool GATEUP>
-hipError_t launch_typed(const GroupedArgs& a, hipStream_t s) {
-  const int rpt = (kWavesPB >> a.lkw) * group_rows<WT, GATEUP>();
-  const int groups = cdiv(a.T, kXP);
-  int K = GATEUP ? a.H : (a.has_routed ? a.r.inter : 0), tiles = 0;
-  if (a.has_routed)
-    tiles += (a.r.max_union + a.r.pairs_max / kXP) * cdiv(GATEUP ? a.r.inter : a.H, rpt);
-  for (int i = 0; i < a.n_dense; ++i) {
-    const DenseSrc& d = a.dense[i];
-    if (!GATEUP && d.cw > K) K = d.cw;
-    tiles += groups * (GATEUP ? cdiv(d.inter, rpt) : d.chunks * cdiv(d.rows, rpt));
-  }
+hipError_t launch_typed(const GroupedArgs& in, hipStream_t s) {
+  const GroupedArgs a = with_geometry<WT, GATEUP>(in);
+  int K = GATEUP ? a.H : (a.has_routed ? a.r.inter : 0);
+  if (!GATEUP)
+    for (int i = 0; i < a.n_dense; ++i) K = a.dense[i].cw > K ? a.dense[i].cw : K;
+  const int tiles =
+      a.geo.ndt + (a.has_routed ? (a.r.max_union + a.r.pairs_max / kXP) * a.geo.tr : 0);
   if (tiles == 0) return hipSuccess;
   const int ks = cdiv(cdiv(K, 32), 1 << a.lkw);
   if (ks <= 2) return launch_ks<WT, 2, GATEUP>(a, tiles, s);

@@ -45,11 +45,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   fill_dense(a, tb);
   int nu;
   if (a.fuse_route) {
-    nu = route_lists(a, tb, z0, lane, wave, &s_absent);
+    nu = uni(route_lists(a, tb, z0, lane, wave, &s_absent));
   } else {
-    nu = routed_count(a);
     __syncthreads();  // s_absent is initialised
-    if (a.has_routed) fill_tables(a, tb, nu, &s_absent);
+    nu = uni(fill_tables(a, tb, &s_absent));
     __syncthreads();
   }
   // A needed member without a slot: reported once per launch.
@@ -68,7 +67,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     GroupedArgs a) {
   constexpr int EPU = WTr<WT>::EPU;
   const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
-  const int nu = routed_count(a);
   const Tables tb = tables_at(a, a.lds_floats);
   __shared__ int s_absent;
   if (threadIdx.x == 0) s_absent = 0;
@@ -77,7 +75,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   // a launch that uses scratch costs several µs more.
   fill_dense(a, tb);
   __syncthreads();  // s_absent is initialised
-  if (a.has_routed) fill_tables(a, tb, nu, &s_absent);
+  const int nu = uni(fill_tables(a, tb, &s_absent));
   __syncthreads();
   if (s_absent && !a.r.absent_ok) absent_rows_zero(a, tb, nu);
   Layout ly = make_layout<RT>(a, nu, false);

@@ -62,7 +62,6 @@
 namespace de {
 namespace {
 
-constexpr int kXP = 16;                       // positions per slice
 constexpr int kRedLd = 20;                    // LDS partials: row stride (4 extra: no bank conflicts)
 constexpr int kRedTile = kXP * kRedLd;        // one 16 x 16 tile of partials
 template <typename WT>
@@ -151,63 +150,34 @@ struct Tiles {
   int arg;              // where the kernel arguments hold a
   Tables tb;
   const int32_t* slc;   // member slices: (member << 8) | position group
-  int groups;           // position groups of a dense source
-  int nds;              // dense slices
   int nms;              // member slices
-  int rpt;              // rows (gate/up: pairs) per tile
-  int tr;               // tiles per member slice
 
-  __device__ __forceinline__ int dense_tiles(const DenseSrc& d) const {
-    return uni(cdiv(GATEUP ? d.inter : d.rows, rpt));
-  }
-  // Slices of a dense source: its column chunks (down), each with every
-  // position group.
-  __device__ __forceinline__ int dense_slices(const DenseSrc& d) const {
-    return GATEUP ? groups : groups * d.chunks;
-  }
+  __device__ __forceinline__ int total() const { return a.geo.ndt + nms * a.geo.tr; }
 
-  // Sets nds and returns the launch's tiles.
-  __device__ __forceinline__ int count() {
-    int t = nms * tr;
-    nds = 0;
-    for (int s = 0; s < a.n_dense; ++s) {
-      const DenseSrc d = dense_arg(arg, s);
-      nds += dense_slices(d);
-      t += dense_slices(d) * dense_tiles(d);
-    }
-    return t;
-  }
-
-  // The slice and row tile of tile t (t < count()).
+  // The slice and row tile of tile t (t < total()).
   __device__ __forceinline__ void locate(int t, int& v, int& r) const {
-    v = 0;
-    for (int s = 0; s < a.n_dense; ++s) {
-      const DenseSrc d = dense_arg(arg, s);
-      const int dt = dense_tiles(d), ns = dense_slices(d);
-      if (t < ns * dt) {
-        const int i = uni(t / dt);
-        v += i;
-        r = t - i * dt;
-        return;
-      }
-      t -= ns * dt;
-      v += ns;
+    const MfmaGeom& g = a.geo;
+    int base = g.ndt, first = g.nds, tiles = g.tr;
+    if (t < g.ndt) {
+      const int s = (a.n_dense > 2 && t >= g.t0[2]) ? 2 : ((a.n_dense > 1 && t >= g.t0[1]) ? 1 : 0);
+      base = s == 0 ? 0 : (s == 1 ? g.t0[1] : g.t0[2]);
+      first = s == 0 ? 0 : (s == 1 ? g.v0[1] : g.v0[2]);
+      tiles = s == 0 ? g.tiles[0] : (s == 1 ? g.tiles[1] : g.tiles[2]);
     }
-    const int i = uni(t / tr);
-    v = nds + i;
-    r = t - i * tr;
+    const int i = uni((int)((uint32_t)(t - base) / (uint32_t)tiles));
+    v = first + i;
+    r = t - base - i * tiles;
   }
 
   __device__ __forceinline__ Slice slice(int v) const {
     Slice c;
-    if (v < nds) {
-      int s = 0, i = v;
-      DenseSrc d = dense_arg(arg, 0);
-      while (i >= dense_slices(d)) {  // v < nds: ends at a source
-        i -= dense_slices(d);
-        d = dense_arg(arg, ++s);
-      }
-      const int ch = uni(i / groups), g = i - ch * groups;
+    const MfmaGeom& geo = a.geo;
+    if (v < geo.nds) {
+      const int s = (a.n_dense > 2 && v >= geo.v0[2]) ? 2 : ((a.n_dense > 1 && v >= geo.v0[1]) ? 1 : 0);
+      const int i = v - (s == 0 ? 0 : (s == 1 ? geo.v0[1] : geo.v0[2]));
+      const DenseSrc d = dense_arg(arg, s);
+      // One group (up to 16 positions) is the common case.
+      const int ch = geo.groups == 1 ? i : uni(i / geo.groups), g = i - ch * geo.groups;
       c.w = static_cast<const char*>(d.w);
       c.p0 = g * kXP;
       c.nt = min(kXP, a.T - c.p0);
@@ -239,9 +209,9 @@ struct Tiles {
       c.srb = c.rb >> 3;
       c.sc = GATEUP ? c.w + (size_t)c.rows * c.rb
                     : static_cast<const char*>(d.ws) + (size_t)ch * (d.cw >> 4);
-      c.tiles = uni(cdiv(c.rows, rpt));
+      c.tiles = s == 0 ? geo.tiles[0] : (s == 1 ? geo.tiles[1] : geo.tiles[2]);
     } else {
-      const int e = uni(slc[v - nds]);
+      const int e = uni(slc[v - geo.nds]);
       const int j = e >> 8, m0 = (e & 255) * kXP;
       const Member mb = tb.mem[j];
       const char* blk = uni(mb.blk);
@@ -276,7 +246,7 @@ struct Tiles {
       }
       c.srb = c.rb >> 3;
       c.sc = c.w + (size_t)c.rows * c.rb;
-      c.tiles = tr;
+      c.tiles = geo.tr;
     }
     return c;
   }
@@ -617,15 +587,19 @@ __device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
   }
 }
 
-// Loads a slice's activations and makes operands of them; the wave's LDS rows
-// are cleared (units past the wave's columns stay zero).  The loads are used
-// at once: left in flight into the next tile, where they may or may not be,
-// they would make every tile wait for all loads but its newest.
+// The loads of a slice's activations (as fp32 values).
 template <typename WT, int KS>
-__device__ __forceinline__ void enter_slice(Regs<WT, KS>& R, const Slice& c,
-                                            const Lanes<WT, KS>& L, char* st, int lane) {
+__device__ __forceinline__ void load_slice(Regs<WT, KS>& R, const Slice& c, const Lanes<WT, KS>& L,
+                                           int lane) {
 #pragma unroll
   for (int q = 0; q < KS; ++q) load_x<WT, KS>(R.act[q], c.act, L, q, lane >> 4);
+}
+
+// Makes operands of them; the wave's LDS rows are cleared (units past the
+// wave's columns stay zero).
+template <typename WT, int KS>
+__device__ __forceinline__ void enter_slice(Regs<WT, KS>& R, const Lanes<WT, KS>& L, char* st,
+                                            int lane) {
   const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = 0; i < kWaveStage<WT, KS>; i += kWave * 16)
@@ -691,21 +665,23 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
 template <typename WT, int KS, bool GATEUP>
 __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int hi, int lkw,
                                        float* red, int lane, int wave) {
-  const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.rpt;
+  const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.a.geo.rpt;
   int v, r;
   tl.locate(lo, v, r);
   Slice c = tl.slice(v);
   Lanes<WT, KS> L = lanes_of<WT, KS>(c, tl.tb, ks, lkw, lane);
   Regs<WT, KS> R;
   char* st = reinterpret_cast<char*>(red + kRedFloats<WT>) + wave * kWaveStage<WT, KS>;
+  // The first activations go out before the weights: they arrive first and
+  // are split while the weights are on their way.
+  load_slice<WT, KS>(R, c, L, lane);
 #pragma unroll
   for (int f = 0; f < Regs<WT, KS>::kDepth; ++f)
     issue_fragment<WT, KS, GATEUP>(R, c, L, rpt, r, rw, f, f, ~0u, lane);
+  enter_slice<WT, KS>(R, L, st, lane);
   float* buf = red;
-  bool enter = true;
 #pragma unroll 1
   for (int left = hi - lo; left > 0; --left) {
-    if (enter) enter_slice<WT, KS>(R, c, L, st, lane);
     // The tile after this one.
     Slice nc = c;
     Lanes<WT, KS> N = L;
@@ -720,7 +696,13 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int 
     lds_barrier();
     tile_outputs<WT, GATEUP>(c, tl.tb, rpt, r, lkw, buf);
     buf = buf == red ? red + kRedBuf<WT> : red;
-    enter = fresh;
+    // A later slice's are used at once: left in flight into the next tile,
+    // where they may or may not be, they would make every tile wait for all
+    // loads but its newest.
+    if (fresh) {
+      load_slice<WT, KS>(R, nc, N, lane);
+      enter_slice<WT, KS>(R, N, st, lane);
+    }
     c = nc;
     L = N;
     r = nr;
@@ -735,14 +717,8 @@ __device__ __forceinline__ int member_slices(const Tables& tb, int nu, int32_t* 
     const int j = j0 + lane;
     int ng = 0;
     if (j < nu && tb.mem[j].blk != nullptr) ng = (tb.mem[j].ntok + kXP - 1) / kXP;
-    int inc = ng;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int up = __shfl_up(inc, o, kWave);
-      if (lane >= o) inc += up;
-    }
-    const int at = base + inc - ng;
-    for (int i = 0; i < ng; ++i) slc[at + i] = (j << 8) | i;
+    const int inc = wave_scan_i32(ng);
+    for (int i = 0; i < ng; ++i) slc[base + inc - ng + i] = (j << 8) | i;
     base += __builtin_amdgcn_readlane(inc, 63);
   }
   return base;
@@ -774,26 +750,25 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
     *absent = 0;
     *nms = 0;
   }
-  mt.nu = 0;
+  int32_t* slc = slices_at(a, mt.tb);
+  mt.slc = slc;
   if (GATEUP && a.fuse_route) {
     float z0[2][4];
     first_logits(a, wave, z0);
-    __syncthreads();  // absent is initialised
-    mt.nu = route_lists(a, mt.tb, z0, lane, wave, absent);
-  } else {
-    mt.nu = routed_count(a);
+    // (route_lists starts with a barrier: absent is initialised.)
+    mt.nu = uni(route_lists(a, mt.tb, z0, lane, wave, absent, slc, nms));
+  } else if (a.has_routed) {
     __syncthreads();
-    if (a.has_routed) fill_tables(a, mt.tb, mt.nu, absent);
+    mt.nu = uni(fill_tables(a, mt.tb, absent));
     __syncthreads();
-  }
-  int32_t* slc = slices_at(a, mt.tb);
-  mt.slc = slc;
-  if (a.has_routed) {
     if (wave == 0) {
       const int c = member_slices(mt.tb, mt.nu, slc, lane);
       if (lane == 0) *nms = c;
     }
     __syncthreads();
+  } else {
+    mt.nu = mt.nms = 0;
+    return mt;
   }
   mt.nms = uni(*nms);
   // A needed member without a slot: reported once per layer.
@@ -807,13 +782,33 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
 template <typename WT, int KS, bool GATEUP>
 __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const Tables& tb,
                                           const int32_t* slc, int nms, int lane, int wave) {
-  Tiles<WT, GATEUP> tl{a, arg, tb, slc, cdiv(a.T, kXP), 0, nms, 0, 0};
-  tl.rpt = (kWavesPB >> a.lkw) * group_rows<WT, GATEUP>();
-  tl.tr = a.has_routed ? uni(cdiv(GATEUP ? a.r.inter : a.H, tl.rpt)) : 1;
-  const int total = tl.count();
-  const int lo = (int)((int64_t)total * blockIdx.x / gridDim.x);
-  const int hi = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
+  const Tiles<WT, GATEUP> tl{a, arg, tb, slc, nms};
+  // The block's share of the tiles: contiguous, sizes differing by one.
+  const uint32_t total = tl.total(), each = uni((int)(total / gridDim.x));
+  const uint32_t rest = total - each * gridDim.x;
+  const int lo = (int)(blockIdx.x * each + min(blockIdx.x, rest));
+  const int hi = lo + (int)(each + (blockIdx.x < rest ? 1u : 0u));
   if (lo < hi) stream<WT, KS, GATEUP>(tl, lo, hi, a.lkw, s_dyn, lane, wave);
+}
+
+// Host side: a with the geometry of its pass.
+template <typename WT, bool GATEUP>
+GroupedArgs with_geometry(GroupedArgs a) {
+  MfmaGeom& g = a.geo;
+  g.rpt = (kWavesPB >> a.lkw) * group_rows<WT, GATEUP>();
+  g.groups = cdiv(a.T, kXP);
+  g.tr = a.has_routed ? cdiv(GATEUP ? a.r.inter : a.H, g.rpt) : 1;
+  g.nds = g.ndt = 0;
+  for (int i = 0; i < a.n_dense; ++i) {
+    const DenseSrc& d = a.dense[i];
+    g.v0[i] = g.nds;
+    g.t0[i] = g.ndt;
+    g.tiles[i] = cdiv(GATEUP ? d.inter : d.rows, g.rpt);
+    const int ns = g.groups * (GATEUP ? 1 : d.chunks);
+    g.nds += ns;
+    g.ndt += ns * g.tiles[i];
+  }
+  return a;
 }
 
 template <typename WT, int KS>

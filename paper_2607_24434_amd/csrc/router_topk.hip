@@ -45,8 +45,6 @@ __device__ inline SelView view_of(SelShared& s) {
 // written on other XCDs are visible; the counter is left at zero) selects the
 // position's ordered top-k and gates.
 __global__ __launch_bounds__(kRsThreads) void route_split_kernel(RouteArgs r) {
-  __shared__ int32_t lidx[kMaxK];
-  __shared__ float lsc[kMaxK];
   __shared__ int s_last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Block L is (position L / G, expert group L % G): workgroups go to the
@@ -75,12 +73,16 @@ __global__ __launch_bounds__(kRsThreads) void route_split_kernel(RouteArgs r) {
   __syncthreads();
   if (!s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (wave == 0) topk_row(r.sel, r.z + (size_t)t * N, lidx, lsc);
-  __syncthreads();
-  if (threadIdx.x < k) {
-    const int i = t * k + threadIdx.x;
-    r.sel.idx_out[i] = lidx[threadIdx.x];
-    r.sel.gate_out[i] = topk_gate(r.sel, lsc, threadIdx.x);
+  if (wave == 0) {
+    float z[1][4], sv[1];
+    int id[1];
+    topk_load(r.sel, r.z + (size_t)t * N, z[0]);
+    topk_regs<1>(r.sel, z, id, sv);
+    const float g = topk_gate(r.sel, sv[0]);
+    if (lane < k) {
+      r.sel.idx_out[t * k + lane] = id[0];
+      r.sel.gate_out[t * k + lane] = g;
+    }
   }
 }
 

@@ -5,7 +5,11 @@
 // the union.
 //
 // Selection: one wave per position, k rounds of a wave-wide argmax (largest
-// key, ties to the lower id).  Gates are normalised in list order.
+// key, ties to the lower id).  Gates are normalised in list order.  It runs in
+// the prologue of every gate/up block, so its latency is the layer's: with up
+// to 64 experts a lane holds one candidate and a round is one wave max of
+// whole numbers and one ballot (with four float candidates per lane and a wave
+// min for the id, two positions took 2.8 us).
 //
 // Union: integer work only.  Every (position, slot) entry sets its position
 // bit in the expert's 64-bit mask with an LDS atomic OR (a bit already set
@@ -62,124 +66,164 @@ __device__ __forceinline__ void topk_load(const TopkUnionArgs& a, const float* z
   }
 }
 
+// Inclusive sum over the lanes of a wave (no LDS): four shifts inside the
+// 16-lane rows, then the rows' totals.
+__device__ __forceinline__ int wave_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
+// Set bits of `mask` below the lane.
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Largest value of a wave (0: smaller than every key).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  int v = (int)x;
+  const auto mx = [](int p, int q) { return (int)max((uint32_t)p, (uint32_t)q); };
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+  return (uint32_t)__builtin_amdgcn_readlane(v, 63);
+}
+
+// Order-preserving whole number of a selection key, never 0; -0 and 0 are the
+// same key, a NaN counts as -inf.
+__device__ __forceinline__ uint32_t key_bits(float v) {
+  if (!(v == v)) v = -INFINITY;
+  const uint32_t u = __float_as_uint(v + 0.0f);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Ordered top-k of R positions at once from their logits in registers (R
-// independent chains interleaved, so their reduction latencies overlap):
-// ids into idx0 / idx1 [0..k), scores into sc0 / sc1 [0..k).  Each of the k rounds
-// takes the largest remaining key, ties to the lower id: every lane offers
-// its best remaining candidate, a wave max finds the key, a wave min the
-// lowest id offering it, and the owning lane records and retires it.  A NaN
-// key counts as -inf; a candidate id >= N never competes.  With a.rounds
-// set, only that many leading entries are selected.  One wave.
-template <int R>
-__device__ __forceinline__ void topk_regs(const TopkUnionArgs& a, const float (&z)[R][4],
-                                          int32_t* idx0, float* sc0, int32_t* idx1 = nullptr,
-                                          float* sc1 = nullptr) {
+// independent chains interleaved, so their latencies overlap), for
+// N <= 64 NQ: lane j < k receives entry j's id and score.  Each of the k
+// rounds takes the largest remaining key, ties to the lower id: a wave max
+// finds the key and ballots find who holds it (candidate q of lane l is expert
+// l + 64 q, so the first set bit of the first ballot is the lowest id).  A
+// candidate id >= N never competes.  With a.rounds set, only that many leading
+// entries are selected.  first(id): called once the leading entry is known
+// (R = 1).  One wave.
+template <int R, int NQ, class First>
+__device__ __forceinline__ void topk_rounds(const TopkUnionArgs& a, const float (&z)[R][4],
+                                            int (&id)[R], float (&sv)[R], const First& first) {
   const int lane = threadIdx.x & 63;
   const int N = a.N, k = a.k;
-  float key[R][4], sc[R][4];
-  bool left[R][4];
+  float key[R][NQ], sc[R][NQ];
+  uint32_t kb[R][NQ];  // the remaining candidates' keys; 0: none
 #pragma unroll
   for (int r = 0; r < R; ++r) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < NQ; ++q) {
       const int e = lane + q * kWave;
-      left[r][q] = e < N;
-      const float b = (left[r][q] && a.bias != nullptr) ? a.bias[e] : 0.f;
-      float kk, sv;
+      const float b = (e < N && a.bias != nullptr) ? a.bias[e] : 0.f;
+      float kk;
       if (a.score_func == 0) {  // softmax(z + b): key z + b
         kk = z[r][q] + b;
-        sv = 0.f;
+        sc[r][q] = 0.f;
       } else {                  // sigmoid(z): key sigmoid(z) + b
-        sv = 1.0f / (1.0f + expf(-z[r][q]));
-        kk = sv + b;
+        sc[r][q] = 1.0f / (1.0f + expf(-z[r][q]));
+        kk = sc[r][q] + b;
       }
       if (!(kk == kk)) kk = -INFINITY;  // a NaN never wins
-      key[r][q] = left[r][q] ? kk : -INFINITY;
-      sc[r][q] = sv;
+      key[r][q] = e < N ? kk : -INFINITY;
+      kb[r][q] = e < N ? key_bits(kk) : 0u;
+    }
+    id[r] = 0;
+  }
+  float top[R];  // the largest key
+  const int kr = a.rounds > 0 ? min(a.rounds, k) : k;
+  for (int j = 0; j < kr; ++j) {
+    uint32_t m[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      m[r] = kb[r][0];
+#pragma unroll
+      for (int q = 1; q < NQ; ++q) m[r] = max(m[r], kb[r][q]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) m[r] = wave_max_u32(m[r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      int win = 0;
+#pragma unroll
+      for (int q = NQ - 1; q >= 0; --q) {
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(kb[r][q] == m[r]);
+        if (b != 0ull) win = q * kWave + (int)__builtin_ctzll(b);
+      }
+      if (j == 0) {
+        first(win);
+        const uint32_t u = (m[r] & 0x80000000u) ? (m[r] & 0x7fffffffu) : ~m[r];
+        top[r] = __uint_as_float(u);
+      }
+      if (lane == j) id[r] = win;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (lane + q * kWave == win) kb[r][q] = 0u;
     }
   }
   if (a.score_func == 0) {
-    float m[R], sum[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      m[r] = -INFINITY;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (left[r][q]) m[r] = fmaxf(m[r], key[r][q]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) m[r] = wave_max(m[r]);
-    float ex[R][4];
+    float ex[R][NQ], sum[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       sum[r] = 0.f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        ex[r][q] = left[r][q] ? expf(key[r][q] - m[r]) : 0.f;
+      for (int q = 0; q < NQ; ++q) {
+        ex[r][q] = lane + q * kWave < N ? expf(key[r][q] - top[r]) : 0.f;
         sum[r] += ex[r][q];
       }
     }
+    // (Candidates that no lane holds add zeros, as every NQ does.)
 #pragma unroll
     for (int r = 0; r < R; ++r) sum[r] = wave_sum(sum[r]);
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sc[r][q] = ex[r][q] / sum[r];
+      for (int q = 0; q < NQ; ++q) sc[r][q] = ex[r][q] / sum[r];
   }
-  const int kr = a.rounds > 0 ? min(a.rounds, k) : k;
-  for (int j = 0; j < kr; ++j) {
-    float bk[R];
-    int bid[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      bk[r] = -INFINITY;
-      bid[r] = INT_MAX;
+  for (int r = 0; r < R; ++r) {
+    sv[r] = 0.f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = lane + q * kWave;
-        if (left[r][q] && (key[r][q] > bk[r] || (key[r][q] == bk[r] && e < bid[r]))) {
-          bk[r] = key[r][q];
-          bid[r] = e;
-        }
-      }
-    }
-    float m[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) m[r] = wave_max(bk[r]);
-    int win[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) win[r] = wave_min_i32(bk[r] == m[r] ? bid[r] : INT_MAX);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (bid[r] == win[r]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (q == (win[r] >> 6)) {
-            left[r][q] = false;
-            (r == 0 ? idx0 : idx1)[j] = win[r];
-            (r == 0 ? sc0 : sc1)[j] = sc[r][q];
-          }
-        }
-      }
+    for (int q = 0; q < NQ; ++q) {
+      const float s = __shfl(sc[r][q], id[r] & 63, kWave);
+      if (id[r] >> 6 == q) sv[r] = s;
     }
   }
 }
 
-// Ordered top-k of one position from its N logits zrow (one wave).
-__device__ inline void topk_row(const TopkUnionArgs& a, const float* zrow, int32_t* idx,
-                                float* sc_out) {
-  float z[1][4];
-  topk_load(a, zrow, z[0]);
-  topk_regs<1>(a, z, idx, sc_out);
+struct NoFirst {
+  __device__ __forceinline__ void operator()(int) const {}
+};
+
+template <int R, class First = NoFirst>
+__device__ __forceinline__ void topk_regs(const TopkUnionArgs& a, const float (&z)[R][4],
+                                          int (&id)[R], float (&sv)[R],
+                                          const First& first = First()) {
+  if (a.N <= kWave)
+    topk_rounds<R, 1>(a, z, id, sv, first);
+  else
+    topk_rounds<R, 4>(a, z, id, sv, first);
 }
 
-// Gate of list entry j of a position from the list's scores: score_j
-// (/ sum of the k scores in list order) * routed_scale.
-__device__ inline float topk_gate(const TopkUnionArgs& a, const float* sc, int j) {
-  float g = sc[j];
+// Gate of list entry `lane` of a position from the list's scores (lane j:
+// entry j): score (/ sum of the k scores in list order) * routed_scale.
+__device__ __forceinline__ float topk_gate(const TopkUnionArgs& a, float sv) {
+  float g = sv;
   if (a.norm_topk) {
     float gsum = 0.f;
-    for (int i = 0; i < a.k; ++i) gsum += sc[i];
+    for (int i = 0; i < a.k; ++i)
+      gsum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sv), i));
     g = g / gsum;
   }
   return g * a.routed_scale;
@@ -288,99 +332,6 @@ __device__ inline void build_union(const TopkUnionArgs& a, const SelView& s, boo
     }
   }
   __syncthreads();
-}
-
-// The union of build_union by one wave, with no block barrier (the caller
-// synchronises the block afterwards): position masks by LDS atomics, the
-// expert scan, and the lists.  Same results as build_union.
-__device__ inline void build_union_wave(const TopkUnionArgs& a, const SelView& s, bool write_out,
-                                        int32_t* ptok, float* pgate) {
-  const int lane = threadIdx.x & 63;
-  const int T = a.T, N = a.N, k = a.k, uc = a.ucols;
-  for (int e = lane; e < N; e += kWave) s.mask[e] = 0ull;
-  bool bad = false;
-  for (int i = lane; i < T * uc; i += kWave) {
-    const int t = i / uc, j = i - t * uc;
-    const int e = s.idx[t * k + j];
-    if (e < 0 || e >= N) {
-      bad = true;
-    } else {
-      const unsigned long long bit = 1ull << t;
-      const unsigned long long old = atomicOr(&s.mask[e], bit);
-      if (old & bit) bad = true;
-    }
-  }
-  if (__ballot(bad) != 0ull) {
-    if (lane == 0) {
-      s.misc[1] = -1;
-      s.misc[2] = 0;
-      if (write_out) *a.n_union = -1;
-    }
-    return;
-  }
-  int cnt[4], flg[4], csum = 0, fsum = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = lane * 4 + q;
-    const unsigned long long m = e < N ? s.mask[e] : 0ull;
-    cnt[q] = (int)__popcll(m);
-    flg[q] = m != 0ull;
-    csum += cnt[q];
-    fsum += flg[q];
-  }
-  int ci = csum, fi = fsum;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int cu = __shfl_up(ci, o, kWave);
-    const int fu = __shfl_up(fi, o, kWave);
-    if (lane >= o) {
-      ci += cu;
-      fi += fu;
-    }
-  }
-  int cbase = ci - csum, fbase = fi - fsum;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = lane * 4 + q;
-    if (e < N) {
-      s.off[e] = cbase;
-      s.upos[e] = fbase;
-    }
-    cbase += cnt[q];
-    fbase += flg[q];
-  }
-  const int nu = __builtin_amdgcn_readlane(fi, 63), total = __builtin_amdgcn_readlane(ci, 63);
-  if (lane == 0) {
-    s.misc[1] = nu;
-    s.misc[2] = total;
-  }
-  if (write_out) {
-    for (int e = lane; e < N; e += kWave) {
-      if (s.mask[e] != 0ull) {
-        a.union_ids[s.upos[e]] = e;
-        a.offsets[s.upos[e]] = s.off[e];
-      }
-    }
-    for (int u = nu + lane; u < N; u += kWave) a.union_ids[u] = -1;
-    for (int u = nu + lane; u <= N; u += kWave) a.offsets[u] = total;
-    if (lane == 0) *a.n_union = nu;
-  }
-  for (int i = lane; i < T * uc; i += kWave) {
-    const int t = i / uc, j = i - t * uc;
-    const int e = s.idx[t * k + j];
-    const unsigned long long below = t == 0 ? 0ull : (s.mask[e] & (~0ull >> (64 - t)));
-    const int p = s.off[e] + (int)__popcll(below);
-    const float g = s.gate[t * k + j];
-    if (write_out) {
-      a.tok_list[p] = t;
-      a.gate_list[p] = g;
-      a.pair_pos[i] = p;
-    }
-    if (ptok != nullptr) {
-      ptok[p] = t;
-      pgate[p] = g;
-    }
-  }
 }
 
 // Router logit of one expert (Eq. 1) by one wave: the dot product of the

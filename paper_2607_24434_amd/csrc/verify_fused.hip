@@ -127,7 +127,10 @@ hipError_t launch_verify_fused(const FusedArgs& f, hipStream_t s) {
     (void)hipGetLastError();
     return note_hip(e);
   }
-  hipLaunchKernelGGL(verify_fused_kernel, dim3(dev_info().num_cus), dim3(kBlock), lds, s, f);
+  FusedArgs a = f;
+  a.gu = with_geometry<uint16_t, true>(f.gu);
+  a.dn = with_geometry<uint16_t, false>(f.dn);
+  hipLaunchKernelGGL(verify_fused_kernel, dim3(dev_info().num_cus), dim3(kBlock), lds, s, a);
   return note_hip(hipGetLastError());
 }
 
