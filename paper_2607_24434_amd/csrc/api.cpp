@@ -10,6 +10,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
+#include <mutex>
 #include <cstring>
 
 namespace de {
@@ -548,17 +549,62 @@ bool pd_single_enabled() {
   return e == nullptr || e[0] != '0';
 }
 
+// What the persistent launches of a device know of each other.  The blocks of
+// one wait for each other, so all of them have to be resident: two launches on
+// two streams could each hold a part of the chip.  A launch therefore joins
+// only its own stream's, or goes out once the last one's blocks need nothing
+// more of the chip (its epoch is then in *done, which it writes).
+struct PDDevice {
+  std::mutex mu;
+  bool asked = false;
+  uint32_t* done = nullptr;  // pinned host word; NULL: not available
+  hipStream_t stream = nullptr;
+  uint32_t epoch = 0;        // the last launch's; 0: none yet
+};
+constexpr int kPDDevices = 64;
+
+PDDevice* pd_device() {
+  static PDDevice devs[kPDDevices];
+  const int i = dev_info().device;
+  return i >= 0 && i < kPDDevices ? &devs[i] : nullptr;
+}
+
+// True when a persistent launch may go to stream s now (p.mu is held).
+bool pd_may_launch(PDDevice& p, hipStream_t s) {
+  // Under capture a replay would find its own epoch in the flags.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (!p.asked) {
+    p.asked = true;
+    void* w = nullptr;
+    if (hipHostMalloc(&w, sizeof(uint32_t), hipHostMallocMapped) == hipSuccess) {
+      p.done = static_cast<uint32_t*>(w);
+      __atomic_store_n(p.done, 0u, __ATOMIC_RELAXED);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  if (p.done == nullptr) return false;
+  if (p.epoch == 0 || __atomic_load_n(p.done, __ATOMIC_ACQUIRE) == p.epoch) return true;
+  // (One handle stands for every thread's own stream.)
+  return s == p.stream && s != hipStreamPerThread;
+}
+
 // Runs draft layers layers[0..n) (n >= 1) of one position (T = 1, the top-1
 // drafter of Eq. 5) in persistent launches of at most kPDMaxLayers layers.  x_in is the
 // first layer's input RMSNorm(h), h_in its residual (NULL: y = layer(x));
 // z_ready: the first layer's router logits are already in the workspace's
 // logit row.  Returns kPDNotApplicable, before enqueueing anything, when the
-// shape or the layers do not fit the kernel.
+// shape or the layers do not fit the kernel, another stream's launch is under
+// way or the stream is being captured.
 int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, const float* x_in,
                          const float* h_in, bool z_ready, float* y_out, float* normed_out,
                          int32_t* pred_idx, float* pred_gate, float eps, void* ws,
                          size_t ws_bytes, hipStream_t s) {
-  if (!draft_persistent_enabled() || n < 1 || d.wdtype != DE_BF16) return kPDNotApplicable;
+  if (!draft_persistent_enabled() || n < 1 || d.wdtype == DE_F32) return kPDNotApplicable;
   if (ws == nullptr || ws_bytes < layout(d, 1).total) return kPDNotApplicable;
   if (n > kPDMaxLayers && normed_out == nullptr) return kPDNotApplicable;
   // Every layer with a draft block, or none (then the term is dropped).
@@ -572,12 +618,18 @@ int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, con
   const int chunks =
       d.shared_inter > 0 ? shared_chunks(d.shared_inter, 1, max_chunks, elem_align(d.wdtype), d.inter)
                          : 0;
-  const PDShape sh{d.hidden, d.n_experts, d.top_k, d.inter, d.shared_inter,
+  const PDShape sh{d.wdtype, d.hidden, d.n_experts, d.top_k, d.inter, d.shared_inter,
                    has_draft ? d.draft_inter : 0, chunks, chunks > 0 ? d.shared_inter / chunks : 0};
   const int grid = dev_info().num_cus;
   if (!draft_persistent_fits(sh, grid, nullptr, nullptr)) return kPDNotApplicable;
+  PDDevice* const dev = pd_device();
+  if (dev == nullptr) return kPDNotApplicable;
+  std::lock_guard<std::mutex> lock(dev->mu);
+  if (!pd_may_launch(*dev, s)) return kPDNotApplicable;
   const Layout L = layout(d, 1);
   PDArgs a{};
+  a.wdtype = d.wdtype;
+  a.done = dev->done;
   a.H = d.hidden;
   a.N = d.n_experts;
   a.k = d.top_k;
@@ -624,6 +676,8 @@ int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, con
         return kPDNotApplicable;
       return DE_ERR_HIP;
     }
+    dev->stream = s;
+    dev->epoch = a.epoch;
   }
   return DE_OK;
 }

@@ -9,7 +9,7 @@ constexpr int kPDMaxH = 2048;      // hidden size the kernel keeps in LDS
 constexpr int kPDMaxLayers = 32;   // layers per launch (their descriptors ride in the kernel arguments)
 constexpr int kPDMaxGrid = 256;    // blocks (one per CU)
 
-// One MoE layer of the run (bf16 weights).
+// One MoE layer of the run.
 struct PDLayer {
   const float* w_router;          // [N, H] fp32
   const float* bias;              // [N] or NULL
@@ -23,12 +23,14 @@ struct PDLayer {
 };
 
 struct PDShape {
+  int wdtype;                     // DE_BF16 or DE_Q4_0
   int H, N, k, I, Is, Id;
   int n_chunks, chunk;            // the shared down projection in n_chunks column chunks
 };
 
 struct PDArgs {
   int L;                          // layers in this launch
+  int wdtype;                     // of the expert blocks: DE_BF16 or DE_Q4_0
   int H, N, k, I, Is, Id;
   int n_chunks, chunk;
   int has_draft;                  // Id > 0 (every layer has a draft block)
@@ -58,6 +60,7 @@ struct PDArgs {
   // launches are always below this launch's values and nothing is reset.
   uint64_t* grid_flags;           // [grid]
   uint32_t epoch;
+  uint32_t* done;                 // host word that receives the epoch once every block has started its last wait
   int32_t* status;                // device status word
   PDLayer layers[kPDMaxLayers];
 };

@@ -27,6 +27,11 @@
 // position runs the whole stack in one launch; a single layer call runs as a
 // one-layer launch, which is also faster than its separate launches.
 //
+// bf16 and Q4_0 blocks; a hidden size of 512 to 2048 whose rows are whole
+// 16-byte units (lanes past a row's end add zeros).  A Q4_0 layer is 19.5 MB
+// and bound by the chain of latencies above: six V2-Lite layer calls 190 us
+// on four launches each, 153 in one each (bf16, 415 MB: 165).
+//
 // The arithmetic is the one of the separate launches, operation for
 // operation (lane l owns the 16-byte weight units l, l + 64, ...; fp32 FMAs in
 // element order; the same wave reductions; the combine's summation order and
@@ -41,6 +46,7 @@
 // block returns at once, so the launch always ends.
 #include "de_common.h"
 #include "draft_persistent.h"
+#include "grouped_core.h"
 #include "topk_union.h"
 
 #include <cstddef>
@@ -66,16 +72,6 @@ constexpr int kPDMaxA = 6144;      // gate/up outputs of a layer (Is + Id + I)
 constexpr int kPDMaxLogit = 32;    // blocks computing router logits (one expert per wave)
 
 typedef __attribute__((address_space(4))) const char kchar;
-
-// Values that are the same in every lane, moved to scalar registers.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <typename P>
-__device__ __forceinline__ P* uni(P* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<P*>(((uint64_t)hi << 32) | lo);
-}
 
 // Layer l's descriptor, read from the kernel argument segment with a uniform
 // index (scalar loads; a run-time index into a by-value argument would make a
@@ -233,88 +229,151 @@ struct DnDot {
   int src;
 };
 
-template <int GU_IT>
+// 16-byte units in flight, Q4_0: with their scales (fp16 bits).
+template <typename WT, int IT>
+struct Units {
+  u32x4 w[IT];
+  uint32_t sc[kQ4<WT> ? IT : 1];
+};
+
+// The lane's units of a row of L: codes (or values) at w, Q4_0 scales at sc.
+template <typename WT, int IT>
+__device__ __forceinline__ void issue_units(const char* w, const char* sc, int L, Units<WT, IT>& r,
+                                            int lane) {
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const uint32_t u = (uint32_t)min(it * kWave + lane, L - 1);
+    r.w[it] = load_stream16(w + u * 16u);
+    if constexpr (kQ4<WT>) r.sc[it] = *gptr<uint16_t>(sc + u * 2u);
+  }
+}
+
+// Place in LDS of element h of the input rows: Q4_0 units in their
+// bank-conflict-free order (a lane reads a unit's 32 floats).
+template <typename WT>
+__device__ __forceinline__ int act_at(int h) {
+  if constexpr (kQ4<WT>) return q4_slot(h >> 5, (h >> 2) & 7) + (h & 3);
+  return h;
+}
+
+// Dot products of NR rows of L units with the LDS input that starts at unit u0,
+// in the lane order and FMA order of the grouped passes (the lane's part).
+template <typename WT, int IT, int NR>
+__device__ __forceinline__ void dot_units(const Units<WT, IT>* const (&r)[NR], int L,
+                                          const float* as, int u0, int lane, float (&acc)[NR]) {
+  const float4* as4 = reinterpret_cast<const float4*>(as);
+#pragma unroll
+  for (int k = 0; k < NR; ++k) acc[k] = 0.f;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int u = it * kWave + lane;
+    const bool ok = u < L;
+    const int uc = u0 + (ok ? u : L - 1);
+    if constexpr (kQ4<WT>) {
+      float qx[NR], xs = 0.f;
+#pragma unroll
+      for (int k = 0; k < NR; ++k) qx[k] = 0.f;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float xv[16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 x = as4[q4_slot(uc, 4 * h + i) >> 2];
+          xv[4 * i + 0] = x.x; xv[4 * i + 1] = x.y; xv[4 * i + 2] = x.z; xv[4 * i + 3] = x.w;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) xs += xv[v];
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const uint32_t nib = (h ? r[k]->w[it][w] >> 4 : r[k]->w[it][w]) & 0x0F0F0F0Fu;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              qx[k] = fmaf((float)((nib >> (8 * b)) & 0xFFu), xv[4 * w + b], qx[k]);
+          }
+      }
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        const float d = ok ? half_bits_to_float(r[k]->sc[it]) : 0.f;
+        acc[k] = fmaf(d, fmaf(-8.f, xs, qx[k]), acc[k]);
+      }
+    } else {
+      const float4 x0 = as4[uc * 2], x1 = as4[uc * 2 + 1];
+      const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        float w[8];
+        unpack(ok ? r[k]->w[it] : u32x4{0u, 0u, 0u, 0u}, w);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) acc[k] = fmaf(w[v], xv[v], acc[k]);
+      }
+    }
+  }
+}
+
+template <typename WT, int GU_IT>
 struct GURegs {
-  u32x4 g[GU_IT], u[GU_IT];
+  Units<WT, GU_IT> g, u;
 };
 
 // Issues the loads of one (G, U) row pair whose G matrix starts at `blk`
 // (the block's [G|U|D] layout with intermediate `inter`).
-template <int GU_IT>
+template <typename WT, int GU_IT>
 __device__ __forceinline__ void issue_gu(const PDArgs& a, const char* blk, int inter, int row,
-                                         GURegs<GU_IT>& r, int lane) {
-  const int L = a.H / 8;  // 16-byte units per row
-  const size_t rb = (size_t)a.H * 2;
+                                         GURegs<WT, GU_IT>& r, int lane) {
+  const size_t rb = qrow_bytes<WT>(a.H);
+  const int L = (int)(rb >> 4);  // 16-byte units per row
   const char* G = uni(blk + (size_t)row * rb);
-  const char* U = uni(blk + (size_t)inter * rb + (size_t)row * rb);
-#pragma unroll
-  for (int it = 0; it < GU_IT; ++it) {
-    const uint32_t u = (uint32_t)min(it * kWave + lane, L - 1);
-    r.g[it] = load_stream16(G + u * 16u);
-    r.u[it] = load_stream16(U + u * 16u);
-  }
+  const size_t to_u = mat_bytes<WT>(inter, a.H);
+  // Q4_0: a matrix's scales follow its codes, an eighth of a row's bytes each.
+  const char* S = kQ4<WT> ? uni(blk + (size_t)inter * rb + (size_t)row * (rb >> 3)) : nullptr;
+  issue_units<WT, GU_IT>(G, S, L, r.g, lane);
+  issue_units<WT, GU_IT>(G + to_u, S + to_u, L, r.u, lane);
 }
 
-// silu(G x) * (U x) with x from LDS, in the lane order and FMA order of the
-// grouped gate/up kernel.
-template <int GU_IT>
-__device__ __forceinline__ float fma_gu(const PDArgs& a, const GURegs<GU_IT>& r, const float* xs,
-                                        int lane) {
-  const int L = a.H / 8;
-  float ag = 0.f, au = 0.f;
-#pragma unroll
-  for (int it = 0; it < GU_IT; ++it) {
-    const int u = it * kWave + lane;
-    const bool ok = u < L;
-    const int uc = ok ? u : L - 1;
-    const float4 x0 = reinterpret_cast<const float4*>(xs)[uc * 2];
-    const float4 x1 = reinterpret_cast<const float4*>(xs)[uc * 2 + 1];
-    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-    const u32x4 z{0u, 0u, 0u, 0u};
-    float wg[8], wu[8];
-    const u32x4 rg = ok ? r.g[it] : z, ru = ok ? r.u[it] : z;
-    wg[0] = bf16_lo(rg.x); wg[1] = bf16_hi(rg.x); wg[2] = bf16_lo(rg.y); wg[3] = bf16_hi(rg.y);
-    wg[4] = bf16_lo(rg.z); wg[5] = bf16_hi(rg.z); wg[6] = bf16_lo(rg.w); wg[7] = bf16_hi(rg.w);
-    wu[0] = bf16_lo(ru.x); wu[1] = bf16_hi(ru.x); wu[2] = bf16_lo(ru.y); wu[3] = bf16_hi(ru.y);
-    wu[4] = bf16_lo(ru.z); wu[5] = bf16_hi(ru.z); wu[6] = bf16_lo(ru.w); wu[7] = bf16_hi(ru.w);
-#pragma unroll
-    for (int v = 0; v < 8; ++v) ag = fmaf(wg[v], xv[v], ag);
-#pragma unroll
-    for (int v = 0; v < 8; ++v) au = fmaf(wu[v], xv[v], au);
-  }
-  const float g = wave_sum(ag);
-  const float u = wave_sum(au);
+// silu(G x) * (U x) with x from LDS.
+template <typename WT, int GU_IT>
+__device__ __forceinline__ float fma_gu(const PDArgs& a, const GURegs<WT, GU_IT>& r,
+                                        const float* xs, int lane) {
+  const Units<WT, GU_IT>* const rows[2] = {&r.g, &r.u};
+  float acc[2];
+  dot_units<WT, GU_IT, 2>(rows, (int)(qrow_bytes<WT>(a.H) >> 4), xs, 0, lane, acc);
+  const float g = wave_sum(acc[0]);
+  const float u = wave_sum(acc[1]);
   return silu_f(g) * u;
 }
-
-template <int DN_IT>
-struct DnRegs {
-  u32x4 w[DN_IT];
-};
 
 // Down row pointer, length and A offset of dot d for layer descriptor ld.
 struct DnRow {
   const char* w;  // first element of the row segment
+  const char* sc; // Q4_0: its first scale
   int len;        // elements
   int aoff;       // offset of its input in the concatenated A
   int routed;     // 1: the top-1 expert (gate g_e1)
 };
 
+template <typename WT>
 __device__ __forceinline__ DnRow dn_row(const PDArgs& a, const PDLayer& ld, int h, int src,
                                         const char* e1blk) {
-  DnRow r{nullptr, 0, 0, 0};
+  DnRow r{nullptr, nullptr, 0, 0, 0};
+  // Columns [c0, c0 + len) of row h of the D matrix of a block [G|U|D].
+  const auto row = [&](const char* blk, int inter, int c0) {
+    const char* D = blk + 2 * mat_bytes<WT>(inter, a.H);
+    const size_t rb = qrow_bytes<WT>(inter);
+    r.w = D + (size_t)h * rb + qrow_bytes<WT>(c0);
+    if constexpr (kQ4<WT>) r.sc = D + (size_t)a.H * rb + (size_t)h * (rb >> 3) + (c0 >> 4);
+  };
   if (src < a.n_chunks) {
-    const char* D = ld.shared + (size_t)4 * a.Is * a.H;  // after G and U (bf16)
-    r.w = D + ((size_t)h * a.Is + (size_t)src * a.chunk) * 2;
+    row(ld.shared, a.Is, src * a.chunk);
     r.len = a.chunk;
     r.aoff = src * a.chunk;
   } else if (a.has_draft && src == a.n_chunks) {
-    const char* D = ld.draft + (size_t)4 * a.Id * a.H;
-    r.w = D + (size_t)h * a.Id * 2;
+    row(ld.draft, a.Id, 0);
     r.len = a.Id;
     r.aoff = a.Is;
   } else {
-    r.w = e1blk == nullptr ? nullptr : e1blk + (size_t)4 * a.I * a.H + (size_t)h * a.I * 2;
+    if (e1blk != nullptr) row(e1blk, a.I, 0);
     r.len = a.I;
     r.aoff = a.Is + a.Id;
     r.routed = 1;
@@ -322,43 +381,23 @@ __device__ __forceinline__ DnRow dn_row(const PDArgs& a, const PDLayer& ld, int 
   return r;
 }
 
-template <int DN_IT>
-__device__ __forceinline__ void issue_dn(const DnRow& r, DnRegs<DN_IT>& w, int lane) {
-  const int L = r.len / 8;
-  const char* base = uni(r.w);
-#pragma unroll
-  for (int it = 0; it < DN_IT; ++it) {
-    const uint32_t u = (uint32_t)min(it * kWave + lane, L - 1);
-    w.w[it] = load_stream16(base + u * 16u);
-  }
+template <typename WT, int DN_IT>
+__device__ __forceinline__ void issue_dn(const DnRow& r, Units<WT, DN_IT>& w, int lane) {
+  issue_units<WT, DN_IT>(uni(r.w), kQ4<WT> ? uni(r.sc) : nullptr, r.len / WTr<WT>::EPU, w, lane);
 }
 
-// The dot product of a down row with its A segment (LDS), in the lane order
-// and FMA order of the grouped down kernel; every lane gets the sum.
-template <int DN_IT>
-__device__ __forceinline__ float fma_dn(const DnRow& r, const DnRegs<DN_IT>& w, const float* as,
+// The dot product of a down row with its A segment (LDS); every lane gets the sum.
+template <typename WT, int DN_IT>
+__device__ __forceinline__ float fma_dn(const DnRow& r, const Units<WT, DN_IT>& w, const float* as,
                                         int lane) {
-  const int L = r.len / 8;
-  float acc = 0.f;
-#pragma unroll
-  for (int it = 0; it < DN_IT; ++it) {
-    const int u = it * kWave + lane;
-    const bool ok = u < L;
-    const int uc = ok ? u : L - 1;
-    const float4 x0 = reinterpret_cast<const float4*>(as + r.aoff)[uc * 2];
-    const float4 x1 = reinterpret_cast<const float4*>(as + r.aoff)[uc * 2 + 1];
-    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-    const u32x4 rr = ok ? w.w[it] : u32x4{0u, 0u, 0u, 0u};
-    float wv[8];
-    wv[0] = bf16_lo(rr.x); wv[1] = bf16_hi(rr.x); wv[2] = bf16_lo(rr.y); wv[3] = bf16_hi(rr.y);
-    wv[4] = bf16_lo(rr.z); wv[5] = bf16_hi(rr.z); wv[6] = bf16_lo(rr.w); wv[7] = bf16_hi(rr.w);
-#pragma unroll
-    for (int v = 0; v < 8; ++v) acc = fmaf(wv[v], xv[v], acc);
-  }
-  return wave_sum(acc);
+  constexpr int EPU = WTr<WT>::EPU;
+  const Units<WT, DN_IT>* const rows[1] = {&w};
+  float acc[1];
+  dot_units<WT, DN_IT, 1>(rows, r.len / EPU, as, r.aoff / EPU, lane, acc);
+  return wave_sum(acc[0]);
 }
 
-template <int GU_IT, int DN_IT>
+template <typename WT, int GU_IT, int DN_IT>
 __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
   extern __shared__ __align__(16) float s_a[];  // the layer's gate/up outputs, staged
   __shared__ __align__(16) float s_x[kPDMaxH];  // normed input of the current layer
@@ -406,12 +445,12 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     dd[q].src = uni(s);
   }
 
-  GURegs<GU_IT> gw[kGUPre];
-  DnRegs<DN_IT> dw[kDnSlots];
+  GURegs<WT, GU_IT> gw[kGUPre];
+  Units<WT, DN_IT> dw[kDnSlots];
 
-  const auto issue_gu_slot = [&](int t, const PDLayer& ld, GURegs<GU_IT>& r) {
-    if (gr[t].src == 0) issue_gu<GU_IT>(a, ld.shared, a.Is, gr[t].row, r, lane);
-    if (gr[t].src == 1) issue_gu<GU_IT>(a, ld.draft, a.Id, gr[t].row, r, lane);
+  const auto issue_gu_slot = [&](int t, const PDLayer& ld, GURegs<WT, GU_IT>& r) {
+    if (gr[t].src == 0) issue_gu<WT, GU_IT>(a, ld.shared, a.Is, gr[t].row, r, lane);
+    if (gr[t].src == 1) issue_gu<WT, GU_IT>(a, ld.draft, a.Id, gr[t].row, r, lane);
   };
   // The wave's first kGUPre dense gate/up row pairs of a layer are issued
   // ahead of the layer's input.
@@ -437,7 +476,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     const int e = b * kPW + wave;
     if (e < a.N) {
       const float4* xs4 = reinterpret_cast<const float4*>(s_x);
-      const float z = router_dot_pre(wr, H4, lane, [&](int h) { return xs4[h]; });
+      const float z = router_dot_pre(wr, H4, lane, [&](int h) { return xs4[act_at<WT>(4 * h) >> 2]; });
       if (lane == 0)
         st_flag(a.z_tag + e, ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(z));
     }
@@ -455,7 +494,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
   issue_dense(0);
   if (logit_block && a.z_in == nullptr) issue_router(0);
   for (int i = threadIdx.x; i < H; i += kPB) {
-    s_x[i] = a.x_in[i];
+    s_x[act_at<WT>(i)] = a.x_in[i];
     s_h[i] = a.h_in != nullptr ? a.h_in[i] : 0.f;
   }
   __syncthreads();
@@ -532,11 +571,11 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
           if (lane == 0) st_coherent(a.a_buf + gr[t].p, 0.f);
           continue;
         }
-        issue_gu<GU_IT>(a, blk, a.I, gr[t].row, gw[t % kGUPre], lane);
+        issue_gu<WT, GU_IT>(a, blk, a.I, gr[t].row, gw[t % kGUPre], lane);
       } else if (t >= kGUPre) {
         issue_gu_slot(t, ld, gw[t % kGUPre]);
       }
-      const float v = fma_gu<GU_IT>(a, gw[t % kGUPre], s_x, lane);
+      const float v = fma_gu<WT, GU_IT>(a, gw[t % kGUPre], s_x, lane);
       if (lane == 0) st_coherent(a.a_buf + gr[t].p, v);
     }
 
@@ -546,7 +585,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
       for (int q = 0; q < kDnSlots; ++q) {
         if (dd[q].i < 0 || dd[q].src == nsrc - 1) continue;
-        issue_dn<DN_IT>(dn_row(a, ld, b + G * dd[q].i, dd[q].src, nullptr), dw[q], lane);
+        issue_dn<WT, DN_IT>(dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, nullptr), dw[q], lane);
       }
     }
     bool need_e1 = false;
@@ -557,7 +596,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
       for (int q = 0; q < kDnSlots; ++q) {
         if (dd[q].i < 0 || dd[q].src != nsrc - 1) continue;
-        issue_dn<DN_IT>(dn_row(a, ld, b + G * dd[q].i, dd[q].src, e1blk), dw[q], lane);
+        issue_dn<WT, DN_IT>(dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, e1blk), dw[q], lane);
       }
     }
     grid_wait(a, 2 * l + 1, &s_abort);
@@ -566,8 +605,8 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     {
       const uint64_t* src = reinterpret_cast<const uint64_t*>(a.a_buf);
       uint64_t* dst = reinterpret_cast<uint64_t*>(s_a);
-      for (int i = threadIdx.x; i < P / 2; i += kPB) dst[i] = ld_coherent64(src + i);
-      if ((P & 1) && threadIdx.x == 0) s_a[P - 1] = ld_coherent(a.a_buf + P - 1);
+      for (int i = threadIdx.x; i < P / 2; i += kPB)  // (P is a multiple of 8)
+        dst[act_at<WT>(2 * i) >> 1] = ld_coherent64(src + i);
     }
     if (wave == kSelWave && lane == 0 && e1blk == nullptr) s_missing = 1;
     __syncthreads();
@@ -575,10 +614,10 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
     for (int q = 0; q < kDnSlots; ++q) {
       if (dd[q].i < 0) continue;
-      const DnRow r = dn_row(a, ld, b + G * dd[q].i, dd[q].src, e1blk);
+      const DnRow r = dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, e1blk);
       float v = 0.f;
       if (r.w != nullptr) {
-        const float dot = fma_dn<DN_IT>(r, dw[q], s_a, lane);
+        const float dot = fma_dn<WT, DN_IT>(r, dw[q], s_a, lane);
         const float gm = r.routed ? g1 : (dd[q].src < a.n_chunks ? 1.0f : ld.gamma);
         v = gm * dot;
       }
@@ -680,7 +719,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
         const int h = threadIdx.x + kPB * j + kCombVT * i;
         if (h < H) {
           s_h[h] = v[j][i];
-          if (want_norm) s_x[h] = v[j][i] * r;
+          if (want_norm) s_x[act_at<WT>(h)] = v[j][i] * r;
           if (!more && b == 0) {
             a.y_out[h] = v[j][i];
             if (a.normed_out != nullptr) a.normed_out[h] = v[j][i] * r;
@@ -695,19 +734,23 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     }
   }
 
+  // Every block wrote its last rows, which this one has read: whatever is
+  // still to run waits for no block that has not started.
+  if (b == 0 && threadIdx.x == 0)
+    __hip_atomic_store(a.done, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (b == 0 && threadIdx.x == 0 && s_missing)
     __hip_atomic_fetch_or(a.status, kStatusNotResident, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int GU_IT, int DN_IT>
+template <typename WT, int GU_IT, int DN_IT>
 hipError_t launch_typed(const PDArgs& a, hipStream_t s) {
-  const void* fn = reinterpret_cast<const void*>(draft_persistent_kernel<GU_IT, DN_IT>);
+  const void* fn = reinterpret_cast<const void*>(draft_persistent_kernel<WT, GU_IT, DN_IT>);
   // At least half of a CU's LDS, so that two blocks never share a CU.
   const size_t lds = a.lds_bytes;
   hipError_t e = allow_lds(fn, lds);
   if (e != hipSuccess) return note_hip(e);
   int occ = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, draft_persistent_kernel<GU_IT, DN_IT>, kPB,
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, draft_persistent_kernel<WT, GU_IT, DN_IT>, kPB,
                                                    lds);
   if (e != hipSuccess) return note_hip(e);
   if (occ < 1 || a.grid > occ * dev_info().num_cus) return note_hip(hipErrorCooperativeLaunchTooLarge);
@@ -733,10 +776,13 @@ hipError_t launch_typed(const PDArgs& a, hipStream_t s) {
 }  // namespace
 
 bool draft_persistent_fits(const PDShape& s, int grid, int* gu_it, int* dn_it) {
-  if (grid < 1 || grid > kPDMaxGrid || s.H < 512 || s.H > kPDMaxH || s.H % 512 != 0) return false;
+  // Columns per 16-byte unit: every row and chunk is a whole number of units.
+  const int al = s.wdtype == DE_Q4_0 ? WTr<q4_t>::EPU : WTr<uint16_t>::EPU;
+  if (s.wdtype != DE_BF16 && s.wdtype != DE_Q4_0) return false;
+  if (grid < 1 || grid > kPDMaxGrid || s.H < 512 || s.H > kPDMaxH || s.H % al != 0) return false;
   if (s.N < 1 || s.N > 256 || s.k < 1 || s.k > 32 || s.k > s.N) return false;
-  if (s.I < 8 || s.I % 8 || s.Is < 0 || s.Is % 8 || s.Id < 0 || s.Id % 8) return false;
-  if (s.n_chunks < 0 || s.n_chunks > 3 || (s.n_chunks > 0 && (s.chunk % 8 || s.chunk * s.n_chunks != s.Is)))
+  if (s.I < al || s.I % al || s.Is < 0 || s.Is % al || s.Id < 0 || s.Id % al) return false;
+  if (s.n_chunks < 0 || s.n_chunks > 3 || (s.n_chunks > 0 && (s.chunk % al || s.chunk * s.n_chunks != s.Is)))
     return false;
   if (s.n_chunks == 0 && s.Is != 0) return false;
   const int P = s.Is + s.Id + s.I;
@@ -750,9 +796,9 @@ bool draft_persistent_fits(const PDShape& s, int grid, int* gu_it, int* dn_it) {
   int len = s.I;
   if (s.Id > len) len = s.Id;
   if (s.chunk > len) len = s.chunk;
-  const int dn = (len / 8 + kWave - 1) / kWave;
-  const int gu = s.H / 512;
-  if (dn < 1 || dn > 4 || gu < 1 || gu > 4) return false;
+  const int dn = cdiv(len / al, kWave), gu = cdiv(s.H / al, kWave);
+  const int most = s.wdtype == DE_Q4_0 ? 1 : 4;
+  if (dn < 1 || dn > most || gu < 1 || gu > most) return false;
   if (gu_it) *gu_it = gu;
   if (dn_it) *dn_it = dn;
   return true;
@@ -764,16 +810,17 @@ size_t draft_persistent_lds(const PDShape& s) {
 }
 
 hipError_t launch_draft_persistent(const PDArgs& a, hipStream_t s) {
-  PDShape sh{a.H, a.N, a.k, a.I, a.Is, a.Id, a.n_chunks, a.chunk};
+  PDShape sh{a.wdtype, a.H, a.N, a.k, a.I, a.Is, a.Id, a.n_chunks, a.chunk};
   int gu = 0, dn = 0;
   if (!draft_persistent_fits(sh, a.grid, &gu, &dn) || a.L < 1 || a.L > kPDMaxLayers)
     return note_hip(hipErrorInvalidValue);
   // Extra iterations past a row's end add exact zeros, so a larger
   // instantiation gives the same bits.
-  if (gu > 2 && dn <= 3) return launch_typed<4, 3>(a, s);
-  if (gu > 2) return launch_typed<4, 4>(a, s);
-  if (gu == 2) return launch_typed<2, 4>(a, s);
-  return launch_typed<1, 4>(a, s);
+  if (a.wdtype == DE_Q4_0) return launch_typed<q4_t, 1, 1>(a, s);
+  if (gu > 2 && dn <= 3) return launch_typed<uint16_t, 4, 3>(a, s);
+  if (gu > 2) return launch_typed<uint16_t, 4, 4>(a, s);
+  if (gu == 2) return launch_typed<uint16_t, 2, 4>(a, s);
+  return launch_typed<uint16_t, 1, 4>(a, s);
 }
 
 }  // namespace de

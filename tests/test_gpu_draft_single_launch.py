@@ -1,0 +1,127 @@
+"""One drafted position in the single launch, over the shapes it accepts: bf16
+and Q4_0 expert weights, hidden sizes that do not fill the lanes, with and
+without shared and draft experts.  The separate launches (DE_PD_SINGLE=0) do
+the same fp32 operations in the same order, so every output is identical bit
+for bit.  Launches on two streams at once, and under stream capture."""
+import pytest
+import torch
+
+import paper_2607_24434_amd as de
+
+from gpu_support import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+# dtype, hidden, experts, top_k, inter, shared, draft, score, norm_topk
+SHAPES = [
+    (de.DE_Q4_0, 2048, 64, 6, 1408, 2816, 1408, de.DE_SOFTMAX, 0),
+    (de.DE_Q4_0, 512, 8, 2, 32, 0, 32, de.DE_SIGMOID, 1),
+    (de.DE_Q4_0, 1056, 33, 4, 160, 320, 0, de.DE_SOFTMAX, 1),
+    (de.DE_Q4_0, 2016, 128, 8, 704, 1408, 704, de.DE_SIGMOID, 0),
+    (de.DE_BF16, 520, 16, 2, 128, 256, 128, de.DE_SOFTMAX, 0),
+    (de.DE_BF16, 1304, 60, 4, 136, 136, 0, de.DE_SIGMOID, 1),
+    (de.DE_BF16, 2040, 64, 6, 1408, 2816, 1408, de.DE_SOFTMAX, 1),
+]
+
+
+class Layer:
+    def __init__(self, shape, seed):
+        require_gpu()
+        dt, H, N, k, I, Is, Id, score, norm = shape
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        self.H, self.k = H, k
+        self.desc = de.make_desc(H, N, k, I, Is, Id, score, norm, 1.0, dt)
+
+        def block(n, inter):
+            if inter == 0:
+                return None
+            m = inter * H
+            if dt == de.DE_BF16:
+                return torch.randn(n, 3 * m, generator=g, device="cuda").mul_(0.02).bfloat16()
+            w = torch.randint(0, 256, (n, 3, m * 9 // 16), generator=g, device="cuda",
+                              dtype=torch.uint8)
+            d = torch.randn(n, 3, m // 32, generator=g, device="cuda").mul_(0.005).half()
+            w[:, :, m // 2:] = d.view(torch.uint8)
+            return w.view(n, -1)
+
+        self.router = torch.randn(N, H, generator=g, device="cuda") * 0.1
+        self.bias = torch.randn(N, generator=g, device="cuda") * 0.1
+        self.routed, self.shared, self.draft = block(N, I), block(1, Is), block(1, Id)
+        self.table = de.make_table(self.routed, de.expert_bytes(dt, I, H), None, N)
+        self.x = torch.randn(1, H, generator=g, device="cuda")
+        self.residual = torch.randn(1, H, generator=g, device="cuda")
+        self.ws = de.workspace(self.desc, 1)
+
+    def outputs(self):
+        f = dict(device="cuda")
+        return [torch.zeros(1, self.H, **f), torch.zeros(1, self.H, **f),
+                torch.zeros(1, self.k, dtype=torch.int32, **f), torch.zeros(1, self.k, **f)]
+
+    def run(self, out, stream=None):
+        y, normed, idx, gate = out
+        de.de_draft_layer(self.desc, 1, self.x, self.router, self.bias, self.table, self.shared,
+                          self.draft, 0.5, y, idx, gate, self.ws,
+                          epi=de.make_epilogue(self.residual, normed, 1e-6), stream=stream)
+
+
+def separate(layer, monkeypatch):
+    monkeypatch.setenv("DE_PD_SINGLE", "0")
+    want = layer.outputs()
+    layer.run(want)
+    torch.cuda.synchronize()
+    monkeypatch.setenv("DE_PD_SINGLE", "1")
+    return want
+
+
+def same(got, want):
+    return all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s[:7])))
+def test_single_launch_equals_separate_launches(shape, monkeypatch):
+    layer = Layer(shape, 1)
+    want = separate(layer, monkeypatch)
+    assert torch.isfinite(want[0]).all()
+    for _ in range(3):  # later launches find the words of earlier ones
+        got = layer.outputs()
+        layer.run(got)
+        torch.cuda.synchronize()
+        assert de.de_layer_status(layer.ws) == 0
+        assert same(got, want)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[6]], ids=["q4", "bf16"])
+def test_two_streams(shape, monkeypatch):
+    """Calls on two streams at once: a launch never shares the chip with
+    another stream's, and the outputs are the same."""
+    layers = [Layer(shape, s) for s in (2, 3)]
+    want = [separate(l, monkeypatch) for l in layers]
+    streams = [torch.cuda.Stream() for _ in layers]
+    got = [[l.outputs() for _ in range(20)] for l in layers]
+    torch.cuda.synchronize()
+    for i in range(20):
+        for l, s, g in zip(layers, streams, got):
+            l.run(g[i], stream=s)
+    torch.cuda.synchronize()
+    for l, g, w in zip(layers, got, want):
+        assert de.de_layer_status(l.ws) == 0
+        assert all(same(o, w) for o in g)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[6]], ids=["q4", "bf16"])
+def test_captured(shape, monkeypatch):
+    """A captured call replays on changed inputs, with eager calls between."""
+    layer = Layer(shape, 4)
+    separate(layer, monkeypatch)
+    graph, out, s = torch.cuda.CUDAGraph(), layer.outputs(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        layer.run(out, stream=s)
+    for i in range(4):
+        layer.x.normal_()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = layer.outputs()
+        layer.run(want)
+        torch.cuda.synchronize()
+        assert same(out, want)
