@@ -130,7 +130,7 @@ int chunk_count(int K, int n, int align) {
 // Blocks of two positions or more whose sources' columns fit the waves'
 // registers.  V2-Lite layer, gate/up + down, us on the matrix cores against
 // the vector ALU: bf16 T = 2 54 against 57, T = 9 120 against 136, T = 64 234
-// against 802; Q4_0 T = 9 81 against 113, T = 1 31 against 26.  (One bf16
+// against 802; Q4_0 T = 9 76 against 113, T = 1 31 against 26.  (One bf16
 // position is the same within the runs' spread, and the persistent draft pass
 // computes it in the vector ALU's order.)  The plan follows from the layer's
 // shape and the block alone, so that calls over parts of a layer (an expert

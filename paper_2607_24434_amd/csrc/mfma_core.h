@@ -41,7 +41,7 @@
 // Q4_0: a fragment is a quarter of the bytes, so a tile is four fragments and
 // all four are in flight.  The codes become bf16 operands with one conversion
 // per two (the vector ALU needed one conversion and one FMA per weight and
-// position); V2-Lite layer at T = 9: gate/up 48 us (vector ALU 63), down 33
+// position); V2-Lite layer at T = 9: gate/up 44 us (vector ALU 63), down 32
 // (51), bound by the latency of a fragment's way through LDS, conversion and
 // matrix cores.
 //
@@ -261,10 +261,14 @@ struct Lanes {
   uint32_t row;       // load j: the unit's row in bits 4 j .. 4 j + 3
   int upw;            // the wave's units per row
   int last;           // last row that a fragment may read
-  uint32_t rb, srb;   // bytes per row of weights and of scales
+  uint32_t rb;        // bytes per row of weights
   uint32_t xo;        // activations: byte offset of the lane's position
   int u0, ulast;      // first unit, last unit of the row
   uint32_t ok;        // bit q: the lane's columns of step q exist
+  // Q4_0, per load: the unit's byte offset from the fragment's first row and its
+  // place in the wave's LDS rows (bytes; codes, and the scale's << 16).  Computed
+  // for every fragment they were a third of its vector instructions.
+  uint32_t lo[kQ4<WT> ? kLoads<WT, KS> : 1], so[kQ4<WT> ? kLoads<WT, KS> : 1];
 };
 
 __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
@@ -272,6 +276,31 @@ __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
 }
 __device__ __forceinline__ u32x4 ldx(const float* base, uint32_t off) {
   return *(const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off);
+}
+
+// The lane's unit of load j: its place in the wave's list, and its row.
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t unit_of(const Lanes<WT, KS>& L, int j, int lane, uint32_t& row) {
+  row = (L.row >> (4 * j)) & 15u;
+  return (uint32_t)min(j * kWave + lane, 16 * L.upw - 1);
+}
+
+// Where that unit goes in the wave's LDS rows of `pitch` units.
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t stage_unit(const Lanes<WT, KS>& L, int j, int lane, int pitch) {
+  uint32_t row;
+  const uint32_t f = unit_of(L, j, lane, row);
+  return f + row * (uint32_t)(pitch - L.upw);
+}
+
+// Its byte offset from the fragment's first row (Q4_0: its scale's is an eighth
+// of it, as the rows' bytes are).
+template <typename WT, int KS>
+__device__ __forceinline__ uint32_t load_off(const Lanes<WT, KS>& L, int j, int lane) {
+  uint32_t row;
+  const uint32_t u = unit_of(L, j, lane, row) - row * (uint32_t)L.upw + (uint32_t)L.u0;
+  row = min(row, (uint32_t)L.last);
+  return row * L.rb + u * 16u;
 }
 
 // Slice c for column slice ks of 2^lkw.  As matrix operands lane l holds row
@@ -293,7 +322,6 @@ __device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& 
   L.upw = upw;
   L.last = min(c.rows, 16) - 1;
   L.rb = c.rb;
-  L.srb = c.srb;
   L.row = 0;
   const uint32_t inv = (65536u + upw - 1) / (uint32_t)upw;  // f / upw = f inv >> 16 for f < 512
 #pragma unroll
@@ -308,31 +336,15 @@ __device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& 
   const int m = min(n, c.nt - 1);
   const int pos = c.listed ? tb.tok[c.p0 + m] : c.p0 + m;
   L.xo = (uint32_t)pos * (uint32_t)c.astride * 4u;
+  if constexpr (kQ4<WT>) {
+#pragma unroll
+    for (int j = 0; j < kLoads<WT, KS>; ++j) {
+      L.so[j] = 16u * stage_unit(L, j, lane, kRowUnits<WT, KS>) |
+                2u * stage_unit(L, j, lane, 8) << 16;
+      L.lo[j] = load_off(L, j, lane);
+    }
+  }
   return L;
-}
-
-// The lane's unit of load j: its place in the wave's list, and its row.
-template <typename WT, int KS>
-__device__ __forceinline__ uint32_t unit_of(const Lanes<WT, KS>& L, int j, int lane, uint32_t& row) {
-  row = (L.row >> (4 * j)) & 15u;
-  return (uint32_t)min(j * kWave + lane, 16 * L.upw - 1);
-}
-
-// Where that unit goes in the wave's LDS rows of `pitch` units.
-template <typename WT, int KS>
-__device__ __forceinline__ uint32_t stage_unit(const Lanes<WT, KS>& L, int j, int lane, int pitch) {
-  uint32_t row;
-  const uint32_t f = unit_of(L, j, lane, row);
-  return f + row * (uint32_t)(pitch - L.upw);
-}
-
-// Its byte offset from the fragment's first row, and (Q4_0) its scale's.
-template <typename WT, int KS>
-__device__ __forceinline__ uint32_t load_off(const Lanes<WT, KS>& L, int j, int lane, bool scale) {
-  uint32_t row;
-  const uint32_t u = unit_of(L, j, lane, row) - row * (uint32_t)L.upw + (uint32_t)L.u0;
-  row = min(row, (uint32_t)L.last);
-  return scale ? row * L.srb + u * 2u : row * L.rb + u * 16u;
 }
 
 // The lane's 8 activations of step q (fp32).
@@ -387,6 +399,19 @@ __device__ __forceinline__ void split8(u32x4 (&f)[3], bool ok) {
 template <int KS>
 constexpr int kStepGroup = KS < 4 ? KS : (KS % 4 == 0 ? 4 : 3);
 
+// c += the steps' products with the activations' hi, then mid, then lo parts.
+template <int N>
+__device__ __forceinline__ void add_products(const u32x4 (*act)[3], const u32x4 (&b)[N],
+                                             f32x4 (&c)[N]) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, act[i][p]),
+                                                     __builtin_bit_cast(bf16x8, b[i]), c[i], 0, 0,
+                                                     0);
+}
+
 // acc of the steps' three products each, summed from zero, smallest part
 // first: a chain through all steps would round every part at the full sum's
 // magnitude.
@@ -416,7 +441,7 @@ __device__ __forceinline__ void stage(u32x4 (&w)[KS], char* st, const Lanes<uint
 #pragma unroll
   for (int j = 0; j < KS; ++j) {
     reinterpret_cast<u32x4*>(st)[stage_unit(L, j, lane, kRowUnits<uint16_t, KS>)] = w[j];
-    w[j] = ldw(nw, load_off(nl, j, lane, false) & mask);
+    w[j] = ldw(nw, load_off(nl, j, lane) & mask);
   }
 }
 
@@ -446,13 +471,14 @@ __device__ __forceinline__ f32x4 fragment_sums(const u32x4 (&act)[KS][3], const 
 // The sums of the staged Q4_0 fragment.  A step is one block of 32 weights per
 // row, d (q - 8): the codes q become bf16 operands (a byte 0 .. 15 read as
 // e4m3 is q / 512, denormal or not, so one conversion with scale 512 makes two
-// of them), the products q x are summed by the matrix cores, and -8 times the
-// block's activation sum (xm) and the scale, which lane l holds for its own
-// row l % 16, are applied to the block's sums.
+// of them), the products q x are summed by the matrix cores on top of -8 times
+// the block's activation sum (xm; hi parts first, so that what follows rounds
+// at the small sum of (q - 8) x), and the scale, which lane l holds for its own
+// row l % 16, is applied to the block's sums.
 template <int KS>
 __device__ __forceinline__ f32x4 fragment_sums_q4(const u32x4 (&act)[KS][3], const f32x4 (&xm)[KS],
                                                   const char* st, int lane) {
-  constexpr int N = kStepGroup<KS>, RU = kRowUnits<q4_t, KS>;
+  constexpr int N = 2, RU = kRowUnits<q4_t, KS>;  // (more would not fit the registers)
   const uint32_t* rd = reinterpret_cast<const uint32_t*>(st) + (lane & 15) * RU * 4 + (lane >> 4);
   const u32x4 dv = reinterpret_cast<const u32x4*>(st + 16 * RU * 16)[lane & 15];
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -470,13 +496,15 @@ __device__ __forceinline__ f32x4 fragment_sums_q4(const u32x4 (&act)[KS][3], con
                    DE_CODES(hi, true)};
 #undef DE_CODES
     }
-    products<N>(act + q0, b, c);
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = xm[q0 + i];
+    add_products<N>(act + q0, b, c);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const int q = q0 + i;
       const float d = half_bits_to_float((dv[q >> 1] >> (16 * (q & 1))) & 0xffffu);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fmaf(d, c[i][j] + xm[q][j], acc[j]);
+      for (int j = 0; j < 4; ++j) acc[j] = fmaf(d, c[i][j], acc[j]);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -579,11 +607,18 @@ __device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
                                                int f, int d, uint32_t mask, int lane) {
   const char* p = frag_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
-  for (int j = 0; j < kLoads<WT, KS>; ++j) R.w[d][j] = ldw(p, load_off(L, j, lane, false) & mask);
+  for (int j = 0; j < kLoads<WT, KS>; ++j) {
+    uint32_t o;
+    if constexpr (kQ4<WT>)
+      o = L.lo[j];
+    else
+      o = load_off(L, j, lane);
+    R.w[d][j] = ldw(p, o & mask);
+  }
   if constexpr (kQ4<WT>) {
     const char* ps = scale_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
-    for (int j = 0; j < kLoads<WT, KS>; ++j) R.sc[d][j] = ldh(ps, load_off(L, j, lane, true) & mask);
+    for (int j = 0; j < kLoads<WT, KS>; ++j) R.sc[d][j] = ldh(ps, (L.lo[j] >> 3) & mask);
   }
 }
 
@@ -636,12 +671,11 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
     asm volatile("" : "+v"(lane));
     f32x4 acc;
     if constexpr (kQ4<WT>) {
-      constexpr int RU = kRowUnits<WT, KS>;
-      uint16_t* sst = reinterpret_cast<uint16_t*>(st + 16 * RU * 16);
+      char* sst = st + 16 * kRowUnits<WT, KS> * 16;
 #pragma unroll
       for (int j = 0; j < kLoads<WT, KS>; ++j) {
-        reinterpret_cast<u32x4*>(st)[stage_unit(L, j, lane, RU)] = R.w[f][j];
-        sst[stage_unit(L, j, lane, 8)] = (uint16_t)R.sc[f][j];
+        *reinterpret_cast<u32x4*>(st + (L.so[j] & 0xffffu)) = R.w[f][j];
+        *reinterpret_cast<uint16_t*>(sst + (L.so[j] >> 16)) = (uint16_t)R.sc[f][j];
       }
       issue_fragment<WT, KS, GATEUP>(R, nc, N, rpt, nr, rw, f, f, mask, lane);
       asm volatile("" ::: "memory");
