@@ -1058,7 +1058,7 @@ int accept_len_embed(int K, int V, const float* target_logits, const int32_t* dr
   if (ws == nullptr || (reinterpret_cast<uintptr_t>(ws) & 255u) != 0 ||
       ws_bytes < de_accept_workspace_bytes(K, V))
     return DE_ERR_WORKSPACE;
-  const size_t rows = (size_t)K + 1, ch = (size_t)de::accept_chunks(V);
+  const size_t rows = (size_t)K + 1;
   de::AcceptArgs a{};
   a.emb = static_cast<const uint16_t*>(emb);
   a.H = H;
@@ -1073,8 +1073,7 @@ int accept_len_embed(int K, int V, const float* target_logits, const int32_t* dr
   a.out = out;
   a.done_cnt = at<unsigned>(ws, 0);
   a.row_cnt = at<unsigned>(ws, 256);
-  a.part_v = at<float>(ws, 256 + up256(rows * 4));
-  a.part_i = at<int32_t>(ws, 256 + up256(rows * 4) + up256(rows * ch * 4));
+  a.part = at<uint64_t>(ws, 256 + up256(rows * 4));
   return hip_status(de::launch_argmax_accept(a, stream));
 }
 

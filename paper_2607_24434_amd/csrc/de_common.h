@@ -256,8 +256,7 @@ struct AcceptArgs {
   const int32_t* drafts;   // [K]
   int32_t* amax;           // [K+1]
   int32_t* out;            // [2]: n, bonus
-  float* part_v;           // [K+1, chunks] scratch
-  int32_t* part_i;
+  uint64_t* part;          // [K+1, chunks] scratch: (index, value) words
   unsigned* row_cnt;       // [K+1], zero between calls
   unsigned* done_cnt;      // [1], zero between calls
   // Optional (emb not NULL): the bonus token's bf16 embedding row [H] goes to
