@@ -168,7 +168,7 @@ bool fused_shape(const de_moe_desc& d, int T) {
 
 constexpr size_t kCtlBytes = 4096;
 constexpr size_t kStatusOff = 256;
-// The persistent draft pass's arrival flags: at an offset that does not
+// The single-launch verify layer's arrival flags: at an offset that does not
 // depend on the block length, which no other call writes (a call with
 // another block length lays its buffers out differently).
 constexpr size_t kPDFlagsOff = 1024;
@@ -178,7 +178,9 @@ static_assert(kPDFlagsOff + (de::kPDMaxGrid + 32) * 8 <= kCtlBytes, "control are
 struct Layout {
   size_t ctl, z, idx, gate, nu, uids, offs, tok, glist, ppos;
   size_t a_r, a_s, a_d, p_r, p_s, p_d;
-  size_t pd;  // persistent draft pass: gate/up outputs [Is + Id + I], row words [H], logit words [N] (8 bytes)
+  // Persistent draft pass: gate/up outputs [Is + Id + I], then 8-byte words: rows
+  // [H], logits [kPDCopies, N], flags [kPDCopies, kPDMaxGrid].
+  size_t pd;
   size_t total;
 };
 
@@ -193,15 +195,14 @@ Layout layout(const de_moe_desc& d, int T) {
   const size_t tk = (size_t)T * d.top_k;
   // Control area: the routing launch's arrival counters [T] (zero after
   // de_workspace_init and after every call), the status word at byte 256
-  // (sticky until de_layer_status reads it), the persistent draft pass's
+  // (sticky until de_layer_status reads it), the single-launch verify layer's
   // flags from byte 1024.
   L.ctl = take(kCtlBytes);
-  // The persistent draft pass's buffers (its logit and down-row words are
-  // tagged), at the same offset in every layout, so that no call of another
-  // block length writes there (a value left there by another buffer could
-  // carry a matching tag).
+  // The persistent draft pass's buffers (its words are tagged), at the same
+  // offset in every layout, so that no call of another block length writes
+  // there (a value left there by another buffer could carry a matching tag).
   L.pd = take(((size_t)d.shared_inter + d.draft_inter + d.inter) * 4 +
-              ((size_t)d.hidden + d.n_experts) * 8);
+              ((size_t)d.hidden + de::kPDCopies * (d.n_experts + de::kPDMaxGrid)) * 8);
   L.z = take((size_t)T * d.n_experts * 4);
   L.idx = take(tk * 4);
   L.gate = take(tk * 4);
@@ -651,7 +652,7 @@ int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, con
   a.d_tag = reinterpret_cast<uint64_t*>(a.a_buf + (sh.Is + sh.Id + sh.I));
   a.z_tag = a.d_tag + d.hidden;
   a.z_plain = at<float>(ws, L.z);
-  a.grid_flags = at<uint64_t>(ws, kPDFlagsOff);
+  a.grid_flags = a.z_tag + de::kPDCopies * d.n_experts;
   a.status = at<int32_t>(ws, kStatusOff);
   for (int l0 = 0; l0 < n; l0 += kPDMaxLayers) {
     const int cnt = n - l0 < kPDMaxLayers ? n - l0 : kPDMaxLayers;

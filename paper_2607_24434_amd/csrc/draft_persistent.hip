@@ -30,7 +30,7 @@
 // bf16 and Q4_0 blocks; a hidden size of 512 to 2048 whose rows are whole
 // 16-byte units (lanes past a row's end add zeros).  A Q4_0 layer is 19.5 MB
 // and bound by the chain of latencies above: six V2-Lite layer calls 190 us
-// on four launches each, 153 in one each (bf16, 415 MB: 165).
+// on four launches each, 128 in one each (bf16, 415 MB: 141).
 //
 // The arithmetic is the one of the separate launches, operation for
 // operation (lane l owns the 16-byte weight units l, l + 64, ...; fp32 FMAs in
@@ -41,9 +41,17 @@
 // Blocks exchange data through agent-scope atomic loads and stores, which
 // stay coherent across the XCDs' L2 caches without a cache-wide write-back,
 // and per-block arrival flags, logit and down-row words tagged with the
-// launch's epoch (nothing is reset between launches).  Every wait is bounded: a wait that runs out
-// records kStatusSyncTimeout in the status word, and every later wait of the
-// block returns at once, so the launch always ends.
+// launch's epoch (nothing is reset between launches).  What every block polls,
+// and how often one line is polled, decides how long a point takes: the logit
+// words and the flags are written in eight copies, each polled by one block in
+// eight; a block's down rows are consecutive, one write; only one block waits
+// for the last layer's rows; and a wave that polls asks for no weights first
+// where it can.  In-kernel clock of a V2-Lite layer call: last rows written to
+// seen 4.2 us with every block polling, 1.2 with one.  Six calls 165 -> 141 us
+// (Q4_0 153 -> 128), a token through a four-layer stack and its head 204 -> 197.
+// Every wait is bounded: a wait that runs out records kStatusSyncTimeout in the
+// status word, and every later wait of the block returns at once, so the launch
+// always ends.
 #include "de_common.h"
 #include "draft_persistent.h"
 #include "grouped_core.h"
@@ -122,20 +130,20 @@ __device__ void give_up(const PDArgs& a, int* s_abort) {
   }
 }
 
-// Waits (one whole wave) until flags[0..n) all reach `target`: lane j watches
-// flags j, j + 64, ...  False on a timeout, or at once when an earlier wait
-// of the block timed out.
-__device__ bool wait_flags(const PDArgs& a, const uint64_t* flags, int n, uint64_t target,
+// Waits (one whole wave) until flags[0..n) all carry this launch's epoch and
+// reach `point`: lane j watches flags j, j + 64, ...  False on a timeout, or at
+// once when an earlier wait of the block timed out.
+__device__ bool wait_flags(const PDArgs& a, const uint64_t* flags, int n, unsigned point,
                            int* s_abort) {
   const int lane = threadIdx.x & 63;
   for (unsigned i = 0; i < a.spin_limit; ++i) {
     if (*(volatile int*)s_abort) return false;
-    uint64_t mn = ~0ull;
+    bool ok = true;
     for (int j = lane; j < n; j += kWave) {
       const uint64_t f = ld_coherent64(flags + j);
-      mn = f < mn ? f : mn;
+      ok = ok && (uint32_t)(f >> 32) == a.epoch && (uint32_t)f >= point;
     }
-    if (__builtin_amdgcn_ballot_w64(mn < target) == 0ull) return true;
+    if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) return true;
     __builtin_amdgcn_s_sleep(2);
   }
   if (lane == 0) give_up(a, s_abort);
@@ -147,12 +155,13 @@ __device__ bool wait_flags(const PDArgs& a, const uint64_t* flags, int n, uint64
 __device__ void grid_arrive(const PDArgs& a, unsigned n) {
   drain();
   __syncthreads();
-  if (threadIdx.x == 0) st_flag(a.grid_flags + blockIdx.x, ((uint64_t)a.epoch << 32) | n);
+  if (threadIdx.x < kPDCopies)
+    st_flag(a.grid_flags + threadIdx.x * kPDMaxGrid + blockIdx.x, ((uint64_t)a.epoch << 32) | n);
 }
 // ... and wait until every block has arrived.
 __device__ void grid_wait(const PDArgs& a, unsigned n, int* s_abort) {
-  if (threadIdx.x < kWave)
-    wait_flags(a, a.grid_flags, gridDim.x, ((uint64_t)a.epoch << 32) | n, s_abort);
+  if (threadIdx.x / kWave == kSelWave)
+    wait_flags(a, a.grid_flags + (blockIdx.x % kPDCopies) * kPDMaxGrid, gridDim.x, n, s_abort);
   __syncthreads();
 }
 
@@ -169,11 +178,12 @@ __device__ __forceinline__ uint32_t layer_tag(const PDArgs& a, int l) {
 __device__ void wait_logits(const PDArgs& a, int l, float (&z)[1][4], int* s_abort) {
   const int lane = threadIdx.x & 63;
   const uint32_t tag = layer_tag(a, l);
+  const uint64_t* const words = a.z_tag + (blockIdx.x % kPDCopies) * a.N;
   uint64_t w[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int e = lane + q * kWave;
-    w[q] = e < a.N ? ld_coherent64(a.z_tag + e) : (uint64_t)tag << 32;
+    w[q] = e < a.N ? ld_coherent64(words + e) : (uint64_t)tag << 32;
   }
   for (unsigned it = 0;; ++it) {
     bool ok = true;
@@ -189,7 +199,7 @@ __device__ void wait_logits(const PDArgs& a, int l, float (&z)[1][4], int* s_abo
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int e = lane + q * kWave;
-      if ((uint32_t)(w[q] >> 32) != tag && e < a.N) w[q] = ld_coherent64(a.z_tag + e);
+      if ((uint32_t)(w[q] >> 32) != tag && e < a.N) w[q] = ld_coherent64(words + e);
     }
   }
 #pragma unroll
@@ -427,10 +437,13 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
   }
 
   // This wave's gate/up rows and down dot products (the same in every layer).
+  // The selecting wave, which starts its rows last, has the first row (of a
+  // dense source) and what the others' slots do not hold.
   GURow gr[kGUSlots];
 #pragma unroll
   for (int t = 0; t < kGUSlots; ++t) {
-    const int j = wave + kPW * t;
+    const int j = wave != kSelWave ? 1 + wave + (kPW - 1) * t
+                                   : (t == 0 ? 0 : (kPW - 1) * kGUSlots + t);
     gr[t] = gu_row(a, b + G * j);
     gr[t].src = uni(gr[t].src);
     gr[t].row = uni(gr[t].row);
@@ -441,7 +454,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
   for (int q = 0; q < kDnSlots; ++q) {
     const int qq = wave + kPW * q;
     const int i = qq / nsrc, s = qq - i * nsrc;
-    dd[q].i = uni((i < rpb && b + G * i < H) ? i : -1);
+    dd[q].i = uni((i < rpb && b * rpb + i < H) ? i : -1);
     dd[q].src = uni(s);
   }
 
@@ -453,7 +466,8 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     if (gr[t].src == 1) issue_gu<WT, GU_IT>(a, ld.draft, a.Id, gr[t].row, r, lane);
   };
   // The wave's first kGUPre dense gate/up row pairs of a layer are issued
-  // ahead of the layer's input.
+  // ahead of the layer's input.  (Not the selecting wave's: its polls for the
+  // logits would complete after them.)
   const auto issue_dense = [&](int l) {
     const PDLayer ld = layer_at(l);
 #pragma unroll
@@ -477,8 +491,8 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     if (e < a.N) {
       const float4* xs4 = reinterpret_cast<const float4*>(s_x);
       const float z = router_dot_pre(wr, H4, lane, [&](int h) { return xs4[act_at<WT>(4 * h) >> 2]; });
-      if (lane == 0)
-        st_flag(a.z_tag + e, ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(z));
+      if (lane < kPDCopies)
+        st_flag(a.z_tag + lane * a.N + e, ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(z));
     }
   };
   // The top-1 expert of layer l's weight block, or NULL when it has no valid slot.
@@ -490,15 +504,38 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     return ld.routed + (size_t)slot * ld.stride;
   };
 
-  // ---- prologue: layer 0's first gate/up pairs in flight, its input in LDS, its logits
-  issue_dense(0);
-  if (logit_block && a.z_in == nullptr) issue_router(0);
-  for (int i = threadIdx.x; i < H; i += kPB) {
-    s_x[act_at<WT>(i)] = a.x_in[i];
-    s_h[i] = a.h_in != nullptr ? a.h_in[i] : 0.f;
+  // ---- prologue: layer 0's input in LDS, its logits, its first gate/up pairs
+  // in flight.  A wave's loads complete in issue order: the input is asked for
+  // first, and a logit block's gate/up pairs after its logits.
+  {
+    constexpr int kPer = kPDMaxH / kPB;
+    float xv[kPer], hv[kPer];
+    const bool want_h = a.h_in != nullptr && (a.L > 1 || b == 0);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int h = min((int)threadIdx.x + i * kPB, H - 1);
+      xv[i] = a.x_in[h];
+      hv[i] = want_h ? a.h_in[h] : 0.f;
+    }
+    asm volatile("" ::: "memory");
+    if (logit_block && a.z_in == nullptr)
+      issue_router(0);
+    else if (wave != kSelWave)
+      issue_dense(0);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int h = threadIdx.x + i * kPB;
+      if (h < H) {
+        s_x[act_at<WT>(h)] = xv[i];
+        s_h[h] = hv[i];
+      }
+    }
   }
   __syncthreads();
-  if (a.z_in == nullptr && logit_block) logits(0);
+  if (a.z_in == nullptr && logit_block) {
+    logits(0);
+    if (wave != kSelWave) issue_dense(0);
+  }
 
   for (int l = 0; l < a.L; ++l) {
     // Opaque to the compiler: per-lane offsets and masks are recomputed in
@@ -533,6 +570,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
             if (lane + q * kWave < a.N) a.z_plain[lane + q * kWave] = z[0][q];
         }
       }
+      issue_dense(l);
       // The top-1 expert (the list's first entry) is published as soon as it
       // is known, so that its rows load while the rest of the selection runs.
       int id[1];
@@ -579,25 +617,14 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
       if (lane == 0) st_coherent(a.a_buf + gr[t].p, v);
     }
 
-    // ---- S2: arrive, put the shared / draft and top-1 down rows in flight, wait
+    // ---- S2: arrive, put the down rows in flight, wait
     grid_arrive(a, 2 * l + 1);
-    {
-#pragma unroll
-      for (int q = 0; q < kDnSlots; ++q) {
-        if (dd[q].i < 0 || dd[q].src == nsrc - 1) continue;
-        issue_dn<WT, DN_IT>(dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, nullptr), dw[q], lane);
-      }
-    }
-    bool need_e1 = false;
-#pragma unroll
-    for (int q = 0; q < kDnSlots; ++q) need_e1 |= dd[q].i >= 0 && dd[q].src == nsrc - 1;
     const char* e1blk = e1_block(ld);  // selected: every wave passed the block barrier
-    if (need_e1 && e1blk != nullptr) {
 #pragma unroll
-      for (int q = 0; q < kDnSlots; ++q) {
-        if (dd[q].i < 0 || dd[q].src != nsrc - 1) continue;
-        issue_dn<WT, DN_IT>(dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, e1blk), dw[q], lane);
-      }
+    for (int q = 0; q < kDnSlots; ++q) {
+      if (dd[q].i < 0) continue;
+      const DnRow r = dn_row<WT>(a, ld, b * rpb + dd[q].i, dd[q].src, e1blk);
+      if (r.w != nullptr) issue_dn<WT, DN_IT>(r, dw[q], lane);
     }
     grid_wait(a, 2 * l + 1, &s_abort);
 
@@ -614,7 +641,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
     for (int q = 0; q < kDnSlots; ++q) {
       if (dd[q].i < 0) continue;
-      const DnRow r = dn_row<WT>(a, ld, b + G * dd[q].i, dd[q].src, e1blk);
+      const DnRow r = dn_row<WT>(a, ld, b * rpb + dd[q].i, dd[q].src, e1blk);
       float v = 0.f;
       if (r.w != nullptr) {
         const float dot = fma_dn<WT, DN_IT>(r, dw[q], s_a, lane);
@@ -625,10 +652,11 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     }
     __syncthreads();
     // Per row: the dense partials in source order, then the routed one.
-    if (threadIdx.x < rpb && b + G * (int)threadIdx.x < H) {
+    // (A block's rows are consecutive: its words are one write.)
+    if (threadIdx.x < rpb && b * rpb + (int)threadIdx.x < H) {
       float x = 0.f;
       for (int s = 0; s < nsrc; ++s) x += s_part[threadIdx.x * nsrc + s];
-      st_flag(a.d_tag + b + G * threadIdx.x,
+      st_flag(a.d_tag + b * rpb + threadIdx.x,
               ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(x));
     }
 
@@ -639,9 +667,13 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     // writes after it staged this layer's A.
     if (more) {
       if (logit_block) issue_router(l + 1);
-      // A logit block's gate/up pair goes out after its logits (below): its
-      // logit words then do not queue behind it.
-      if (!logit_block) issue_dense(l + 1);
+      // A logit block's gate/up pairs go out after its logits (below): its
+      // logit words then do not queue behind them.
+      if (!logit_block && wave != kSelWave) issue_dense(l + 1);
+    } else if (b != 0) {
+      // The last layer's rows are one block's to combine: 256 blocks polling
+      // for them kept it waiting.
+      break;
     }
 
     // ---- combine: y = residual + the row sums; RMSNorm(y) (the combine
@@ -720,7 +752,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
         if (h < H) {
           s_h[h] = v[j][i];
           if (want_norm) s_x[act_at<WT>(h)] = v[j][i] * r;
-          if (!more && b == 0) {
+          if (!more) {
             a.y_out[h] = v[j][i];
             if (a.normed_out != nullptr) a.normed_out[h] = v[j][i] * r;
           }
@@ -730,12 +762,12 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     __syncthreads();
     if (more && logit_block) {
       logits(l + 1);
-      issue_dense(l + 1);
+      if (wave != kSelWave) issue_dense(l + 1);
     }
   }
 
   // Every block wrote its last rows, which this one has read: whatever is
-  // still to run waits for no block that has not started.
+  // still to run waits for nothing.
   if (b == 0 && threadIdx.x == 0)
     __hip_atomic_store(a.done, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (b == 0 && threadIdx.x == 0 && s_missing)
