@@ -41,7 +41,7 @@
 // Q4_0: a fragment is a quarter of the bytes, so a tile is four fragments and
 // all four are in flight.  The codes become bf16 operands with one conversion
 // per two (the vector ALU needed one conversion and one FMA per weight and
-// position); V2-Lite layer at T = 9: gate/up 44 us (vector ALU 63), down 32
+// position); V2-Lite layer at T = 9: gate/up 43 us (vector ALU 63), down 31
 // (51), bound by the latency of a fragment's way through LDS, conversion and
 // matrix cores.
 //
@@ -74,11 +74,19 @@ constexpr int kRedFloats = 2 * kRedBuf<WT>;   // double buffered: one barrier pe
 // 16-byte units of a row per step of 32 columns (Q4_0: one unit is one block).
 template <typename WT>
 constexpr int kStepUnits = kQ4<WT> ? 1 : 4;
-// Load instructions of a fragment of KS steps.
+constexpr int pow2_ceil(int v) {
+  int p = 1;
+  while (p < v) p *= 2;
+  return p;
+}
+// Lanes that load a row's units (a power of two), and the rows and number of a
+// fragment's load instructions.
 template <typename WT, int KS>
-constexpr int kLoads = (16 * KS * kStepUnits<WT> + kWave - 1) / kWave;
-template <int KS>
-constexpr int kQ4Loads = kLoads<q4_t, KS>;
+constexpr int kRowLanes = pow2_ceil(KS * kStepUnits<WT>);
+template <typename WT, int KS>
+constexpr int kLoadRows = kWave / kRowLanes<WT, KS> < 16 ? kWave / kRowLanes<WT, KS> : 16;
+template <typename WT, int KS>
+constexpr int kLoads = 16 / kLoadRows<WT, KS>;
 // LDS of a wave's staged fragment: 16 rows of units with one unit of padding
 // per row (no bank conflicts in the fragment reads), then (Q4_0) 16 rows of 8
 // scales.
@@ -253,22 +261,21 @@ struct Tiles {
 };
 
 // A wave's share of a slice.  The wave's columns are units u0 .. u0 + upw of
-// 16 bytes in every row; its fragment (16 rows of them) is loaded as one list
-// of units in row order, 64 per load, so that a load reads whole runs of a
-// row (512 bytes of two rows for 2048 columns over 8 waves).
+// 16 bytes in every row; a load instruction reads them of kLoadRows consecutive
+// rows of its fragment (whole runs: 512 bytes of two rows for 2048 columns over
+// 8 waves), kRowLanes lanes a row.  So the loads' offsets, in memory and in LDS,
+// differ by one constant and take two vector instructions; packed as one list of
+// units (no idle lanes where the columns are no power of two) they took two
+// products and a dozen (verify layers 1 to 3% slower).
 template <typename WT, int KS>
 struct Lanes {
-  uint32_t row;       // load j: the unit's row in bits 4 j .. 4 j + 3
-  int upw;            // the wave's units per row
-  int last;           // last row that a fragment may read
+  uint32_t lo, lim;   // the lane's unit of load 0, and of the last row (byte offsets)
+  uint32_t so;        // the unit of load 0 in the wave's LDS rows (bytes)
+  uint32_t ss;        // Q4_0: its scale there
   uint32_t rb;        // bytes per row of weights
   uint32_t xo;        // activations: byte offset of the lane's position
   int u0, ulast;      // first unit, last unit of the row
   uint32_t ok;        // bit q: the lane's columns of step q exist
-  // Q4_0, per load: the unit's byte offset from the fragment's first row and its
-  // place in the wave's LDS rows (bytes; codes, and the scale's << 16).  Computed
-  // for every fragment they were a third of its vector instructions.
-  uint32_t lo[kQ4<WT> ? kLoads<WT, KS> : 1], so[kQ4<WT> ? kLoads<WT, KS> : 1];
 };
 
 __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
@@ -278,29 +285,12 @@ __device__ __forceinline__ u32x4 ldx(const float* base, uint32_t off) {
   return *(const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off);
 }
 
-// The lane's unit of load j: its place in the wave's list, and its row.
+// The lane's byte offset of load j from the fragment's first row (rows past the
+// source's last one re-read that; with mask 0 every lane reads the first word).
+// Q4_0: the scale's offset is an eighth of it, as the rows' bytes are.
 template <typename WT, int KS>
-__device__ __forceinline__ uint32_t unit_of(const Lanes<WT, KS>& L, int j, int lane, uint32_t& row) {
-  row = (L.row >> (4 * j)) & 15u;
-  return (uint32_t)min(j * kWave + lane, 16 * L.upw - 1);
-}
-
-// Where that unit goes in the wave's LDS rows of `pitch` units.
-template <typename WT, int KS>
-__device__ __forceinline__ uint32_t stage_unit(const Lanes<WT, KS>& L, int j, int lane, int pitch) {
-  uint32_t row;
-  const uint32_t f = unit_of(L, j, lane, row);
-  return f + row * (uint32_t)(pitch - L.upw);
-}
-
-// Its byte offset from the fragment's first row (Q4_0: its scale's is an eighth
-// of it, as the rows' bytes are).
-template <typename WT, int KS>
-__device__ __forceinline__ uint32_t load_off(const Lanes<WT, KS>& L, int j, int lane) {
-  uint32_t row;
-  const uint32_t u = unit_of(L, j, lane, row) - row * (uint32_t)L.upw + (uint32_t)L.u0;
-  row = min(row, (uint32_t)L.last);
-  return row * L.rb + u * 16u;
+__device__ __forceinline__ uint32_t load_off(const Lanes<WT, KS>& L, int j, uint32_t mask) {
+  return min(L.lo + (uint32_t)(j * kLoadRows<WT, KS>) * L.rb, L.lim & mask);
 }
 
 // Slice c for column slice ks of 2^lkw.  As matrix operands lane l holds row
@@ -319,16 +309,13 @@ __device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& 
   L.ulast = U - 1;
   L.u0 = min(s0 * SU, L.ulast);
   const int upw = max(min(s1 * SU, U) - L.u0, 1);
-  L.upw = upw;
-  L.last = min(c.rows, 16) - 1;
+  const int row = min(lane / kRowLanes<WT, KS>, kLoadRows<WT, KS> - 1);
+  const int u = min(lane % kRowLanes<WT, KS>, upw - 1);  // (a lane without a unit: the last one)
   L.rb = c.rb;
-  L.row = 0;
-  const uint32_t inv = (65536u + upw - 1) / (uint32_t)upw;  // f / upw = f inv >> 16 for f < 512
-#pragma unroll
-  for (int j = 0; j < kLoads<WT, KS>; ++j) {
-    const uint32_t f = (uint32_t)min(j * kWave + lane, 16 * upw - 1);
-    L.row |= ((f * inv) >> 16) << (4 * j);
-  }
+  L.lo = (uint32_t)row * c.rb + (uint32_t)(L.u0 + u) * 16u;
+  L.lim = (uint32_t)(min(c.rows, 16) - 1) * c.rb + (uint32_t)(L.u0 + u) * 16u;
+  L.so = (uint32_t)(row * kRowUnits<WT, KS> + u) * 16u;
+  L.ss = (uint32_t)(row * 8 + u) * 2u;
   L.ok = 0;
 #pragma unroll
   for (int q = 0; q < KS; ++q)
@@ -336,14 +323,6 @@ __device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& 
   const int m = min(n, c.nt - 1);
   const int pos = c.listed ? tb.tok[c.p0 + m] : c.p0 + m;
   L.xo = (uint32_t)pos * (uint32_t)c.astride * 4u;
-  if constexpr (kQ4<WT>) {
-#pragma unroll
-    for (int j = 0; j < kLoads<WT, KS>; ++j) {
-      L.so[j] = 16u * stage_unit(L, j, lane, kRowUnits<WT, KS>) |
-                2u * stage_unit(L, j, lane, 8) << 16;
-      L.lo[j] = load_off(L, j, lane);
-    }
-  }
   return L;
 }
 
@@ -434,14 +413,14 @@ __device__ __forceinline__ void products(const u32x4 (*act)[3], const u32x4 (&b)
 // fragment (first row nw, lane offsets of nl; with mask 0 every lane re-reads
 // nw).  The wave's LDS accesses execute in order, so only the compiler has to
 // be kept from moving them.
-template <int KS>
-__device__ __forceinline__ void stage(u32x4 (&w)[KS], char* st, const Lanes<uint16_t, KS>& L,
-                                      const char* nw, const Lanes<uint16_t, KS>& nl, uint32_t mask,
-                                      int lane) {
+template <typename WT, int KS>
+__device__ __forceinline__ void stage(u32x4* w, char* st,
+                                      const Lanes<WT, KS>& L, const char* nw,
+                                      const Lanes<WT, KS>& nl, uint32_t mask) {
 #pragma unroll
-  for (int j = 0; j < KS; ++j) {
-    reinterpret_cast<u32x4*>(st)[stage_unit(L, j, lane, kRowUnits<uint16_t, KS>)] = w[j];
-    w[j] = ldw(nw, load_off(nl, j, lane) & mask);
+  for (int j = 0; j < kLoads<WT, KS>; ++j) {
+    *reinterpret_cast<u32x4*>(st + L.so + j * kLoadRows<WT, KS> * kRowUnits<WT, KS> * 16) = w[j];
+    w[j] = ldw(nw, load_off(nl, j, mask));
   }
 }
 
@@ -604,21 +583,14 @@ __device__ __forceinline__ uint32_t ldh(const char* base, uint32_t off) {
 template <typename WT, int KS, bool GATEUP>
 __device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
                                                const Lanes<WT, KS>& L, int rpt, int r, int rw,
-                                               int f, int d, uint32_t mask, int lane) {
+                                               int f, int d, uint32_t mask) {
   const char* p = frag_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
-  for (int j = 0; j < kLoads<WT, KS>; ++j) {
-    uint32_t o;
-    if constexpr (kQ4<WT>)
-      o = L.lo[j];
-    else
-      o = load_off(L, j, lane);
-    R.w[d][j] = ldw(p, o & mask);
-  }
+  for (int j = 0; j < kLoads<WT, KS>; ++j) R.w[d][j] = ldw(p, load_off(L, j, mask));
   if constexpr (kQ4<WT>) {
     const char* ps = scale_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
-    for (int j = 0; j < kLoads<WT, KS>; ++j) R.sc[d][j] = ldh(ps, (L.lo[j] >> 3) & mask);
+    for (int j = 0; j < kLoads<WT, KS>; ++j) R.sc[d][j] = ldh(ps, load_off(L, j, mask) >> 3);
   }
 }
 
@@ -672,21 +644,20 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
     f32x4 acc;
     if constexpr (kQ4<WT>) {
       char* sst = st + 16 * kRowUnits<WT, KS> * 16;
+      constexpr int LR = kLoadRows<WT, KS>;
 #pragma unroll
       for (int j = 0; j < kLoads<WT, KS>; ++j) {
-        *reinterpret_cast<u32x4*>(st + (L.so[j] & 0xffffu)) = R.w[f][j];
-        *reinterpret_cast<uint16_t*>(sst + (L.so[j] >> 16)) = (uint16_t)R.sc[f][j];
+        *reinterpret_cast<u32x4*>(st + L.so + j * LR * kRowUnits<WT, KS> * 16) = R.w[f][j];
+        *reinterpret_cast<uint16_t*>(sst + L.ss + j * LR * 16) = (uint16_t)R.sc[f][j];
       }
-      issue_fragment<WT, KS, GATEUP>(R, nc, N, rpt, nr, rw, f, f, mask, lane);
+      issue_fragment<WT, KS, GATEUP>(R, nc, N, rpt, nr, rw, f, f, mask);
       asm volatile("" ::: "memory");
       acc = fragment_sums_q4<KS>(R.act, R.xm, st, lane);
     } else {
       if (f + D < NF)
-        stage<KS>(R.w[0], st, L, frag_base<WT, GATEUP>(c, rpt, r, rw, f + D), L, ~0u,
-                  lane);
+        stage<WT, KS>(R.w[0], st, L, frag_base<WT, GATEUP>(c, rpt, r, rw, f + D), L, ~0u);
       else
-        stage<KS>(R.w[0], st, L, frag_base<WT, GATEUP>(nc, rpt, nr, rw, f + D - NF), N,
-                  mask, lane);
+        stage<WT, KS>(R.w[0], st, L, frag_base<WT, GATEUP>(nc, rpt, nr, rw, f + D - NF), N, mask);
       asm volatile("" ::: "memory");
       acc = fragment_sums<KS>(R.act, st, lane);
     }
@@ -711,7 +682,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int 
   load_slice<WT, KS>(R, c, L, lane);
 #pragma unroll
   for (int f = 0; f < Regs<WT, KS>::kDepth; ++f)
-    issue_fragment<WT, KS, GATEUP>(R, c, L, rpt, r, rw, f, f, ~0u, lane);
+    issue_fragment<WT, KS, GATEUP>(R, c, L, rpt, r, rw, f, f, ~0u);
   enter_slice<WT, KS>(R, L, st, lane);
   float* buf = red;
 #pragma unroll 1
