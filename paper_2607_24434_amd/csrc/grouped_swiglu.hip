@@ -161,10 +161,14 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
   const size_t rowoff = (size_t)t * a.H;
   int pp[8];
   const int kk = a.p_r ? min(a.kk, 8) : 0;
-  for (int j = 0; j < kk; ++j) {
-    const int p = a.pair_pos[(size_t)t * a.kk + j];
-    pp[j] = (p >= 0 && p < a.pairs_max) ? p : -1;
+  // All entries' loads are in flight together (clamped: in bounds).
+  if (kk > 0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) pp[j] = a.pair_pos[(size_t)t * a.kk + min(j, kk - 1)];
   }
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (j >= kk || pp[j] < 0 || pp[j] >= a.pairs_max) pp[j] = -1;
   float ss = 0.f;
   float v[kCombPer];
   for (int h0 = threadIdx.x; h0 < a.H; h0 += NTH * kCombPer) {
@@ -173,12 +177,12 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
     float dv[kCombPer][3], rv[kCombPer][8], res[kCombPer];
 #pragma unroll
     for (int i = 0; i < kCombPer; ++i) {
-      const int h = min(h0 + i * NTH, a.H - 1);
+      const int h = h0 + i * NTH;
+      if (h >= a.H) continue;
 #pragma unroll
       for (int s = 0; s < 3; ++s) dv[i][s] = s < a.n_dense ? a.dense_p[s][rowoff + h] : 0.f;
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        rv[i][j] = (j < kk && pp[j] >= 0) ? a.p_r[(size_t)pp[j] * a.H + h] : 0.f;
+      for (int j = 0; j < 8; ++j) rv[i][j] = pp[j] >= 0 ? a.p_r[(size_t)pp[j] * a.H + h] : 0.f;
       if constexpr (MORE) {  // a dense layer: no routed partials
 #pragma unroll
         for (int s = 0; s < kMaxMore; ++s)
@@ -192,6 +196,9 @@ __device__ __forceinline__ void combine_row(const CombineArgs& a, int t, float* 
       const int h = h0 + i * NTH;
       float x = 0.f;
       if (h < a.H) {
+        // (Opaque to the compiler, which else adds the first partial right after
+        // its load and waits for it before the next ones.)
+        asm volatile("" : "+v"(dv[i][0]));
 #pragma unroll
         for (int s = 0; s < 3; ++s)
           if (s < a.n_dense) x += dv[i][s];
