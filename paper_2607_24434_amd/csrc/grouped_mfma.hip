@@ -5,7 +5,7 @@
 namespace de {
 namespace {
 
-template <typename WT, int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP, bool REREAD>
 __global__ __launch_bounds__(kBlock, 2) void grouped_mfma_kernel(GroupedArgs a) {
   const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
   __shared__ int s_absent, s_nms;
@@ -13,12 +13,24 @@ __global__ __launch_bounds__(kBlock, 2) void grouped_mfma_kernel(GroupedArgs a) 
   if constexpr (!GATEUP) {
     if (s_absent && !a.r.absent_ok) absent_rows_zero(a, mt.tb, mt.nu);
   }
-  mfma_pass<WT, KS, GATEUP>(a, 0, mt.tb, mt.slc, mt.nms, lane, wave);
+  mfma_pass<WT, KS, GATEUP, REREAD>(a, 0, mt.tb, mt.slc, mt.nms, lane, wave);
 }
 
-template <typename WT, int KS, bool GATEUP>
+// True when the blocks of a launch can be cut into one run per position group
+// that reads the same rows at the same time through the same L2: workgroups go
+// to the eight XCDs in turn, so a run is a multiple of eight blocks.  (Three
+// groups would leave CUs idle: their weights pass the L2 by.)
+bool shares_rows(const GroupedArgs& a, int cus) {
+  const int G = a.geo.groups;
+  return !a.has_routed && a.n_dense == 1 && G > 1 && cus % G == 0 && cus / G % 8 == 0 &&
+         a.geo.ndt >= cus;
+}
+
+template <typename WT, int KS, bool GATEUP, bool REREAD = false>
 hipError_t launch_ks(const GroupedArgs& a, int tiles, hipStream_t s) {
-  const auto kernel = grouped_mfma_kernel<WT, KS, GATEUP>;
+  if constexpr (!REREAD && !kQ4<WT>)
+    if (shares_rows(a, dev_info().num_cus)) return launch_ks<WT, KS, GATEUP, true>(a, tiles, s);
+  const auto kernel = grouped_mfma_kernel<WT, KS, GATEUP, REREAD>;
   const size_t lds = mfma_lds<WT, KS>(a);
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
   if (e != hipSuccess) {

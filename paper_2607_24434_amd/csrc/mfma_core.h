@@ -41,7 +41,7 @@
 // Q4_0: a fragment is a quarter of the bytes, so a tile is four fragments and
 // all four are in flight.  The codes become bf16 operands with one conversion
 // per two (the vector ALU needed one conversion and one FMA per weight and
-// position); V2-Lite layer at T = 9: gate/up 43 us (vector ALU 63), down 31
+// position); V2-Lite layer at T = 9: gate/up 41 us (vector ALU 63), down 30
 // (51), bound by the latency of a fragment's way through LDS, conversion and
 // matrix cores.
 //
@@ -50,9 +50,13 @@
 // dense layer of 10944 at T = 9 21 and 15 (78 us with the combine before, 41
 // now); LM head of 102400 at T = 9 72 (101).
 //
-// More than 16 positions are several slices of 16 over the same rows.  Blocks
-// at the same place of two slices' ranges run side by side, so the second
-// reading is served by the caches.
+// More than 16 positions are several slices of 16 over the same rows.  Where
+// a launch has one dense source (a dense layer, the LM head) the blocks that
+// read the same rows for two groups sit on one XCD and run side by side, so the
+// second reading comes from its L2, us before and now (loads that pass the L2
+// by, blocks that drift apart when their groups' sizes differ): LM head of
+// 102400 T = 17 134 and 98, T = 32 103 and 107, T = 64 165 and 160; dense layer
+// of 10944 T = 17 62 and 57, T = 32 64 and 56, T = 64 100 and 72.
 #pragma once
 
 #include "grouped_core.h"
@@ -278,8 +282,16 @@ struct Lanes {
   uint32_t ok;        // bit q: the lane's columns of step q exist
 };
 
+// Weights: past the L2 where they are read once (through it the passes are 4 to
+// 11% slower), kept there for the other position group's block of the XCD with
+// REREAD.
+template <bool REREAD>
 __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
-  return __builtin_nontemporal_load((const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off));
+  const DE_GLOBAL u32x4* p = (const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off);
+  if constexpr (REREAD)
+    return *p;
+  else
+    return __builtin_nontemporal_load(p);
 }
 __device__ __forceinline__ u32x4 ldx(const float* base, uint32_t off) {
   return *(const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off);
@@ -413,14 +425,14 @@ __device__ __forceinline__ void products(const u32x4 (*act)[3], const u32x4 (&b)
 // fragment (first row nw, lane offsets of nl; with mask 0 every lane re-reads
 // nw).  The wave's LDS accesses execute in order, so only the compiler has to
 // be kept from moving them.
-template <typename WT, int KS>
+template <typename WT, int KS, bool REREAD>
 __device__ __forceinline__ void stage(u32x4* w, char* st,
                                       const Lanes<WT, KS>& L, const char* nw,
                                       const Lanes<WT, KS>& nl, uint32_t mask) {
 #pragma unroll
   for (int j = 0; j < kLoads<WT, KS>; ++j) {
     *reinterpret_cast<u32x4*>(st + L.so + j * kLoadRows<WT, KS> * kRowUnits<WT, KS> * 16) = w[j];
-    w[j] = ldw(nw, load_off(nl, j, mask));
+    w[j] = ldw<REREAD>(nw, load_off(nl, j, mask));
   }
 }
 
@@ -457,7 +469,7 @@ __device__ __forceinline__ f32x4 fragment_sums(const u32x4 (&act)[KS][3], const 
 template <int KS>
 __device__ __forceinline__ f32x4 fragment_sums_q4(const u32x4 (&act)[KS][3], const f32x4 (&xm)[KS],
                                                   const char* st, int lane) {
-  constexpr int N = 2, RU = kRowUnits<q4_t, KS>;  // (more would not fit the registers)
+  constexpr int N = kStepGroup<KS>, RU = kRowUnits<q4_t, KS>;
   const uint32_t* rd = reinterpret_cast<const uint32_t*>(st) + (lane & 15) * RU * 4 + (lane >> 4);
   const u32x4 dv = reinterpret_cast<const u32x4*>(st + 16 * RU * 16)[lane & 15];
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -580,13 +592,13 @@ __device__ __forceinline__ uint32_t ldh(const char* base, uint32_t off) {
 }
 
 // The loads of the wave's fragment f of tile r into ring slot d.
-template <typename WT, int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP, bool REREAD>
 __device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
                                                const Lanes<WT, KS>& L, int rpt, int r, int rw,
                                                int f, int d, uint32_t mask) {
   const char* p = frag_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
-  for (int j = 0; j < kLoads<WT, KS>; ++j) R.w[d][j] = ldw(p, load_off(L, j, mask));
+  for (int j = 0; j < kLoads<WT, KS>; ++j) R.w[d][j] = ldw<REREAD>(p, load_off(L, j, mask));
   if constexpr (kQ4<WT>) {
     const char* ps = scale_base<WT, GATEUP>(c, rpt, r, rw, f);
 #pragma unroll
@@ -629,7 +641,7 @@ __device__ __forceinline__ void enter_slice(Regs<WT, KS>& R, const Lanes<WT, KS>
 // One tile of the wave: its fragments' sums to buf.  The registers are
 // refilled from tile nr of slice nc (lanes N; mask 0: nothing follows, the
 // loads all read one word).
-template <typename WT, int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP, bool REREAD>
 __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lanes<WT, KS>& L, int r,
                                      const Slice& nc, const Lanes<WT, KS>& N, int nr, uint32_t mask,
                                      int rpt, int rw, char* st, float* buf, int wave,
@@ -650,14 +662,15 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
         *reinterpret_cast<u32x4*>(st + L.so + j * LR * kRowUnits<WT, KS> * 16) = R.w[f][j];
         *reinterpret_cast<uint16_t*>(sst + L.ss + j * LR * 16) = (uint16_t)R.sc[f][j];
       }
-      issue_fragment<WT, KS, GATEUP>(R, nc, N, rpt, nr, rw, f, f, mask);
+      issue_fragment<WT, KS, GATEUP, REREAD>(R, nc, N, rpt, nr, rw, f, f, mask);
       asm volatile("" ::: "memory");
       acc = fragment_sums_q4<KS>(R.act, R.xm, st, lane);
     } else {
       if (f + D < NF)
-        stage<WT, KS>(R.w[0], st, L, frag_base<WT, GATEUP>(c, rpt, r, rw, f + D), L, ~0u);
+        stage<WT, KS, REREAD>(R.w[0], st, L, frag_base<WT, GATEUP>(c, rpt, r, rw, f + D), L, ~0u);
       else
-        stage<WT, KS>(R.w[0], st, L, frag_base<WT, GATEUP>(nc, rpt, nr, rw, f + D - NF), N, mask);
+        stage<WT, KS, REREAD>(R.w[0], st, L, frag_base<WT, GATEUP>(nc, rpt, nr, rw, f + D - NF), N,
+                              mask);
       asm volatile("" ::: "memory");
       acc = fragment_sums<KS>(R.act, st, lane);
     }
@@ -666,13 +679,12 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
   }
 }
 
-// The block's tiles [lo, hi), hi > lo.
-template <typename WT, int KS, bool GATEUP>
-__device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int hi, int lkw,
-                                       float* red, int lane, int wave) {
+// The block's `count` > 0 tiles from tile r of slice v (then of every step-th
+// slice after it).
+template <typename WT, int KS, bool GATEUP, bool REREAD>
+__device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r, int step,
+                                       int count, int lkw, float* red, int lane, int wave) {
   const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.a.geo.rpt;
-  int v, r;
-  tl.locate(lo, v, r);
   Slice c = tl.slice(v);
   Lanes<WT, KS> L = lanes_of<WT, KS>(c, tl.tb, ks, lkw, lane);
   Regs<WT, KS> R;
@@ -682,22 +694,22 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int 
   load_slice<WT, KS>(R, c, L, lane);
 #pragma unroll
   for (int f = 0; f < Regs<WT, KS>::kDepth; ++f)
-    issue_fragment<WT, KS, GATEUP>(R, c, L, rpt, r, rw, f, f, ~0u);
+    issue_fragment<WT, KS, GATEUP, REREAD>(R, c, L, rpt, r, rw, f, f, ~0u);
   enter_slice<WT, KS>(R, L, st, lane);
   float* buf = red;
 #pragma unroll 1
-  for (int left = hi - lo; left > 0; --left) {
+  for (int left = count; left > 0; --left) {
     // The tile after this one.
     Slice nc = c;
     Lanes<WT, KS> N = L;
     int nr = r + 1;
     const bool more = left > 1, fresh = more && nr >= c.tiles;
     if (fresh) {
-      nc = tl.slice(++v);
+      nc = tl.slice(v += step);
       N = lanes_of<WT, KS>(nc, tl.tb, ks, lkw, lane);
     }
     if (!more || fresh) nr = more ? 0 : r;
-    tile<WT, KS, GATEUP>(R, c, L, r, nc, N, nr, more ? ~0u : 0u, rpt, rw, st, buf, wave, lane);
+    tile<WT, KS, GATEUP, REREAD>(R, c, L, r, nc, N, nr, more ? ~0u : 0u, rpt, rw, st, buf, wave, lane);
     lds_barrier();
     tile_outputs<WT, GATEUP>(c, tl.tb, rpt, r, lkw, buf);
     buf = buf == red ? red + kRedBuf<WT> : red;
@@ -705,8 +717,12 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int lo, int 
     // where they may or may not be, they would make every tile wait for all
     // loads but its newest.
     if (fresh) {
-      load_slice<WT, KS>(R, nc, N, lane);
-      enter_slice<WT, KS>(R, N, st, lane);
+      // (Offsets computed again, not kept in registers across the tile.)
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const Lanes<WT, KS> M = lanes_of<WT, KS>(nc, tl.tb, ks, lkw, ln);
+      load_slice<WT, KS>(R, nc, M, ln);
+      enter_slice<WT, KS>(R, M, st, ln);
     }
     c = nc;
     L = N;
@@ -783,17 +799,36 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
   return mt;
 }
 
-// One pass over the tables of a block: the slices are known (slc, nms).
-template <typename WT, int KS, bool GATEUP>
+// Member `part` of `parts` equal shares of `total` tiles: first tile, and their
+// number to `count`.
+__device__ __forceinline__ int share(uint32_t total, uint32_t part, uint32_t parts, int& count) {
+  const uint32_t each = uni((int)(total / parts)), rest = total - each * parts;
+  count = (int)(each + (part < rest ? 1u : 0u));
+  return (int)(part * each + min(part, rest));
+}
+
+// One pass over the tables of a block: the slices are known (slc, nms).  The
+// block's share of the tiles is contiguous.  REREAD: one dense source and G
+// position groups; the blocks are cut into G runs, and block i of every run
+// takes the same rows for its group.
+template <typename WT, int KS, bool GATEUP, bool REREAD = false>
 __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const Tables& tb,
                                           const int32_t* slc, int nms, int lane, int wave) {
   const Tiles<WT, GATEUP> tl{a, arg, tb, slc, nms};
-  // The block's share of the tiles: contiguous, sizes differing by one.
-  const uint32_t total = tl.total(), each = uni((int)(total / gridDim.x));
-  const uint32_t rest = total - each * gridDim.x;
-  const int lo = (int)(blockIdx.x * each + min(blockIdx.x, rest));
-  const int hi = lo + (int)(each + (blockIdx.x < rest ? 1u : 0u));
-  if (lo < hi) stream<WT, KS, GATEUP>(tl, lo, hi, a.lkw, s_dyn, lane, wave);
+  int count, v, r, step = 1;
+  if constexpr (REREAD) {
+    const int G = a.geo.groups, run = gridDim.x / G, g = uni((int)blockIdx.x / run);
+    const int lo = share(a.geo.ndt / G, blockIdx.x - g * run, run, count);
+    const int chunk = uni(lo / a.geo.tiles[0]);
+    v = chunk * G + g;
+    r = lo - chunk * a.geo.tiles[0];
+    step = G;
+  } else {
+    const int lo = share(tl.total(), blockIdx.x, gridDim.x, count);
+    if (count > 0) tl.locate(lo, v, r);
+  }
+  if (count > 0)
+    stream<WT, KS, GATEUP, REREAD>(tl, v, r, step, count, a.lkw, s_dyn, lane, wave);
 }
 
 // Host side: a with the geometry of its pass.
