@@ -26,21 +26,28 @@ __global__ __launch_bounds__(kResThreads) void residual_kernel(ResidualArgs a) {
   a.out[(size_t)t * a.H + h] = m;
 }
 
-constexpr int kKlThreads = 256;
+// Threads of a row's block, and the values of a row that a thread has in flight.
+// One value at a time on 256 threads, each with a load and an exponential behind
+// the last, 32 rows of 102400 logits took 318 us (the whole signals of a 32-position
+// block 1289 us, 1112 now).
+constexpr int kKlWide = 1024, kKlNarrow = 256, kKlBatch = 8;
+constexpr int kKlNarrowN = 2048;  // router rows: one batch of the narrow block
 
 // Running (max, sum exp(v - max)).
 struct Lse {
   float m, s;
 };
 
-__device__ __forceinline__ Lse lse_add(Lse a, float v) {
-  if (v > a.m) {
-    a.s = a.s * expf(a.m - v) + 1.f;
-    a.m = v;
-  } else {
-    a.s += expf(v - a.m);
-  }
-  return a;
+// a with the values v (-inf adds nothing), rescaled once.
+__device__ __forceinline__ Lse lse_add(Lse a, const float (&v)[kKlBatch]) {
+  float m = a.m;
+#pragma unroll
+  for (int j = 0; j < kKlBatch; ++j) m = fmaxf(m, v[j]);
+  float s = a.m == m ? a.s : a.s * expf(a.m - m);
+#pragma unroll
+  for (int j = 0; j < kKlBatch; ++j)
+    s += v[j] == -INFINITY ? 0.f : (v[j] == m ? 1.f : expf(v[j] - m));
+  return Lse{m, s};
 }
 
 __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
@@ -59,7 +66,7 @@ __device__ __forceinline__ float log_sigmoid(float z) {
 
 // Reduces v over the block with op (every thread receives the result); the
 // members of V are floats.
-template <typename V, typename Op>
+template <int NTH, typename V, typename Op>
 __device__ __forceinline__ V block_reduce(V v, V* red, Op op, V zero) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -76,7 +83,7 @@ __device__ __forceinline__ V block_reduce(V v, V* red, Op op, V zero) {
   if (lane == 0) red[wave] = v;
   __syncthreads();
   V t = zero;
-  for (int w = 0; w < kKlThreads / 64; ++w) t = op(t, red[w]);
+  for (int w = 0; w < NTH / 64; ++w) t = op(t, red[w]);
   return t;
 }
 
@@ -111,50 +118,71 @@ struct SumOp {
 // b; kl = tau^2 KL(p || q).  sigmoid mode: p = sigmoid(a) normalised to sum
 // one, q likewise; kl = KL(p || q).  ce (optional) = -log softmax(b + bias)
 // at the argmax of a + bias (ties to the lower index).
-__global__ __launch_bounds__(kKlThreads) void rowkl_kernel(RowKlArgs a) {
-  __shared__ Lse rl[kKlThreads / 64];
-  __shared__ Best rb[kKlThreads / 64];
-  __shared__ Sum rs[kKlThreads / 64];
+template <int NTH>
+__global__ __launch_bounds__(NTH) void rowkl_kernel(RowKlArgs a) {
+  __shared__ Lse rl[NTH / 64];
+  __shared__ Best rb[NTH / 64];
+  __shared__ Sum rs[NTH / 64];
   const float* pa = a.a + (size_t)blockIdx.x * a.lda;
   const float* pb = a.b + (size_t)blockIdx.x * a.ldb;
   const float it = 1.f / a.tau;
   Lse la{-INFINITY, 0.f}, lb{-INFINITY, 0.f}, lb1{-INFINITY, 0.f};
   Best best{-INFINITY, __int_as_float(INT_MAX)};
-  for (int i = threadIdx.x; i < a.n; i += kKlThreads) {
-    const float bias = a.bias ? a.bias[i] : 0.f;
-    const float va = pa[i], vb = pb[i];
-    if (a.sigmoid) {
-      la = lse_add(la, log_sigmoid(va));
-      lb = lse_add(lb, log_sigmoid(vb));
-    } else {
-      la = lse_add(la, (va + bias) * it);
-      lb = lse_add(lb, (vb + bias) * it);
-      lb1 = lse_add(lb1, vb + bias);
+  // The batch from value i0 on: a + bias and b + bias (sigmoid: log sigmoid of
+  // a and b in x and y, and a + bias in c).  Loads are clamped; what lies past
+  // the row is -inf.
+  float x[kKlBatch], y[kKlBatch], c[kKlBatch];
+  const auto load = [&](int i0) {
+#pragma unroll
+    for (int j = 0; j < kKlBatch; ++j) {
+      const int i = min(i0 + j * NTH, a.n - 1);
+      c[j] = a.bias ? a.bias[i] : 0.f;
+      x[j] = pa[i];
+      y[j] = pb[i];
     }
-    // Argmax of a + bias; a NaN counts as -infinity, as in the argmax.
-    const float vc = va == va ? va + bias : -INFINITY;
-    const int bi = __float_as_int(best.i);
-    if (bi == INT_MAX || vc > best.v) best = Best{vc, __int_as_float(i)};
+#pragma unroll
+    for (int j = 0; j < kKlBatch; ++j) {
+      const bool in = i0 + j * NTH < a.n;
+      const float bias = c[j];
+      c[j] = x[j] + bias;
+      x[j] = !in ? -INFINITY : (a.sigmoid ? log_sigmoid(x[j]) : c[j]);
+      y[j] = !in ? -INFINITY : (a.sigmoid ? log_sigmoid(y[j]) : y[j] + bias);
+    }
+  };
+  for (int i0 = threadIdx.x; i0 < a.n; i0 += NTH * kKlBatch) {
+    load(i0);
+    if (!a.sigmoid) lb1 = lse_add(lb1, y);
+#pragma unroll
+    for (int j = 0; j < kKlBatch; ++j) {
+      // Argmax of a + bias; a NaN counts as -infinity, as in the argmax.
+      const int i = i0 + j * NTH;
+      const float vc = c[j] == c[j] ? c[j] : -INFINITY;
+      if (i < a.n && (__float_as_int(best.i) == INT_MAX || vc > best.v))
+        best = Best{vc, __int_as_float(i)};
+      if (!a.sigmoid) {
+        x[j] *= it;
+        y[j] *= it;
+      }
+    }
+    la = lse_add(la, x);
+    lb = lse_add(lb, y);
   }
-  la = block_reduce(la, rl, LseOp{}, Lse{-INFINITY, 0.f});
-  lb = block_reduce(lb, rl, LseOp{}, Lse{-INFINITY, 0.f});
-  lb1 = block_reduce(lb1, rl, LseOp{}, Lse{-INFINITY, 0.f});
-  best = block_reduce(best, rb, BestOp{}, Best{-INFINITY, __int_as_float(INT_MAX)});
+  la = block_reduce<NTH>(la, rl, LseOp{}, Lse{-INFINITY, 0.f});
+  lb = block_reduce<NTH>(lb, rl, LseOp{}, Lse{-INFINITY, 0.f});
+  lb1 = block_reduce<NTH>(lb1, rl, LseOp{}, Lse{-INFINITY, 0.f});
+  best = block_reduce<NTH>(best, rb, BestOp{}, Best{-INFINITY, __int_as_float(INT_MAX)});
   const float lsa = lse_val(la), lsb = lse_val(lb);
   float acc = 0.f;
-  for (int i = threadIdx.x; i < a.n; i += kKlThreads) {
-    const float bias = a.bias ? a.bias[i] : 0.f;
-    float xa, xb;
-    if (a.sigmoid) {
-      xa = log_sigmoid(pa[i]) - lsa;
-      xb = log_sigmoid(pb[i]) - lsb;
-    } else {
-      xa = (pa[i] + bias) * it - lsa;
-      xb = (pb[i] + bias) * it - lsb;
+  for (int i0 = threadIdx.x; i0 < a.n; i0 += NTH * kKlBatch) {
+    load(i0);
+#pragma unroll
+    for (int j = 0; j < kKlBatch; ++j) {
+      const float xa = (a.sigmoid ? x[j] : x[j] * it) - lsa;
+      const float xb = (a.sigmoid ? y[j] : y[j] * it) - lsb;
+      if (i0 + j * NTH < a.n) acc += expf(xa) * (xa - xb);
     }
-    acc += expf(xa) * (xa - xb);
   }
-  const Sum tot = block_reduce(Sum{acc}, rs, SumOp{}, Sum{0.f});
+  const Sum tot = block_reduce<NTH>(Sum{acc}, rs, SumOp{}, Sum{0.f});
   if (threadIdx.x == 0) {
     a.kl[blockIdx.x] = a.sigmoid ? tot.s : a.tau * a.tau * tot.s;
     if (a.ce != nullptr) {
@@ -175,7 +203,10 @@ hipError_t launch_residual(const ResidualArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_rowkl(const RowKlArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(rowkl_kernel, dim3(a.rows), dim3(kKlThreads), 0, s, a);
+  if (a.n <= kKlNarrowN)
+    hipLaunchKernelGGL(rowkl_kernel<kKlNarrow>, dim3(a.rows), dim3(kKlNarrow), 0, s, a);
+  else
+    hipLaunchKernelGGL(rowkl_kernel<kKlWide>, dim3(a.rows), dim3(kKlWide), 0, s, a);
   return note_hip(hipGetLastError());
 }
 
