@@ -178,9 +178,6 @@ static_assert(kPDFlagsOff + (de::kPDMaxGrid + 32) * 8 <= kCtlBytes, "control are
 struct Layout {
   size_t ctl, z, idx, gate, nu, uids, offs, tok, glist, ppos;
   size_t a_r, a_s, a_d, p_r, p_s, p_d;
-  // Persistent draft pass: gate/up outputs [Is + Id + I], then 8-byte words: rows
-  // [H], logits [kPDCopies, N], flags [kPDCopies, kPDMaxGrid].
-  size_t pd;
   size_t total;
 };
 
@@ -198,11 +195,6 @@ Layout layout(const de_moe_desc& d, int T) {
   // (sticky until de_layer_status reads it), the single-launch verify layer's
   // flags from byte 1024.
   L.ctl = take(kCtlBytes);
-  // The persistent draft pass's buffers (its words are tagged), at the same
-  // offset in every layout, so that no call of another block length writes
-  // there (a value left there by another buffer could carry a matching tag).
-  L.pd = take(((size_t)d.shared_inter + d.draft_inter + d.inter) * 4 +
-              ((size_t)d.hidden + de::kPDCopies * (d.n_experts + de::kPDMaxGrid)) * 8);
   L.z = take((size_t)T * d.n_experts * 4);
   L.idx = take(tk * 4);
   L.gate = take(tk * 4);
@@ -212,6 +204,8 @@ Layout layout(const de_moe_desc& d, int T) {
   L.tok = take(tk * 4);
   L.glist = take(tk * 4);
   L.ppos = take(tk * 4);
+  // (The persistent draft pass keeps all its gate/up outputs, Is + Id + I of them,
+  // from a_r on: a_r holds at least I.)
   L.a_r = take(tk * d.inter * 4);
   L.a_s = take((size_t)T * d.shared_inter * 4);
   L.a_d = take((size_t)T * d.draft_inter * 4);
@@ -647,12 +641,8 @@ int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, con
   a.grid = grid;
   a.spin_limit = 1u << 20;
   a.lds_bytes = draft_persistent_lds(sh);
-  a.a_buf = at<float>(ws, L.pd);
-  // 8-byte aligned: Is, Id and I are multiples of 8.
-  a.d_tag = reinterpret_cast<uint64_t*>(a.a_buf + (sh.Is + sh.Id + sh.I));
-  a.z_tag = a.d_tag + d.hidden;
+  a.a_buf = at<float>(ws, L.a_r);
   a.z_plain = at<float>(ws, L.z);
-  a.grid_flags = a.z_tag + de::kPDCopies * d.n_experts;
   a.status = at<int32_t>(ws, kStatusOff);
   for (int l0 = 0; l0 < n; l0 += kPDMaxLayers) {
     const int cnt = n - l0 < kPDMaxLayers ? n - l0 : kPDMaxLayers;

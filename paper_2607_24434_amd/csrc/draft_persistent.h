@@ -8,7 +8,6 @@ namespace de {
 constexpr int kPDMaxH = 2048;      // hidden size the kernel keeps in LDS
 constexpr int kPDMaxLayers = 32;   // layers per launch (their descriptors ride in the kernel arguments)
 constexpr int kPDMaxGrid = 256;    // blocks (one per CU)
-constexpr int kPDCopies = 8;       // of the logit words and the arrival flags
 
 // One MoE layer of the run.
 struct PDLayer {
@@ -47,19 +46,10 @@ struct PDArgs {
   float* normed_out;              // [H] RMSNorm(y), or NULL
   int32_t* pred_idx;              // [L, k] the top-k of every layer, or NULL
   float* pred_gate;               // [L, k] their gates, or NULL
-  float* a_buf;                   // [Is + Id + I] gate/up outputs
-  // [H] per-row sums of the down partials as (value, tag) words, tagged like
-  // the logit words.
-  uint64_t* d_tag;
-  // [kPDCopies, N] router logits as 64-bit words (value, tag): the tag in the high half
-  // is (epoch << 6) + layer + 1, so a word of another layer or launch is never
-  // taken for this one's.
-  uint64_t* z_tag;
+  float* a_buf;                   // [Is + Id + I] gate/up outputs (16-byte aligned)
   float* z_plain;                 // [N] the last selected layer's logits (the workspace's logit row)
-  // [kPDCopies, kPDMaxGrid] arrival flags, a 64-bit word per block:
-  // (epoch << 32) | arrivals so far.  Every launch has another epoch, so flags
-  // left by earlier launches never count and nothing is reset.
-  uint64_t* grid_flags;
+  // Every launch has another epoch: the exchanged words of earlier launches never
+  // count, and nothing is reset.
   uint32_t epoch;
   uint32_t* done;                 // host word that receives the epoch once every block has started its last wait
   int32_t* status;                // device status word

@@ -78,6 +78,23 @@ constexpr int kMaxSrc = 5;         // down sources: shared chunks, draft expert,
 constexpr int kMaxRows = 16;       // down rows per block
 constexpr int kPDMaxA = 6144;      // gate/up outputs of a layer (Is + Id + I)
 constexpr int kPDMaxLogit = 32;    // blocks computing router logits (one expert per wave)
+constexpr int kPDMaxN = 256;       // experts
+constexpr int kPDCopies = 8;       // of the logit words and the arrival flags
+
+// The words that the blocks of a launch poll.  They belong to the device, not to
+// a workspace: nothing but these launches ever writes here, every kind of word
+// has its own place whatever the shape, and the launches of a device never run
+// side by side.  Zero when the module is loaded, which no epoch is.
+struct PDExchange {
+  // Per-row sums of the down partials, and router logits, as (value, tag) words:
+  // the tag in the high half is (epoch << 6) + layer + 1, so a word of another
+  // layer or launch is never taken for this one's.
+  uint64_t rows[kPDMaxH];
+  uint64_t logits[kPDCopies][kPDMaxN];
+  // Arrival flags, a word per block: (epoch << 32) | arrivals so far.
+  uint64_t flags[kPDCopies][kPDMaxGrid];
+};
+__device__ __align__(256) PDExchange g_exchange;
 
 typedef __attribute__((address_space(4))) const char kchar;
 
@@ -156,12 +173,12 @@ __device__ void grid_arrive(const PDArgs& a, unsigned n) {
   drain();
   __syncthreads();
   if (threadIdx.x < kPDCopies)
-    st_flag(a.grid_flags + threadIdx.x * kPDMaxGrid + blockIdx.x, ((uint64_t)a.epoch << 32) | n);
+    st_flag(&g_exchange.flags[threadIdx.x][blockIdx.x], ((uint64_t)a.epoch << 32) | n);
 }
 // ... and wait until every block has arrived.
 __device__ void grid_wait(const PDArgs& a, unsigned n, int* s_abort) {
   if (threadIdx.x / kWave == kSelWave)
-    wait_flags(a, a.grid_flags + (blockIdx.x % kPDCopies) * kPDMaxGrid, gridDim.x, n, s_abort);
+    wait_flags(a, g_exchange.flags[blockIdx.x % kPDCopies], gridDim.x, n, s_abort);
   __syncthreads();
 }
 
@@ -178,7 +195,7 @@ __device__ __forceinline__ uint32_t layer_tag(const PDArgs& a, int l) {
 __device__ void wait_logits(const PDArgs& a, int l, float (&z)[1][4], int* s_abort) {
   const int lane = threadIdx.x & 63;
   const uint32_t tag = layer_tag(a, l);
-  const uint64_t* const words = a.z_tag + (blockIdx.x % kPDCopies) * a.N;
+  const uint64_t* const words = g_exchange.logits[blockIdx.x % kPDCopies];
   uint64_t w[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -492,7 +509,8 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
       const float4* xs4 = reinterpret_cast<const float4*>(s_x);
       const float z = router_dot_pre(wr, H4, lane, [&](int h) { return xs4[act_at<WT>(4 * h) >> 2]; });
       if (lane < kPDCopies)
-        st_flag(a.z_tag + lane * a.N + e, ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(z));
+        st_flag(&g_exchange.logits[lane][e],
+                ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(z));
     }
   };
   // The top-1 expert of layer l's weight block, or NULL when it has no valid slot.
@@ -619,6 +637,9 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 
     // ---- S2: arrive, put the down rows in flight, wait
     grid_arrive(a, 2 * l + 1);
+    // A block without rows is done with the exchanged words of the last layer here:
+    // those that have some say so by writing them (see the end).
+    if (!more && b * rpb >= H) break;
     const char* e1blk = e1_block(ld);  // selected: every wave passed the block barrier
 #pragma unroll
     for (int q = 0; q < kDnSlots; ++q) {
@@ -656,7 +677,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     if (threadIdx.x < rpb && b * rpb + (int)threadIdx.x < H) {
       float x = 0.f;
       for (int s = 0; s < nsrc; ++s) x += s_part[threadIdx.x * nsrc + s];
-      st_flag(a.d_tag + b * rpb + threadIdx.x,
+      st_flag(g_exchange.rows + b * rpb + threadIdx.x,
               ((uint64_t)layer_tag(a, l) << 32) | __float_as_uint(x));
     }
 
@@ -691,7 +712,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
           const int h = threadIdx.x + kPB * j + kCombVT * i;
-          dwd[j][i] = h < H ? ld_coherent64(a.d_tag + h) : (uint64_t)tag << 32;
+          dwd[j][i] = h < H ? ld_coherent64(g_exchange.rows + h) : (uint64_t)tag << 32;
         }
       for (unsigned it = 0;; ++it) {
         bool ok = true;
@@ -711,7 +732,7 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
 #pragma unroll
           for (int i = 0; i < kPer; ++i) {
             const int h = threadIdx.x + kPB * j + kCombVT * i;
-            if ((uint32_t)(dwd[j][i] >> 32) != tag && h < H) dwd[j][i] = ld_coherent64(a.d_tag + h);
+            if ((uint32_t)(dwd[j][i] >> 32) != tag && h < H) dwd[j][i] = ld_coherent64(g_exchange.rows + h);
           }
       }
     }
@@ -766,9 +787,11 @@ __global__ __launch_bounds__(kPB) void draft_persistent_kernel(PDArgs a) {
     }
   }
 
-  // Every block wrote its last rows, which this one has read: whatever is
-  // still to run waits for nothing.
-  if (b == 0 && threadIdx.x == 0)
+  // Every block wrote its last rows, which this one has read, or had none: whatever
+  // is still to run waits for nothing and reads no exchanged word, so another
+  // stream's launch may follow.  (After a wait that ran out nothing is known of the
+  // other blocks: only this stream's launches may.)
+  if (b == 0 && threadIdx.x == 0 && !*(volatile int*)&s_abort)
     __hip_atomic_store(a.done, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (b == 0 && threadIdx.x == 0 && s_missing)
     __hip_atomic_fetch_or(a.status, kStatusNotResident, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -812,7 +835,7 @@ bool draft_persistent_fits(const PDShape& s, int grid, int* gu_it, int* dn_it) {
   const int al = s.wdtype == DE_Q4_0 ? WTr<q4_t>::EPU : WTr<uint16_t>::EPU;
   if (s.wdtype != DE_BF16 && s.wdtype != DE_Q4_0) return false;
   if (grid < 1 || grid > kPDMaxGrid || s.H < 512 || s.H > kPDMaxH || s.H % al != 0) return false;
-  if (s.N < 1 || s.N > 256 || s.k < 1 || s.k > 32 || s.k > s.N) return false;
+  if (s.N < 1 || s.N > kPDMaxN || s.k < 1 || s.k > 32 || s.k > s.N) return false;
   if (s.I < al || s.I % al || s.Is < 0 || s.Is % al || s.Id < 0 || s.Id % al) return false;
   if (s.n_chunks < 0 || s.n_chunks > 3 || (s.n_chunks > 0 && (s.chunk % al || s.chunk * s.n_chunks != s.Is)))
     return false;

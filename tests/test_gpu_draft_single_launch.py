@@ -125,3 +125,55 @@ def test_captured(shape, monkeypatch):
         layer.run(want)
         torch.cuda.synchronize()
         assert same(out, want)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[6]], ids=["q4", "bf16"])
+def test_with_and_without_the_draft_block_on_one_workspace(shape, monkeypatch):
+    """Calls with and without the draft block, and verify calls, in turn on one
+    workspace: none finds another's values in place of a word it waits for."""
+    layer = Layer(shape, 5)
+    verify = layer.outputs()
+
+    def call(draft, out):
+        keep, layer.draft = layer.draft, layer.draft if draft else None
+        layer.run(out)
+        layer.draft = keep
+
+    want = {}
+    for draft in (True, False):
+        monkeypatch.setenv("DE_PD_SINGLE", "0")
+        want[draft] = layer.outputs()
+        call(draft, want[draft])
+        torch.cuda.synchronize()
+        monkeypatch.setenv("DE_PD_SINGLE", "1")
+    assert not torch.equal(want[True][0], want[False][0])
+    for i in range(70):
+        got = layer.outputs()
+        call(i % 2 == 0, got)
+        if i % 5 == 0:
+            de.de_verify_layer(layer.desc, 1, layer.x, layer.router, layer.bias, layer.table,
+                               layer.shared, verify[0], ws=layer.ws)
+        torch.cuda.synchronize()
+        assert same(got, want[i % 2 == 0]), i
+    assert de.de_layer_status(layer.ws) == 0
+
+
+@pytest.mark.parametrize("dt", [de.DE_Q4_0, de.DE_BF16], ids=["q4", "bf16"])
+def test_blocks_without_rows_on_two_streams(dt, monkeypatch):
+    """A hidden size whose rows do not reach every block (544 rows, three a block),
+    on two streams at once."""
+    shape = (dt, 544, 64, 4, 1408, 2816, 1408, de.DE_SOFTMAX, 0)
+    layers = [Layer(shape, s) for s in (6, 7)]
+    want = [separate(l, monkeypatch) for l in layers]
+    streams = [torch.cuda.Stream() for _ in layers]
+    got = [[l.outputs() for _ in range(40)] for l in layers]
+    torch.cuda.synchronize()
+    for i in range(40):
+        for l, s, g in zip(layers, streams, got):
+            l.run(g[i], stream=s)
+            if i % 4 == 3:
+                s.synchronize()  # the next call, on the other stream, may follow
+    torch.cuda.synchronize()
+    for l, g, w in zip(layers, got, want):
+        assert de.de_layer_status(l.ws) == 0
+        assert all(same(o, w) for o in g)
