@@ -541,28 +541,71 @@ __device__ __forceinline__ void put_partial(float* buf, const f32x4& acc, int f,
   }
 }
 
-// The tile's outputs from the waves' sums (after the barrier).
-template <typename WT, bool GATEUP>
-__device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
-                                             int lkw, const float* buf) {
+// A bf16 row's product with one position in fp32, by one wave, in the vector ALU
+// path's order: what a sum that came out NaN is taken from.  (An infinite weight
+// meets a zero mid or lo part of nearly every finite activation, and that product
+// is NaN on the matrix cores.)  Every lane gets the sum.
+__device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int pos, int row,
+                                           int64_t to, int lane) {
+  const int p = c.listed ? tb.tok[c.p0 + pos] : c.p0 + pos;
+  const float* x = c.act + (size_t)p * c.astride;
+  const char* w = c.w + (size_t)row * c.rb + to;
+  float s = 0.f;
+#pragma unroll 1
+  for (int u = lane; u < c.K / 8; u += kWave) {
+    float v[8];
+    unpack(ldw<true>(w, (uint32_t)u * 16u), v);
+    const u32x4 x0 = ldx(x, u * 32u), x1 = ldx(x, u * 32u + 16u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = fmaf(v[i], __uint_as_float(x0[i]), s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = fmaf(v[4 + i], __uint_as_float(x1[i]), s);
+  }
+  return row_total(s);
+}
+
+// The tile's outputs from the waves' sums (after the barrier).  With PLAIN a sum
+// that is NaN is taken from plain_dot.  True when the thread met one.
+template <typename WT, bool GATEUP, bool PLAIN>
+__device__ __forceinline__ bool write_outputs(const Slice& c, const Tables& tb, int rpt, int r,
+                                              int lkw, const float* buf) {
   const int kw = 1 << lkw, nrw = kWavesPB >> lkw;
   constexpr int kG = GATEUP ? kFrags<WT> / 2 : kFrags<WT>;  // 16-row groups of a row group
   constexpr int kWaveRed = kFrags<WT> * kRedTile;
+  bool met = false;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // addresses are computed again for every tile
 #pragma unroll 1
-  for (int o = tid; o < 256 * kG * nrw; o += kBlock) {
+  for (int o = tid; o < 256 * kG * nrw; o += kBlock) {  // (whole waves)
     // Row within 16, 16-row group, position, row group.
     const int rr = o & 15, i = (o >> 4) & (kG - 1), pos = (o / (16 * kG)) & 15, rg = o / (256 * kG);
     const int row = frag_row<WT, GATEUP>(c, rpt, r, rg, i) + rr;
-    if (pos < c.nt && row < c.rows) {
+    const bool mine = pos < c.nt && row < c.rows;
+    float s = 0.f, u = 0.f;
+    if (mine) {
       const float* q = buf + (rg << lkw) * kWaveRed + (GATEUP ? 2 * i : i) * kRedTile +
                        pos * kRedLd + rr;
-      float s = 0.f, u = 0.f;
       for (int k = 0; k < kw; ++k) {
         s += q[k * kWaveRed];
         if constexpr (GATEUP) u += q[k * kWaveRed + kRedTile];
       }
+      met = met || !(s == s) || !(u == u);
+    }
+    if constexpr (PLAIN) {
+      unsigned long long bad = __builtin_amdgcn_ballot_w64(!(s == s) || !(u == u));
+#pragma unroll 1
+      for (; bad != 0ull; bad &= bad - 1) {
+        const int l = (int)__builtin_ctzll(bad), lane = tid & 63;
+        const int p = __builtin_amdgcn_readlane(pos, l), w = __builtin_amdgcn_readlane(row, l);
+        const float ds = plain_dot(c, tb, p, w, 0, lane);
+        if (lane == l && !(s == s)) s = ds;
+        if constexpr (GATEUP) {
+          const float du = plain_dot(c, tb, p, w, c.w2, lane);
+          if (lane == l && !(u == u)) u = du;
+        }
+      }
+    }
+    if (mine) {
       float val;
       if constexpr (GATEUP)
         val = silu_f(s) * u;
@@ -570,6 +613,17 @@ __device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, i
         val = (c.goff >= 0 ? tb.gate[c.goff + pos] : c.gscalar) * s;
       *(DE_GLOBAL float*)(c.out + (size_t)(c.p0 + pos) * c.ostride + row) = val;
     }
+  }
+  return met;
+}
+
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
+                                             int lkw, const float* buf) {
+  const bool met = write_outputs<WT, GATEUP, false>(c, tb, rpt, r, lkw, buf);
+  if constexpr (!kQ4<WT>) {
+    if (__builtin_amdgcn_ballot_w64(met) != 0ull)
+      write_outputs<WT, GATEUP, true>(c, tb, rpt, r, lkw, buf);
   }
 }
 
