@@ -784,19 +784,28 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
   }
 }
 
+// Room for the member slices: lists that share no entry need no more.
+__host__ __device__ __forceinline__ int slice_room(const RoutedSrc& r) {
+  return r.max_union + r.pairs_max / kXP + 1;
+}
+
 // The member slices: every resident member's positions in groups of 16, in
-// member order.  One wave; returns their number.
-__device__ __forceinline__ int member_slices(const Tables& tb, int nu, int32_t* slc, int lane) {
+// member order.  Each member's list has been checked by itself (fill_tables);
+// lists that overlap could make more slices than there is room for, and those are
+// dropped.  One wave; returns their number.
+__device__ __forceinline__ int member_slices(const Tables& tb, int nu, int32_t* slc, int room,
+                                             int lane) {
   int base = 0;
   for (int j0 = 0; j0 < nu; j0 += kWave) {
     const int j = j0 + lane;
     int ng = 0;
     if (j < nu && tb.mem[j].blk != nullptr) ng = (tb.mem[j].ntok + kXP - 1) / kXP;
     const int inc = wave_scan_i32(ng);
-    for (int i = 0; i < ng; ++i) slc[base + inc - ng + i] = (j << 8) | i;
+    const int first = base + inc - ng;
+    for (int i = 0; i < ng && first + i < room; ++i) slc[first + i] = (j << 8) | i;
     base += __builtin_amdgcn_readlane(inc, 63);
   }
-  return base;
+  return min(base, room);
 }
 
 // LDS: [partials][staged weights][tables][selection state (gate/up)][member slices]
@@ -837,7 +846,7 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
     mt.nu = uni(fill_tables(a, mt.tb, absent));
     __syncthreads();
     if (wave == 0) {
-      const int c = member_slices(mt.tb, mt.nu, slc, lane);
+      const int c = member_slices(mt.tb, mt.nu, slc, slice_room(a.r), lane);
       if (lane == 0) *nms = c;
     }
     __syncthreads();
@@ -908,7 +917,7 @@ GroupedArgs with_geometry(GroupedArgs a) {
 template <typename WT, int KS>
 size_t mfma_lds(const GroupedArgs& a) {
   size_t b = (size_t)(kRedFloats<WT> + kStageFloats<WT, KS>)*4 + tables_bytes(a);
-  if (a.has_routed) b += ((size_t)a.r.max_union + a.r.pairs_max / kXP + 1) * 4;
+  if (a.has_routed) b += (size_t)slice_room(a.r) * 4;
   return b;
 }
 

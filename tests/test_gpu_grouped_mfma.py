@@ -154,3 +154,32 @@ def test_lm_head(T, H, V):
     out = torch.empty(T, V, device="cuda")
     de.de_lm_head(T, H, V, x, w, out)
     assert torch.equal(out.double(), x.double() @ w.double().t())
+
+
+@pytest.mark.parametrize("dt", [de.DE_BF16, de.DE_Q4_0], ids=["bf16", "q4"])
+def test_lists_that_overlap_stay_in_bounds(dt):
+    """Offsets that no union has (every second member owns all T k entries) make
+    eight times the slices a block has room for: those past it are dropped.  With
+    equal experts the members that remain write what one member would."""
+    T, H, N, k, I = 64, 288, 64, 6, 160
+    x, w, _ = inputs(T, H, 1, I, 0, 9)
+    blk = w[0] if dt == de.DE_BF16 else q4_blocks(w[0], 1, I, H)[0]
+    d = de.make_desc(H, N, k, I, 0, 0, de.DE_SOFTMAX, False, 1.0, dt)
+    tab = de.make_table(blk.expand(N, -1).contiguous(), de.expert_bytes(dt, I, H), None, N)
+
+    def i32(*v):
+        return torch.tensor(v, dtype=torch.int32, device="cuda")
+
+    pos = torch.arange(T * k, dtype=torch.int32, device="cuda")
+    tok, ppos = (pos // k).contiguous(), pos.view(T, k)
+    gate = torch.rand(T * k, generator=torch.Generator().manual_seed(1)).cuda()
+    ws = de.workspace(d, T)
+    out = []
+    for n, offs in ((1, [0] + [T * k] * N), (N, [0, T * k] * (N // 2) + [0])):
+        y = torch.empty_like(x)
+        de.de_grouped_swiglu(d, T, x, tab, i32(n), i32(*range(N)), i32(*offs), tok, gate, ppos,
+                             None, y, ws)
+        torch.cuda.synchronize()
+        assert de.de_layer_status(ws) == 0
+        out.append(y)
+    assert torch.isfinite(out[0]).all() and torch.equal(out[0], out[1])
