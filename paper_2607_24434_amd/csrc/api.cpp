@@ -350,6 +350,51 @@ int mfma_chunks(int K, int rows, int T, int most) {
   return best;
 }
 
+// What the launches of a device whose blocks wait for each other (drafted
+// positions, the single-launch verify layer) know of each other.  All blocks of
+// one have to be resident: two launches on two streams could each hold a part of
+// the chip.  A launch therefore joins only its own stream's, or goes out once the
+// last one's blocks need nothing more of the chip (its epoch is then in *done,
+// which it writes); else the caller's separate launches run, with the same bits.
+struct PDDevice {
+  std::mutex mu;
+  bool asked = false;
+  uint32_t* done = nullptr;  // pinned host word; NULL: not available
+  hipStream_t stream = nullptr;
+  uint32_t epoch = 0;        // the last launch's; 0: none yet
+};
+constexpr int kPDDevices = 64;
+
+PDDevice* pd_device() {
+  static PDDevice devs[kPDDevices];
+  const int i = de::dev_info().device;
+  return i >= 0 && i < kPDDevices ? &devs[i] : nullptr;
+}
+
+// True when such a launch may go to stream s now (p.mu is held).
+bool pd_may_launch(PDDevice& p, hipStream_t s) {
+  // Under capture a replay would find its own epoch in the flags.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (!p.asked) {
+    p.asked = true;
+    void* w = nullptr;
+    if (hipHostMalloc(&w, sizeof(uint32_t), hipHostMallocMapped) == hipSuccess) {
+      p.done = static_cast<uint32_t*>(w);
+      __atomic_store_n(p.done, 0u, __ATOMIC_RELAXED);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  if (p.done == nullptr) return false;
+  if (p.epoch == 0 || __atomic_load_n(p.done, __ATOMIC_ACQUIRE) == p.epoch) return true;
+  // (One handle stands for every thread's own stream.)
+  return s == p.stream && s != hipStreamPerThread;
+}
+
 // gate/up + down + combine over the union (kk entries per position) and the
 // dense sources (shared path with gate 1, optionally the draft expert).
 // With dense_on false the dense sources are left out of the two grouped
@@ -361,9 +406,17 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
                 const de::TopkUnionArgs* fused_sel, hipStream_t s, bool dense_on = true,
                 bool combine_on = true, bool fuse_select = false,
                 const float* next_router = nullptr) {
-  const bool fused = fused_sel != nullptr && fuse_select && dense_on && combine_on &&
-                     next_router == nullptr && draft_w == nullptr && !r.absent_ok &&
-                     fused_shape(d, T) && de::verify_fused_enabled();
+  bool fused = fused_sel != nullptr && fuse_select && dense_on && combine_on &&
+               next_router == nullptr && draft_w == nullptr && !r.absent_ok &&
+               fused_shape(d, T) && de::verify_fused_enabled() &&
+               de::dev_info().num_cus <= de::kPDMaxGrid;
+  PDDevice* const dev = fused ? pd_device() : nullptr;
+  std::unique_lock<std::mutex> lock;
+  if (fused) {
+    if (dev != nullptr) lock = std::unique_lock<std::mutex>(dev->mu);
+    fused = dev != nullptr && pd_may_launch(*dev, s);
+    if (!fused && lock.owns_lock()) lock.unlock();
+  }
   const bool q4 = d.wdtype == DE_Q4_0;
   const size_t esz = q4 ? 0 : elem_bytes(d.wdtype);
   de::GroupedArgs g{};
@@ -488,7 +541,13 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
     f.flags = at<uint64_t>(ws, kPDFlagsOff);
     f.epoch = next_epoch();
     f.status = r.status;
-    return hip_status(timed_layer(s, [&] { return de::launch_verify_fused(f, s); }));
+    f.done = dev->done;
+    e = timed_layer(s, [&] { return de::launch_verify_fused(f, s); });
+    if (e == hipSuccess) {
+      dev->stream = s;
+      dev->epoch = f.epoch;
+    }
+    return hip_status(e);
   }
   e = timed_phase(DE_PHASE_DOWN, s, [&] { return de::launch_down(g, d.wdtype, s); });
   if (e != hipSuccess) return DE_ERR_HIP;
@@ -542,50 +601,6 @@ bool draft_persistent_enabled() {
 bool pd_single_enabled() {
   const char* e = std::getenv("DE_PD_SINGLE");
   return e == nullptr || e[0] != '0';
-}
-
-// What the persistent launches of a device know of each other.  The blocks of
-// one wait for each other, so all of them have to be resident: two launches on
-// two streams could each hold a part of the chip.  A launch therefore joins
-// only its own stream's, or goes out once the last one's blocks need nothing
-// more of the chip (its epoch is then in *done, which it writes).
-struct PDDevice {
-  std::mutex mu;
-  bool asked = false;
-  uint32_t* done = nullptr;  // pinned host word; NULL: not available
-  hipStream_t stream = nullptr;
-  uint32_t epoch = 0;        // the last launch's; 0: none yet
-};
-constexpr int kPDDevices = 64;
-
-PDDevice* pd_device() {
-  static PDDevice devs[kPDDevices];
-  const int i = dev_info().device;
-  return i >= 0 && i < kPDDevices ? &devs[i] : nullptr;
-}
-
-// True when a persistent launch may go to stream s now (p.mu is held).
-bool pd_may_launch(PDDevice& p, hipStream_t s) {
-  // Under capture a replay would find its own epoch in the flags.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (!p.asked) {
-    p.asked = true;
-    void* w = nullptr;
-    if (hipHostMalloc(&w, sizeof(uint32_t), hipHostMallocMapped) == hipSuccess) {
-      p.done = static_cast<uint32_t*>(w);
-      __atomic_store_n(p.done, 0u, __ATOMIC_RELAXED);
-    } else {
-      (void)hipGetLastError();
-    }
-  }
-  if (p.done == nullptr) return false;
-  if (p.epoch == 0 || __atomic_load_n(p.done, __ATOMIC_ACQUIRE) == p.epoch) return true;
-  // (One handle stands for every thread's own stream.)
-  return s == p.stream && s != hipStreamPerThread;
 }
 
 // Runs draft layers layers[0..n) (n >= 1) of one position (T = 1, the top-1

@@ -12,6 +12,7 @@ struct FusedArgs {
   uint64_t* flags;     // [grid] arrival words, never decreasing
   uint32_t epoch;      // this launch's; the words of earlier launches are smaller
   int32_t* status;     // device status word
+  uint32_t* done;      // host word that receives the epoch once no block waits any more
 };
 
 // Blocks of 2 to 9 positions of a matrix-core layer.

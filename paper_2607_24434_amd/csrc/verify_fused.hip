@@ -9,9 +9,10 @@
 //
 // A block arrives at a point by storing (launch epoch, point) to its word and
 // waits until no block's word is smaller.  The grid is one block per CU (each
-// takes more than half of a CU's LDS), so on a device the stream has to itself
-// every block is resident from the start; every wait is bounded in any case,
-// and one that runs out records kStatusSyncTimeout.
+// takes more than half of a CU's LDS), and the host sends no such launch beside
+// another one whose blocks wait (nor into a graph, whose replays would find their
+// own epoch in the words), so every block gets its CU; every wait is bounded in
+// any case, and one that runs out records kStatusSyncTimeout.
 #include "verify_fused.h"
 
 #include <algorithm>
@@ -112,6 +113,9 @@ __global__ __launch_bounds__(kBlock, 2) void verify_fused_kernel(FusedArgs f) {
   if (s_absent) absent_rows_zero(f.dn, mt.tb, mt.nu);
   mfma_pass<uint16_t, kFKS, false>(f.dn, offsetof(FusedArgs, dn), mt.tb, mt.slc, mt.nms, lane, wave);
   grid_point(f, 2, &s_abort);
+  // Every block is past its work for the others: another stream's launch may follow.
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !*(volatile int*)&s_abort)
+    __hip_atomic_store(f.done, f.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   for (int t = blockIdx.x; t < f.c.T; t += gridDim.x) {
     combine_position(f.c, t, s_red);
     __syncthreads();  // s_red is reused

@@ -222,3 +222,60 @@ def test_layer_phase_timer_brackets_the_launch():
     ms = e[0].elapsed_time(e[1])
     print(f"single launch: {1e3 * ms:.1f} us", flush=True)
     assert 0.0 < ms < 50.0
+
+
+def fresh(dev, x, T, ws, y, stream=None):
+    de.de_verify_layer(dev.desc, T, x, dev.router, dev.bias, dev.table, dev.shared, y, ws=ws,
+                       stream=stream)
+
+
+def test_two_streams_and_drafted_positions():
+    """Single-launch layers on two streams at once, with drafted positions (whose
+    blocks wait for each other too) on a third: no launch shares the chip with
+    another one that waits, and every output is that of the separate launches."""
+    cfg, T, n = configs.CFG2, 9, 20
+    orc, dev = layer_pair(cfg)
+    x = f32(gapped_x(orc, T, block=3)[0])
+    y = torch.empty(n, 3, T, cfg.hidden, dtype=torch.float32, device="cuda")
+    want, draft = torch.empty_like(y[0, 0]), torch.empty_like(y[0, 0, 0])
+
+    def drafted(out, ws, stream=None):
+        de.de_draft_layer(dev.desc, 1, x, dev.router, dev.bias, dev.table, dev.shared, dev.draft,
+                          cfg.gamma, out, None, None, ws, stream=stream)
+
+    ws = [dev.ws(T) for _ in range(3)]
+    with launch_mode("0"):
+        fresh(dev, x, T, ws[0], want)
+        drafted(draft, ws[2])
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for i in range(n):
+        for j in range(2):
+            fresh(dev, x, T, ws[j], y[i, j], streams[j])
+        drafted(y[i, 2, 0], ws[2], streams[2])
+    torch.cuda.synchronize()
+    for w in ws:
+        assert de.de_layer_status(w) == 0
+    assert all(same_bits(y[i, j], want) for i in range(n) for j in range(2))
+    assert all(same_bits(y[i, 2, 0], draft) for i in range(n))
+
+
+def test_captured():
+    """A captured call replays on changed inputs, with eager calls between."""
+    cfg, T = configs.CFG2, 9
+    _, dev = layer_pair(cfg)
+    x = torch.randn(T, cfg.hidden, device="cuda")
+    y, want, ws = torch.empty_like(x), torch.empty_like(x), [dev.ws(T), dev.ws(T)]
+    fresh(dev, x, T, ws[0], y)
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        fresh(dev, x, T, ws[0], y, s)
+    for _ in range(4):
+        x.normal_()
+        graph.replay()
+        torch.cuda.synchronize()
+        fresh(dev, x, T, ws[1], want)
+        torch.cuda.synchronize()
+        assert same_bits(y, want)
+    assert de.de_layer_status(ws[0]) == de.de_layer_status(ws[1]) == 0
