@@ -581,9 +581,9 @@ bool lmhead_mfma_enabled() {
 }
 
 // The verify layer runs as one launch, where its shape allows, only when
-// DE_VERIFY_FUSED is "1": the down blocks wait for gate/up outputs that the
-// last gate/up waves write, so the launch is slower than the separate
-// launches (both give the same bits).
+// DE_VERIFY_FUSED is "1": every block waits at its two device-wide points for the
+// slowest one, and it is slower than the separate launches (both give the same
+// bits).
 bool verify_fused_enabled() {
   const char* e = std::getenv("DE_VERIFY_FUSED");
   return e != nullptr && e[0] == '1';

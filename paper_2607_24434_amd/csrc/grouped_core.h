@@ -541,7 +541,8 @@ __device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& t
     if (out) {
       a.sel.tok_list[p] = t;
       a.sel.gate_list[p] = g;
-      a.sel.pair_pos[i] = p;
+      // (Read by other blocks of the single-launch verify layer.)
+      __hip_atomic_store(a.sel.pair_pos + i, p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   if (out) {
@@ -552,8 +553,19 @@ __device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& t
   return min(nu, rs.max_union);
 }
 
+// An output value; SHARED: read by other blocks of the same launch, so it goes past
+// the XCD's own L2 cache.
+template <bool SHARED>
+__device__ __forceinline__ void st_out(float* p, float v) {
+  if constexpr (SHARED)
+    __hip_atomic_store((DE_GLOBAL float*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *(DE_GLOBAL float*)p = v;
+}
+
 // Down: a needed member without a slot contributes zero partials (the combine
 // sums its pairs like any other), spread over the grid.
+template <bool SHARED = false>
 __device__ __forceinline__ void absent_rows_zero(const GroupedArgs& a, const Tables& tb, int nu) {
   const size_t gstride = (size_t)gridDim.x * kBlock;
   for (int j = 0; j < nu; ++j) {
@@ -562,7 +574,7 @@ __device__ __forceinline__ void absent_rows_zero(const GroupedArgs& a, const Tab
     float* p = a.r.p + (size_t)m.off * a.H;
     const size_t n = (size_t)m.ntok * a.H;
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += gstride)
-      *(DE_GLOBAL float*)(p + i) = 0.f;
+      st_out<SHARED>(p + i, 0.f);
   }
 }
 

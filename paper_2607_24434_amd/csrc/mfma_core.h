@@ -293,8 +293,24 @@ __device__ __forceinline__ u32x4 ldw(const char* base, uint32_t off) {
   else
     return __builtin_nontemporal_load(p);
 }
+// Activations.  SHARED: written by other blocks of this launch, so read at agent
+// scope, past the XCDs' own L2 caches.
+template <bool SHARED>
 __device__ __forceinline__ u32x4 ldx(const float* base, uint32_t off) {
-  return *(const DE_GLOBAL u32x4*)((const DE_GLOBAL char*)base + off);
+  const DE_GLOBAL char* p = (const DE_GLOBAL char*)base + off;
+  if constexpr (SHARED) {
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint64_t w = __hip_atomic_load((const DE_GLOBAL uint64_t*)p + i, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      v[2 * i] = (uint32_t)w;
+      v[2 * i + 1] = (uint32_t)(w >> 32);
+    }
+    return v;
+  } else {
+    return *(const DE_GLOBAL u32x4*)p;
+  }
 }
 
 // The lane's byte offset of load j from the fragment's first row (rows past the
@@ -339,17 +355,17 @@ __device__ __forceinline__ Lanes<WT, KS> lanes_of(const Slice& c, const Tables& 
 }
 
 // The lane's 8 activations of step q (fp32).
-template <typename WT, int KS>
+template <typename WT, int KS, bool SHARED>
 __device__ __forceinline__ void load_x(u32x4 (&f)[3], const float* x, const Lanes<WT, KS>& L, int q,
                                        int g) {
   if constexpr (kQ4<WT>) {
     const uint32_t o = L.xo + (uint32_t)min(L.u0 + q, L.ulast) * 128u + g * 16u;
-    f[0] = ldx(x, o);
-    f[1] = ldx(x, o + 64u);
+    f[0] = ldx<SHARED>(x, o);
+    f[1] = ldx<SHARED>(x, o + 64u);
   } else {
     const uint32_t o = L.xo + (uint32_t)min(L.u0 + 4 * q + g, L.ulast) * 32u;
-    f[0] = ldx(x, o);
-    f[1] = ldx(x, o + 16u);
+    f[0] = ldx<SHARED>(x, o);
+    f[1] = ldx<SHARED>(x, o + 16u);
   }
 }
 
@@ -545,6 +561,7 @@ __device__ __forceinline__ void put_partial(float* buf, const f32x4& acc, int f,
 // path's order: what a sum that came out NaN is taken from.  (An infinite weight
 // meets a zero mid or lo part of nearly every finite activation, and that product
 // is NaN on the matrix cores.)  Every lane gets the sum.
+template <bool SHARED>
 __device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int pos, int row,
                                            int64_t to, int lane) {
   const int p = c.listed ? tb.tok[c.p0 + pos] : c.p0 + pos;
@@ -555,7 +572,7 @@ __device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int
   for (int u = lane; u < c.K / 8; u += kWave) {
     float v[8];
     unpack(ldw<true>(w, (uint32_t)u * 16u), v);
-    const u32x4 x0 = ldx(x, u * 32u), x1 = ldx(x, u * 32u + 16u);
+    const u32x4 x0 = ldx<SHARED>(x, u * 32u), x1 = ldx<SHARED>(x, u * 32u + 16u);
 #pragma unroll
     for (int i = 0; i < 4; ++i) s = fmaf(v[i], __uint_as_float(x0[i]), s);
 #pragma unroll
@@ -565,8 +582,10 @@ __device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int
 }
 
 // The tile's outputs from the waves' sums (after the barrier).  With PLAIN a sum
-// that is NaN is taken from plain_dot.  True when the thread met one.
-template <typename WT, bool GATEUP, bool PLAIN>
+// that is NaN is taken from plain_dot.  True when the thread met one.  SHARED:
+// other blocks of this launch read them (and the down pass's activations come from
+// other blocks).
+template <typename WT, bool GATEUP, bool SHARED, bool PLAIN>
 __device__ __forceinline__ bool write_outputs(const Slice& c, const Tables& tb, int rpt, int r,
                                               int lkw, const float* buf) {
   const int kw = 1 << lkw, nrw = kWavesPB >> lkw;
@@ -597,10 +616,10 @@ __device__ __forceinline__ bool write_outputs(const Slice& c, const Tables& tb, 
       for (; bad != 0ull; bad &= bad - 1) {
         const int l = (int)__builtin_ctzll(bad), lane = tid & 63;
         const int p = __builtin_amdgcn_readlane(pos, l), w = __builtin_amdgcn_readlane(row, l);
-        const float ds = plain_dot(c, tb, p, w, 0, lane);
+        const float ds = plain_dot<SHARED && !GATEUP>(c, tb, p, w, 0, lane);
         if (lane == l && !(s == s)) s = ds;
         if constexpr (GATEUP) {
-          const float du = plain_dot(c, tb, p, w, c.w2, lane);
+          const float du = plain_dot<false>(c, tb, p, w, c.w2, lane);
           if (lane == l && !(u == u)) u = du;
         }
       }
@@ -611,19 +630,19 @@ __device__ __forceinline__ bool write_outputs(const Slice& c, const Tables& tb, 
         val = silu_f(s) * u;
       else
         val = (c.goff >= 0 ? tb.gate[c.goff + pos] : c.gscalar) * s;
-      *(DE_GLOBAL float*)(c.out + (size_t)(c.p0 + pos) * c.ostride + row) = val;
+      st_out<SHARED>(c.out + (size_t)(c.p0 + pos) * c.ostride + row, val);
     }
   }
   return met;
 }
 
-template <typename WT, bool GATEUP>
+template <typename WT, bool GATEUP, bool SHARED>
 __device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
                                              int lkw, const float* buf) {
-  const bool met = write_outputs<WT, GATEUP, false>(c, tb, rpt, r, lkw, buf);
+  const bool met = write_outputs<WT, GATEUP, SHARED, false>(c, tb, rpt, r, lkw, buf);
   if constexpr (!kQ4<WT>) {
     if (__builtin_amdgcn_ballot_w64(met) != 0ull)
-      write_outputs<WT, GATEUP, true>(c, tb, rpt, r, lkw, buf);
+      write_outputs<WT, GATEUP, SHARED, true>(c, tb, rpt, r, lkw, buf);
   }
 }
 
@@ -661,11 +680,11 @@ __device__ __forceinline__ void issue_fragment(Regs<WT, KS>& R, const Slice& c,
 }
 
 // The loads of a slice's activations (as fp32 values).
-template <typename WT, int KS>
+template <typename WT, int KS, bool SHARED>
 __device__ __forceinline__ void load_slice(Regs<WT, KS>& R, const Slice& c, const Lanes<WT, KS>& L,
                                            int lane) {
 #pragma unroll
-  for (int q = 0; q < KS; ++q) load_x<WT, KS>(R.act[q], c.act, L, q, lane >> 4);
+  for (int q = 0; q < KS; ++q) load_x<WT, KS, SHARED>(R.act[q], c.act, L, q, lane >> 4);
 }
 
 // Makes operands of them; the wave's LDS rows are cleared (units past the
@@ -735,7 +754,7 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
 
 // The block's `count` > 0 tiles from tile r of slice v (then of every step-th
 // slice after it).
-template <typename WT, int KS, bool GATEUP, bool REREAD>
+template <typename WT, int KS, bool GATEUP, bool REREAD, bool SHARED>
 __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r, int step,
                                        int count, int lkw, float* red, int lane, int wave) {
   const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.a.geo.rpt;
@@ -745,7 +764,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
   char* st = reinterpret_cast<char*>(red + kRedFloats<WT>) + wave * kWaveStage<WT, KS>;
   // The first activations go out before the weights: they arrive first and
   // are split while the weights are on their way.
-  load_slice<WT, KS>(R, c, L, lane);
+  load_slice<WT, KS, SHARED && !GATEUP>(R, c, L, lane);
 #pragma unroll
   for (int f = 0; f < Regs<WT, KS>::kDepth; ++f)
     issue_fragment<WT, KS, GATEUP, REREAD>(R, c, L, rpt, r, rw, f, f, ~0u);
@@ -765,7 +784,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
     if (!more || fresh) nr = more ? 0 : r;
     tile<WT, KS, GATEUP, REREAD>(R, c, L, r, nc, N, nr, more ? ~0u : 0u, rpt, rw, st, buf, wave, lane);
     lds_barrier();
-    tile_outputs<WT, GATEUP>(c, tl.tb, rpt, r, lkw, buf);
+    tile_outputs<WT, GATEUP, SHARED>(c, tl.tb, rpt, r, lkw, buf);
     buf = buf == red ? red + kRedBuf<WT> : red;
     // A later slice's are used at once: left in flight into the next tile,
     // where they may or may not be, they would make every tile wait for all
@@ -775,7 +794,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
       int ln = lane;
       asm volatile("" : "+v"(ln));
       const Lanes<WT, KS> M = lanes_of<WT, KS>(nc, tl.tb, ks, lkw, ln);
-      load_slice<WT, KS>(R, nc, M, ln);
+      load_slice<WT, KS, SHARED && !GATEUP>(R, nc, M, ln);
       enter_slice<WT, KS>(R, M, st, ln);
     }
     c = nc;
@@ -873,8 +892,9 @@ __device__ __forceinline__ int share(uint32_t total, uint32_t part, uint32_t par
 // One pass over the tables of a block: the slices are known (slc, nms).  The
 // block's share of the tiles is contiguous.  REREAD: one dense source and G
 // position groups; the blocks are cut into G runs, and block i of every run
-// takes the same rows for its group.
-template <typename WT, int KS, bool GATEUP, bool REREAD = false>
+// takes the same rows for its group.  SHARED: blocks of this launch read what
+// others wrote.
+template <typename WT, int KS, bool GATEUP, bool REREAD = false, bool SHARED = false>
 __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const Tables& tb,
                                           const int32_t* slc, int nms, int lane, int wave) {
   const Tiles<WT, GATEUP> tl{a, arg, tb, slc, nms};
@@ -891,7 +911,7 @@ __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const T
     if (count > 0) tl.locate(lo, v, r);
   }
   if (count > 0)
-    stream<WT, KS, GATEUP, REREAD>(tl, v, r, step, count, a.lkw, s_dyn, lane, wave);
+    stream<WT, KS, GATEUP, REREAD, SHARED>(tl, v, r, step, count, a.lkw, s_dyn, lane, wave);
 }
 
 // Host side: a with the geometry of its pass.

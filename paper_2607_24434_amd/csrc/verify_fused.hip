@@ -7,6 +7,11 @@
 // combine sums in theirs' order, so the results are bit-identical to theirs.
 // The member tables stay in LDS from the gate/up pass to the down pass.
 //
+// What blocks hand on (A, the partials, the pairs' places) is stored and loaded at
+// agent scope, past the XCDs' own L2 caches.  (With a cache-wide write-back and
+// invalidation per block and point instead, a V2-Lite layer took 196 us at T = 2 and
+// 270 at T = 9; now 63 and 136, the separate launches 59 and 127.)
+//
 // A block arrives at a point by storing (launch epoch, point) to its word and
 // waits until no block's word is smaller.  The grid is one block per CU (each
 // takes more than half of a CU's LDS), and the host sends no such launch beside
@@ -27,7 +32,7 @@ constexpr unsigned kSpinLimit = 1u << 20;         // polls before a wait gives u
 constexpr int kVT = kCombThreads / kBlock;        // combine: virtual threads per thread
 
 __device__ __forceinline__ void grid_point(const FusedArgs& f, unsigned n, int* s_abort) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have completed
   __syncthreads();
   const uint64_t target = ((uint64_t)f.epoch << 32) | n;
   if (threadIdx.x == 0)
@@ -51,7 +56,12 @@ __device__ __forceinline__ void grid_point(const FusedArgs& f, unsigned n, int* 
     }
   }
   __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  asm volatile("" ::: "memory");
+}
+
+template <typename T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+  return __hip_atomic_load((const DE_GLOBAL T*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The combine of position t, its kCombThreads threads played by kBlock (thread
@@ -60,26 +70,54 @@ __device__ __forceinline__ void grid_point(const FusedArgs& f, unsigned n, int* 
 __device__ __forceinline__ void combine_position(const CombineArgs& a, int t, float* red) {
   const size_t rowoff = (size_t)t * a.H;
   float ss[kVT], v[kVT][kCombPer];
+  const auto element = [&](int j, int i) {
+    return (int)threadIdx.x + j * kBlock + i * kCombThreads;
+  };
+#pragma unroll
+  for (int j = 0; j < kVT; ++j)
+#pragma unroll
+    for (int i = 0; i < kCombPer; ++i) {
+      v[j][i] = 0.f;
+      if (element(j, i) >= a.H) continue;
+#pragma unroll
+      for (int s = 0; s < 3; ++s)
+        if (s < a.n_dense) v[j][i] += ld_agent(a.dense_p[s] + rowoff + element(j, i));
+    }
+  // Eight list entries' partials in flight at a time.
+  for (int q0 = 0; q0 < a.kk; q0 += 8) {
+    int pp[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      pp[q] = ld_agent(a.pair_pos + (size_t)t * a.kk + min(q0 + q, a.kk - 1));
+#pragma unroll
+    for (int j = 0; j < kVT; ++j)
+#pragma unroll
+      for (int i = 0; i < kCombPer; ++i) {
+        const int h = element(j, i);
+        if (h >= a.H) continue;
+        float p[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const bool ok = q0 + q < a.kk && pp[q] >= 0 && pp[q] < a.pairs_max;
+          p[q] = ok ? ld_agent(a.p_r + (size_t)pp[q] * a.H + h) : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const bool ok = q0 + q < a.kk && pp[q] >= 0 && pp[q] < a.pairs_max;
+          if (ok) v[j][i] += p[q];
+        }
+      }
+  }
 #pragma unroll
   for (int j = 0; j < kVT; ++j) {
     ss[j] = 0.f;
 #pragma unroll
     for (int i = 0; i < kCombPer; ++i) {
-      const int h = (int)threadIdx.x + j * kBlock + i * kCombThreads;
-      float x = 0.f;
-      if (h < a.H) {
-#pragma unroll
-        for (int s = 0; s < 3; ++s)
-          if (s < a.n_dense) x += a.dense_p[s][rowoff + h];
-        for (int q = 0; q < a.kk; ++q) {
-          const int p = a.pair_pos[(size_t)t * a.kk + q];
-          if (p >= 0 && p < a.pairs_max) x += a.p_r[(size_t)p * a.H + h];
-        }
-        if (a.residual) x = a.residual[rowoff + h] + x;
-        a.y[rowoff + h] = x;
-        ss[j] = fmaf(x, x, ss[j]);
-      }
-      v[j][i] = x;
+      const int h = element(j, i);
+      if (h >= a.H) continue;
+      if (a.residual) v[j][i] = a.residual[rowoff + h] + v[j][i];
+      a.y[rowoff + h] = v[j][i];
+      ss[j] = fmaf(v[j][i], v[j][i], ss[j]);
     }
   }
   if (a.normed == nullptr) return;
@@ -108,10 +146,12 @@ __global__ __launch_bounds__(kBlock, 2) void verify_fused_kernel(FusedArgs f) {
   __shared__ float s_red[kCombThreads / kWave];
   if (threadIdx.x == 0) s_abort = 0;
   const MfmaTables mt = mfma_tables<uint16_t, kFKS, true>(f.gu, lane, wave, &s_absent, &s_nms);
-  mfma_pass<uint16_t, kFKS, true>(f.gu, offsetof(FusedArgs, gu), mt.tb, mt.slc, mt.nms, lane, wave);
+  mfma_pass<uint16_t, kFKS, true, false, true>(f.gu, offsetof(FusedArgs, gu), mt.tb, mt.slc, mt.nms,
+                                               lane, wave);
   grid_point(f, 1, &s_abort);
-  if (s_absent) absent_rows_zero(f.dn, mt.tb, mt.nu);
-  mfma_pass<uint16_t, kFKS, false>(f.dn, offsetof(FusedArgs, dn), mt.tb, mt.slc, mt.nms, lane, wave);
+  if (s_absent) absent_rows_zero<true>(f.dn, mt.tb, mt.nu);
+  mfma_pass<uint16_t, kFKS, false, false, true>(f.dn, offsetof(FusedArgs, dn), mt.tb, mt.slc,
+                                                mt.nms, lane, wave);
   grid_point(f, 2, &s_abort);
   // Every block is past its work for the others: another stream's launch may follow.
   if (blockIdx.x == 0 && threadIdx.x == 0 && !*(volatile int*)&s_abort)
