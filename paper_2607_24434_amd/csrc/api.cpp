@@ -358,8 +358,7 @@ int mfma_chunks(int K, int rows, int T, int most) {
 // which it writes); else the caller's separate launches run, with the same bits.
 struct PDDevice {
   std::mutex mu;
-  bool asked = false;
-  uint32_t* done = nullptr;  // pinned host word; NULL: not available
+  uint32_t* done = nullptr;  // pinned host word; NULL: not allocated yet
   hipStream_t stream = nullptr;
   uint32_t epoch = 0;        // the last launch's; 0: none yet
 };
@@ -379,17 +378,21 @@ bool pd_may_launch(PDDevice& p, hipStream_t s) {
     (void)hipGetLastError();
     return false;
   }
-  if (!p.asked) {
-    p.asked = true;
+  if (p.done == nullptr) {
+    // (Another stream may be under capture, which forbids allocations and would be
+    // spoilt by one, except in the thread's relaxed mode.)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void* w = nullptr;
-    if (hipHostMalloc(&w, sizeof(uint32_t), hipHostMallocMapped) == hipSuccess) {
-      p.done = static_cast<uint32_t*>(w);
-      __atomic_store_n(p.done, 0u, __ATOMIC_RELAXED);
-    } else {
+    const hipError_t e = hipHostMalloc(&w, sizeof(uint32_t), hipHostMallocMapped);
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {  // the next call tries again
       (void)hipGetLastError();
+      return false;
     }
+    p.done = static_cast<uint32_t*>(w);
+    __atomic_store_n(p.done, 0u, __ATOMIC_RELAXED);
   }
-  if (p.done == nullptr) return false;
   if (p.epoch == 0 || __atomic_load_n(p.done, __ATOMIC_ACQUIRE) == p.epoch) return true;
   // (One handle stands for every thread's own stream.)
   return s == p.stream && s != hipStreamPerThread;

@@ -3,6 +3,10 @@ and Q4_0 expert weights, hidden sizes that do not fill the lanes, with and
 without shared and draft experts.  The separate launches (DE_PD_SINGLE=0) do
 the same fp32 operations in the same order, so every output is identical bit
 for bit.  Launches on two streams at once, and under stream capture."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -177,3 +181,53 @@ def test_blocks_without_rows_on_two_streams(dt, monkeypatch):
     for l, g, w in zip(layers, got, want):
         assert de.de_layer_status(l.ws) == 0
         assert all(same(o, w) for o in g)
+
+
+FIRST_CALL = """
+import sys
+sys.path.insert(0, "tests")
+import torch
+import paper_2607_24434_amd as de
+from test_gpu_draft_single_launch import SHAPES, Layer
+
+layer, out, s = Layer(SHAPES[0], 8), None, torch.cuda.Stream()
+out, ev = layer.outputs(), [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+a, b = torch.ones(8, device="cuda"), torch.zeros(8, device="cuda")
+b.copy_(a + a)
+graph = torch.cuda.CUDAGraph()
+
+
+def single():
+    # Ran as one launch: its phase timer brackets it (the events are else in
+    # reverse order).
+    ev[1].record(s)
+    ev[0].record(s)
+    de.de_time_next_phase(de.DE_PHASE_DRAFT_PASS, ev[0], ev[1])
+    layer.run(out, stream=s)
+
+
+torch.cuda.synchronize()
+with torch.cuda.graph(graph):
+    b.copy_(a)
+    single()
+torch.cuda.synchronize()
+assert ev[0].elapsed_time(ev[1]) > 0.002, "first call, another stream under capture"
+single()
+torch.cuda.synchronize()
+assert ev[0].elapsed_time(ev[1]) > 0.002, "second call"
+a.fill_(3.0)
+graph.replay()
+torch.cuda.synchronize()
+assert b.tolist() == [3.0] * 8 and de.de_layer_status(layer.ws) == 0
+print("ok")
+"""
+
+
+def test_first_call_while_another_stream_is_captured():
+    """A process's first single launch, while another stream is under capture: the
+    capture stays whole and the launch is not given up (a process of its own,
+    since what it needs is allocated once)."""
+    require_gpu()
+    r = subprocess.run([sys.executable, "-c", FIRST_CALL], capture_output=True, text=True,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
