@@ -222,8 +222,8 @@ int de_verify_layer(const de_moe_desc* d, int T, const float* x, const float* w_
  * the same kernels and results, with the layer's scratch taken from a
  * file-scope device array of de_noalloc_scratch_bytes() bytes (16 MiB) that
  * each GPU holds until the process ends, instead of a caller workspace.  The
- * call allocates nothing.  DE_ERR_WORKSPACE when de_workspace_bytes(d, T)
- * exceeds that size.  Every call on one GPU shares that GPU's array: calls
+ * call allocates nothing.  DE_ERR_WORKSPACE when the layer's scratch (at most
+ * de_workspace_bytes(d, T)) exceeds that size.  Every call on one GPU shares that GPU's array: calls
  * that overlap on one GPU (other streams, other host threads) race.  A needed
  * routed expert without a valid slot has its term dropped as in
  * de_verify_layer, but nothing reports it (use de_verify_layer and

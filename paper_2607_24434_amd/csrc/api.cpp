@@ -212,14 +212,19 @@ Layout layout(const de_moe_desc& d, int T) {
   L.p_r = take(tk * d.hidden * 4);
   L.p_s = take((size_t)kMaxSharedChunks * T * d.hidden * 4);
   L.p_d = take((size_t)T * d.hidden * 4);
-  // Room for the single launch's exchange (a (value, epoch) word for every value
-  // that its blocks hand on).  The launch hands them on through the plain
-  // buffers now; the room stays part of the workspace's size.
-  if (fused_shape(d, T))
-    take((tk * (d.inter + d.hidden) + (size_t)T * d.shared_inter +
-          (size_t)kMaxSharedChunks * T * d.hidden) * 8);
   L.total = o;
   return L;
+}
+
+// What de_workspace_bytes reports beyond what the calls use: room for a (value,
+// epoch) word for every value of a single-launch verify layer, which its blocks once
+// handed on in that form.  The size reported for these shapes stays what programs
+// have sized their memory by; no call asks for the room.
+size_t spare_bytes(const de_moe_desc& d, int T) {
+  if (!fused_shape(d, T)) return 0;
+  const size_t tk = (size_t)T * d.top_k;
+  return up256((tk * (d.inter + d.hidden) + (size_t)T * d.shared_inter +
+                (size_t)kMaxSharedChunks * T * d.hidden) * 8);
 }
 
 // Every launch that waits at device-wide points gets its own epoch (its arrival
@@ -575,6 +580,9 @@ namespace de {
 
 int32_t* layer_status_word(void* ws) { return at<int32_t>(ws, kStatusOff); }
 
+size_t layer_scratch_bytes(const de_moe_desc& d, int T) { return layout(d, T).total; }
+size_t layer_values_offset(const de_moe_desc& d, int T) { return layout(d, T).a_r; }
+
 // The LM head of a block of positions runs on the matrix cores unless
 // DE_LMHEAD_MFMA is "0" (the vector-ALU row-dot then runs; the two differ only
 // in the fp32 summation order).
@@ -796,7 +804,7 @@ int de_check_desc(const de_moe_desc* d) {
 
 size_t de_workspace_bytes(const de_moe_desc* d, int T) {
   if (de_check_desc(d) != DE_OK || check_T(T) != DE_OK) return 0;
-  return layout(*d, T).total;
+  return layout(*d, T).total + spare_bytes(*d, T);
 }
 
 int de_workspace_init(void* ws, size_t ws_bytes, hipStream_t stream) {

@@ -46,6 +46,8 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
                        const de_moe_desc* next_desc, void* next_ws, const float* next_router);
 bool combine_route_fits(int H);
 int32_t* layer_status_word(void* ws);
+size_t layer_scratch_bytes(const de_moe_desc& d, int T);
+size_t layer_values_offset(const de_moe_desc& d, int T);
 int take_status(int32_t* word, hipStream_t stream);
 PDLayer pd_layer(const de_layer_weights& w);
 int draft_persistent_run(const de_moe_desc& d, int n, const PDLayer* layers, const float* x_in,
@@ -92,11 +94,15 @@ ModelLayout model_layout(const de_model& m, int T) {
   const size_t H = (size_t)m.moe.hidden;
   L.accept_bytes = de_accept_workspace_bytes(kMaxBlock - 1, m.vocab);
   // At least the control area: its status word also serves the embedding.
-  L.layer_bytes = std::max<size_t>(de_workspace_bytes(&m.moe, T), 4096);
+  L.layer_bytes = std::max<size_t>(de::layer_scratch_bytes(m.moe, T), 4096);
   L.dense_bytes = m.dense_inter > 0 ? de_dense_workspace_bytes(T, (int)H, m.dense_inter) : 0;
   L.accept_ws = take(L.accept_bytes);
-  L.layer_ws = take(L.layer_bytes);
-  L.dense_ws = take(L.dense_bytes);
+  // The dense layer's scratch lies over the activations and partials of the MoE
+  // layers, which come after it (what it leaves for the first of them, its router
+  // logits, comes before those).
+  const size_t values = de::layer_values_offset(m.moe, T);
+  L.layer_ws = take(std::max(L.layer_bytes, values + L.dense_bytes));
+  L.dense_ws = L.layer_ws + values;
   L.misc = take(8);
   L.ridx = take((size_t)kMaxBlock * m.moe.top_k * 4);
   L.rgate = take((size_t)kMaxBlock * m.moe.top_k * 4);

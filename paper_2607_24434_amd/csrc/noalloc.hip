@@ -15,13 +15,13 @@ int verify_layer_chain(const de_moe_desc* d, int T, const float* x, const float*
                        int32_t* union_ids, int32_t* offsets, int32_t* tok_list, float* gate_list,
                        int32_t* pair_pos, const de_epilogue* epi, void* ws, size_t ws_bytes,
                        hipStream_t stream, bool logits_ready, const float* next_router);
+size_t layer_scratch_bytes(const de_moe_desc& d, int T);
 }  // namespace de
 
 namespace {
 
-// Largest layer scratch this entry point serves (de_workspace_bytes of the
-// call's shape and block length): the V2-Lite layer up to T = 64 needs about
-// 8.5 MB.
+// Largest layer scratch this entry point serves: the V2-Lite layer up to T = 64
+// needs about 8.5 MB.
 constexpr size_t kScratchBytes = 16u << 20;
 constexpr size_t kCtlBytes = 4096;  // the layer scratch's control area (counters, status, flags)
 
@@ -68,12 +68,11 @@ int de_verify_layer_noalloc(const de_moe_desc* d, int T, const float* x, const f
                             int32_t* union_ids, int32_t* offsets, int32_t* tok_list,
                             float* gate_list, int32_t* pair_pos, const de_epilogue* epi,
                             hipStream_t stream) {
-  const size_t need = de_workspace_bytes(d, T);
-  if (need == 0) {
+  if (de_workspace_bytes(d, T) == 0) {
     const int rc = de_check_desc(d);
     return rc != DE_OK ? rc : DE_ERR_INVALID;
   }
-  if (need > kScratchBytes) return DE_ERR_WORKSPACE;
+  if (de::layer_scratch_bytes(*d, T) > kScratchBytes) return DE_ERR_WORKSPACE;
   void* ws = device_scratch(stream);
   if (ws == nullptr) return DE_ERR_HIP;
   return de::verify_layer_chain(d, T, x, w_router, bias, routed, shared_w, y, topk_idx,
