@@ -268,8 +268,10 @@ int de_embed_gather(int T, int H, int V, const int32_t* tokens, const void* emb,
 
 /* Dense SwiGLU layer y = E(x) of intermediate I (layer 0 of the stack), with
  * the optional epilogue.  Scratch: de_dense_workspace_bytes(T, H, I).  The
- * down projection runs in up to three intermediate chunks whose partials are
- * summed in chunk order. */
+ * down projection runs in intermediate chunks whose partials are summed in
+ * chunk order: up to eight for bf16 weights with H <= 2048, else up to three.
+ * Scratch for three partials (up256(4 T I) + 3 up256(4 T H) bytes, up256 rounding
+ * up to a multiple of 256) serves too: the same results in more launches. */
 size_t de_dense_workspace_bytes(int T, int H, int I);
 int de_dense_swiglu(int T, int H, int I, int wdtype, const float* x, const void* w, float* y,
                     const de_epilogue* epi, void* ws, size_t ws_bytes, hipStream_t stream);

@@ -1204,12 +1204,10 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
   g.dense[0].w = w;
   g.dense[0].inter = I;
   g.dense[0].out = A;
-  // Down: D [H, I] in column chunks, each a dense source with its own partial.
+  // Down: D [H, I] in column chunks, each with its own partial.  (Their number
+  // follows from the shape alone, whatever the scratch holds: the same sums.)
   int nc = 0;
-  if (wdtype == DE_BF16 && H <= de::kMfmaMaxK) {
-    const size_t fit = (ws_bytes - up256((size_t)T * I * 4)) / up256((size_t)T * H * 4);
-    nc = mfma_chunks(I, H, T, (int)std::min<size_t>(fit, kMaxDenseChunks));
-  }
+  if (wdtype == DE_BF16 && H <= de::kMfmaMaxK) nc = mfma_chunks(I, H, T, kMaxDenseChunks);
   const bool mx = nc > 0;
   if (!mx) nc = dense_chunks(I, al);
   const int cw = (I / al + nc - 1) / nc * al;
@@ -1222,32 +1220,55 @@ int dense_swiglu_chain(int T, int H, int I, int wdtype, const float* x, const vo
     return DE_ERR_HIP;
   if (mx) g.lkw = de::mfma_lkw(wdtype, false, cw, nc * H);
   const char* D = static_cast<const char*>(w) + 2 * (size_t)I * H * elem_bytes(wdtype);
-  g.n_dense = mx ? 1 : nc;
-  for (int i = 0; i < g.n_dense; ++i) {
-    g.dense[i] = de::DenseSrc{};
-    g.dense[i].w = D + (size_t)i * cw * elem_bytes(wdtype);
-    g.dense[i].inter = mx ? I : cw;
-    g.dense[i].ld = I;
-    g.dense[i].rows = H;
-    g.dense[i].gate = 1.0f;
-    g.dense[i].vin = A + (size_t)i * cw;
-    g.dense[i].vin_stride = I;
-    g.dense[i].out = P + (size_t)i * pstride;
-    g.dense[i].out_stride = H;
-    g.dense[i].chunks = nc;
-    g.dense[i].cw = cw;
-    g.dense[i].chunk_out = (int)pstride;
-  }
-  if (timed_phase(DE_PHASE_DOWN, stream, [&] { return de::launch_down(g, wdtype, stream); }) !=
-      hipSuccess)
-    return DE_ERR_HIP;
+  // The `n` chunks from chunk c0 on, to the partials from `slot` on.
+  const auto down = [&](int c0, int n, int slot) {
+    g.n_dense = mx ? 1 : n;
+    for (int i = 0; i < g.n_dense; ++i) {
+      const int col = (c0 + i) * cw;
+      g.dense[i] = de::DenseSrc{};
+      g.dense[i].w = D + (size_t)col * elem_bytes(wdtype);
+      g.dense[i].inter = mx ? I - col : cw;
+      g.dense[i].ld = I;
+      g.dense[i].rows = H;
+      g.dense[i].gate = 1.0f;
+      g.dense[i].vin = A + (size_t)col;
+      g.dense[i].vin_stride = I;
+      g.dense[i].out = P + (size_t)(slot + i) * pstride;
+      g.dense[i].out_stride = H;
+      g.dense[i].chunks = n;
+      g.dense[i].cw = cw;
+      g.dense[i].chunk_out = (int)pstride;
+    }
+    return de::launch_down(g, wdtype, stream);
+  };
   de::CombineArgs c{};
   c.T = T;
   c.H = H;
-  c.n_dense = std::min(nc, 3);
-  for (int i = 0; i < c.n_dense; ++i) c.dense_p[i] = P + (size_t)i * pstride;
-  c.n_more = nc - c.n_dense;
   c.more_stride = (int)pstride;
+  const auto partials = [&](int n) {
+    c.n_dense = std::min(n, 3);
+    for (int i = 0; i < c.n_dense; ++i) c.dense_p[i] = P + (size_t)i * pstride;
+    c.n_more = n - c.n_dense;
+  };
+  // A scratch of three partials or more that does not hold all of them: the sum of
+  // the chunks so far is the first partial of the next group (the combine sums in
+  // chunk order, from zero, so the bits are those of one group).
+  const int fit = (int)std::min<size_t>(
+      (ws_bytes - up256((size_t)T * I * 4)) / up256((size_t)T * H * 4), (size_t)nc);
+  const hipError_t e = timed_phase(DE_PHASE_DOWN, stream, [&] {
+    hipError_t r = down(0, fit, 0);
+    partials(fit);
+    for (int c0 = fit; c0 < nc && r == hipSuccess;) {
+      c.y = P;
+      if ((r = de::launch_combine(c, stream)) != hipSuccess) break;
+      const int n = std::min(fit - 1, nc - c0);
+      r = down(c0, n, 1);
+      partials(n + 1);
+      c0 += n;
+    }
+    return r;
+  });
+  if (e != hipSuccess) return DE_ERR_HIP;
   c.y = y;
   c.residual = epi ? epi->residual : nullptr;
   c.normed = epi ? epi->normed : nullptr;

@@ -73,3 +73,31 @@ def test_noalloc_serves_what_its_scratch_holds():
     de.de_verify_layer_noalloc(d, T, x, router, None, tab, shared, y[1])
     torch.cuda.synchronize()
     assert torch.isfinite(y[0]).all() and torch.equal(y[0], y[1])
+
+
+@pytest.mark.parametrize("T,H,I", [(1, 8, 8), (9, 520, 10944), (17, 2048, 10944), (3, 64, 16384),
+                                   (2, 2056, 1000)])
+def test_dense_layer_with_three_partials(T, H, I):
+    """Scratch for three partials gives the bits of scratch for all of them."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(T + I)
+    x = torch.randn(T, H, generator=g, device="cuda")
+    w = (torch.randn(3 * I * H, generator=g, device="cuda") * 0.05).bfloat16()
+    least = up256(4 * T * I) + 3 * up256(4 * T * H)
+    full = de.de_dense_workspace_bytes(T, H, I)
+    assert full >= least
+    out = []
+    for n in (full, least, least + up256(4 * T * H)):
+        store = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        y, normed = torch.empty_like(x), torch.empty_like(x)
+        de.de_dense_swiglu(T, H, I, de.DE_BF16, x, w, y, store[:n],
+                           epi=de.make_epilogue(x, normed, 1e-6))
+        torch.cuda.synchronize()
+        assert (store[n:] == 0x5A).all()
+        out.append((y, normed))
+    assert torch.isfinite(out[0][0]).all()
+    for o in out[1:]:
+        assert torch.equal(o[0], out[0][0]) and torch.equal(o[1], out[0][1])
+    with pytest.raises(de.DEError) as e:
+        de.de_dense_swiglu(T, H, I, de.DE_BF16, x, w, y, store[:least - 256])
+    assert e.value.code == -4
