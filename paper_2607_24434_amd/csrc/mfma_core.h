@@ -557,17 +557,70 @@ __device__ __forceinline__ void put_partial(float* buf, const f32x4& acc, int f,
   }
 }
 
+// Output o of a tile (a thread's are threadIdx.x, + kBlock, ...: whole waves): its
+// position in the slice and its row.
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ bool output_at(const Slice& c, int rpt, int r, int o, int& rr, int& i,
+                                          int& rg, int& pos, int& row) {
+  constexpr int kG = GATEUP ? kFrags<WT> / 2 : kFrags<WT>;  // 16-row groups of a row group
+  // Row within 16, 16-row group, position, row group.
+  rr = o & 15;
+  i = (o >> 4) & (kG - 1);
+  pos = (o / (16 * kG)) & 15;
+  rg = o / (256 * kG);
+  row = frag_row<WT, GATEUP>(c, rpt, r, rg, i) + rr;
+  return pos < c.nt && row < c.rows;
+}
+template <typename WT, bool GATEUP>
+__device__ __forceinline__ int tile_outs(int lkw) {
+  return 256 * (GATEUP ? kFrags<WT> / 2 : kFrags<WT>) * (kWavesPB >> lkw);
+}
+
+template <bool GATEUP>
+__device__ __forceinline__ float output_value(const Slice& c, const Tables& tb, int pos, float s,
+                                              float u) {
+  if constexpr (GATEUP) return silu_f(s) * u;
+  return (c.goff >= 0 ? tb.gate[c.goff + pos] : c.gscalar) * s;
+}
+
+// The tile's outputs from the waves' sums (after the barrier).  SHARED: other
+// blocks of this launch read them.  nan is set where one is NaN.
+template <typename WT, bool GATEUP, bool SHARED>
+__device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
+                                             int lkw, const float* buf, bool& nan) {
+  const int kw = 1 << lkw;
+  constexpr int kWaveRed = kFrags<WT> * kRedTile;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // addresses are computed again for every tile
+#pragma unroll 1
+  for (int o = tid; o < tile_outs<WT, GATEUP>(lkw); o += kBlock) {
+    int rr, i, rg, pos, row;
+    if (output_at<WT, GATEUP>(c, rpt, r, o, rr, i, rg, pos, row)) {
+      const float* q = buf + (rg << lkw) * kWaveRed + (GATEUP ? 2 * i : i) * kRedTile +
+                       pos * kRedLd + rr;
+      float s = 0.f, u = 0.f;
+      for (int k = 0; k < kw; ++k) {
+        s += q[k * kWaveRed];
+        if constexpr (GATEUP) u += q[k * kWaveRed + kRedTile];
+      }
+      const float val = output_value<GATEUP>(c, tb, pos, s, u);
+      st_out<SHARED>(c.out + (size_t)(c.p0 + pos) * c.ostride + row, val);
+      nan = nan || !(val == val);
+    }
+  }
+}
+
 // A bf16 row's product with one position in fp32, by one wave, in the vector ALU
-// path's order: what a sum that came out NaN is taken from.  (An infinite weight
-// meets a zero mid or lo part of nearly every finite activation, and that product
-// is NaN on the matrix cores.)  Every lane gets the sum.
+// path's order.  Every lane gets the sum, and whether the position itself holds a
+// NaN.
 template <bool SHARED>
 __device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int pos, int row,
-                                           int64_t to, int lane) {
+                                           int64_t to, int lane, bool& xnan) {
   const int p = c.listed ? tb.tok[c.p0 + pos] : c.p0 + pos;
   const float* x = c.act + (size_t)p * c.astride;
   const char* w = c.w + (size_t)row * c.rb + to;
   float s = 0.f;
+  bool nan = false;
 #pragma unroll 1
   for (int u = lane; u < c.K / 8; u += kWave) {
     float v[8];
@@ -577,72 +630,53 @@ __device__ __forceinline__ float plain_dot(const Slice& c, const Tables& tb, int
     for (int i = 0; i < 4; ++i) s = fmaf(v[i], __uint_as_float(x0[i]), s);
 #pragma unroll
     for (int i = 0; i < 4; ++i) s = fmaf(v[4 + i], __uint_as_float(x1[i]), s);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      nan = nan || (x0[i] & 0x7fffffffu) > 0x7f800000u || (x1[i] & 0x7fffffffu) > 0x7f800000u;
   }
+  xnan = __builtin_amdgcn_ballot_w64(nan) != 0ull;
   return row_total(s);
 }
 
-// The tile's outputs from the waves' sums (after the barrier).  With PLAIN a sum
-// that is NaN is taken from plain_dot.  True when the thread met one.  SHARED:
-// other blocks of this launch read them (and the down pass's activations come from
-// other blocks).
-template <typename WT, bool GATEUP, bool SHARED, bool PLAIN>
-__device__ __forceinline__ bool write_outputs(const Slice& c, const Tables& tb, int rpt, int r,
-                                              int lkw, const float* buf) {
-  const int kw = 1 << lkw, nrw = kWavesPB >> lkw;
-  constexpr int kG = GATEUP ? kFrags<WT> / 2 : kFrags<WT>;  // 16-row groups of a row group
-  constexpr int kWaveRed = kFrags<WT> * kRedTile;
-  bool met = false;
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // addresses are computed again for every tile
+// Takes the wave's outputs that are NaN among the block's tiles (as in stream)
+// from plain products: an infinite weight meets a zero mid or lo part of nearly
+// every finite activation, and that product is NaN on the matrix cores.  After the
+// tiles, so that the loop over them only notes a NaN (0.2%; with the products in
+// the loop 1%).
+template <typename WT, bool GATEUP, bool SHARED, class TL>
+__device__ __forceinline__ void plain_outputs(const TL& tl, int v, int r, int step, int count,
+                                              int lkw, int lane) {
+  const int rpt = tl.a.geo.rpt;
+  Slice c = tl.slice(v);
 #pragma unroll 1
-  for (int o = tid; o < 256 * kG * nrw; o += kBlock) {  // (whole waves)
-    // Row within 16, 16-row group, position, row group.
-    const int rr = o & 15, i = (o >> 4) & (kG - 1), pos = (o / (16 * kG)) & 15, rg = o / (256 * kG);
-    const int row = frag_row<WT, GATEUP>(c, rpt, r, rg, i) + rr;
-    const bool mine = pos < c.nt && row < c.rows;
-    float s = 0.f, u = 0.f;
-    if (mine) {
-      const float* q = buf + (rg << lkw) * kWaveRed + (GATEUP ? 2 * i : i) * kRedTile +
-                       pos * kRedLd + rr;
-      for (int k = 0; k < kw; ++k) {
-        s += q[k * kWaveRed];
-        if constexpr (GATEUP) u += q[k * kWaveRed + kRedTile];
-      }
-      met = met || !(s == s) || !(u == u);
-    }
-    if constexpr (PLAIN) {
-      unsigned long long bad = __builtin_amdgcn_ballot_w64(!(s == s) || !(u == u));
+  for (; count > 0; --count) {
 #pragma unroll 1
-      for (; bad != 0ull; bad &= bad - 1) {
-        const int l = (int)__builtin_ctzll(bad), lane = tid & 63;
-        const int p = __builtin_amdgcn_readlane(pos, l), w = __builtin_amdgcn_readlane(row, l);
-        const float ds = plain_dot<SHARED && !GATEUP>(c, tb, p, w, 0, lane);
-        if (lane == l && !(s == s)) s = ds;
-        if constexpr (GATEUP) {
-          const float du = plain_dot<false>(c, tb, p, w, c.w2, lane);
-          if (lane == l && !(u == u)) u = du;
+    for (int o = threadIdx.x; o < tile_outs<WT, GATEUP>(lkw); o += kBlock) {
+      int rr, i, rg, pos, row;
+      const bool mine = output_at<WT, GATEUP>(c, rpt, r, o, rr, i, rg, pos, row);
+      float* const p = c.out + (size_t)(c.p0 + pos) * c.ostride + row;
+      float val = 0.f;
+      if (mine) val = *(DE_GLOBAL float*)p;  // (its own store)
+      unsigned long long bad = __builtin_amdgcn_ballot_w64(!(val == val));
+      while (bad != 0ull) {
+        const int l = (int)__builtin_ctzll(bad);
+        const int lp = __builtin_amdgcn_readlane(pos, l), lr = __builtin_amdgcn_readlane(row, l);
+        bad &= bad - 1;
+        bool xnan;
+        const float s = plain_dot<SHARED && !GATEUP>(c, tl.tb, lp, lr, 0, lane, xnan);
+        if (xnan) {  // all outputs of the position are NaN, whatever the weights
+          bad &= ~__builtin_amdgcn_ballot_w64(pos == lp);
+          continue;
         }
+        float u = 0.f;
+        if constexpr (GATEUP) u = plain_dot<false>(c, tl.tb, lp, lr, c.w2, lane, xnan);
+        if (lane == l) st_out<SHARED>(p, output_value<GATEUP>(c, tl.tb, pos, s, u));
       }
     }
-    if (mine) {
-      float val;
-      if constexpr (GATEUP)
-        val = silu_f(s) * u;
-      else
-        val = (c.goff >= 0 ? tb.gate[c.goff + pos] : c.gscalar) * s;
-      st_out<SHARED>(c.out + (size_t)(c.p0 + pos) * c.ostride + row, val);
+    if (++r >= c.tiles && count > 1) {
+      r = 0;
+      c = tl.slice(v += step);
     }
-  }
-  return met;
-}
-
-template <typename WT, bool GATEUP, bool SHARED>
-__device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
-                                             int lkw, const float* buf) {
-  const bool met = write_outputs<WT, GATEUP, SHARED, false>(c, tb, rpt, r, lkw, buf);
-  if constexpr (!kQ4<WT>) {
-    if (__builtin_amdgcn_ballot_w64(met) != 0ull)
-      write_outputs<WT, GATEUP, SHARED, true>(c, tb, rpt, r, lkw, buf);
   }
 }
 
@@ -757,6 +791,8 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
 template <typename WT, int KS, bool GATEUP, bool REREAD, bool SHARED>
 __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r, int step,
                                        int count, int lkw, float* red, int lane, int wave) {
+  const int v0 = v, r0 = r;
+  bool nan = false;
   const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.a.geo.rpt;
   Slice c = tl.slice(v);
   Lanes<WT, KS> L = lanes_of<WT, KS>(c, tl.tb, ks, lkw, lane);
@@ -784,7 +820,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
     if (!more || fresh) nr = more ? 0 : r;
     tile<WT, KS, GATEUP, REREAD>(R, c, L, r, nc, N, nr, more ? ~0u : 0u, rpt, rw, st, buf, wave, lane);
     lds_barrier();
-    tile_outputs<WT, GATEUP, SHARED>(c, tl.tb, rpt, r, lkw, buf);
+    tile_outputs<WT, GATEUP, SHARED>(c, tl.tb, rpt, r, lkw, buf, nan);
     buf = buf == red ? red + kRedBuf<WT> : red;
     // A later slice's are used at once: left in flight into the next tile,
     // where they may or may not be, they would make every tile wait for all
@@ -800,6 +836,10 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
     c = nc;
     L = N;
     r = nr;
+  }
+  if constexpr (!kQ4<WT>) {
+    if (__builtin_amdgcn_ballot_w64(nan) != 0ull)
+      plain_outputs<WT, GATEUP, SHARED>(tl, v0, r0, step, count, lkw, lane);
   }
 }
 

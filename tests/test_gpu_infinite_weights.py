@@ -116,3 +116,22 @@ def test_infinite_logit_wins_the_acceptance():
     drafts = torch.tensor([4321, 4321], dtype=torch.int32, device="cuda")
     de.de_accept_len(T - 1, V, logits, drafts, amax, out, de.accept_workspace(T - 1, V))
     assert amax.tolist() == [4321] * T and out.tolist() == [2, 4321]
+
+
+@pytest.mark.parametrize("T,H,V", [(3, 264, 5000), (18, 2048, 4099)])
+def test_a_position_with_a_nan_beside_infinite_weights(T, H, V):
+    """A NaN activation makes all outputs of its position NaN, and no others."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randint(1, 9, (T, H), generator=g, device="cuda").float()
+    w = torch.randint(-8, 9, (V, H), generator=g, device="cuda").bfloat16()
+    w[9, 5], w[V - 1, 0] = INF, -INF
+    x[1, H - 1] = NAN
+    out = torch.empty(T, V, device="cuda")
+    de.de_lm_head(T, H, V, x, w, out)
+    clean = w.clone()
+    clean[[9, V - 1]] = 0
+    want = x.double() @ clean.double().t()
+    want[:, 9], want[:, V - 1], want[1] = INF, -INF, NAN
+    assert same_kind(out, want)
+    fin = want.isfinite()
+    assert torch.equal(out.double()[fin], want[fin])
