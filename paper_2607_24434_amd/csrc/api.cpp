@@ -1102,8 +1102,10 @@ int de_lm_head(int T, int H, int V, const float* x, const void* w_lm, float* log
                hipStream_t stream) {
   if (check_T(T) != DE_OK || H < 8 || H % 8 || V < 1 || !x || !w_lm || !logits) return DE_ERR_INVALID;
   if (!aligned16(x) || !aligned16(w_lm)) return DE_ERR_INVALID;
-  // A block of positions on the matrix cores (the vector-ALU row-dot is
-  // arithmetic-bound there); one position streams at the HBM rate already.
+  // On the matrix cores wherever a row's columns fit the waves' registers (102400
+  // rows of 2048, us against the row-dot: T = 1 67 and 74, T = 4 69 and 77; 8192
+  // rows 11 and 14).  Wider rows: 5 to 12 positions in a kernel that keeps their
+  // parts in LDS, else the row-dot.
   const bool mx = H <= de::kMfmaMaxK && de::lmhead_mfma_enabled();
   if (!mx && de::rowdot_mfma_fits(T, H) && de::lmhead_mfma_enabled())
     return hip_status(de::launch_rowdot_mfma(T, H, V, x, w_lm, logits, stream));

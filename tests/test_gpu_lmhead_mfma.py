@@ -6,8 +6,10 @@ The matrix-core path splits each fp32 activation exactly into three bf16 parts,
 so every product is exact; only the fp32 summation order differs from the
 row-dot.  Integer-valued weights and activations make every partial sum exact,
 so there both paths must match the exact dot product bit for bit: a wrong
-operand or output lane layout cannot pass that.  Blocks of 5 to 12 positions
-take the matrix cores; 1, 2 and 13 positions check the row-dot fallback.
+operand or output lane layout cannot pass that.  Rows of at most 2048 columns
+take the grouped passes' kernel at every block length; with DE_LMHEAD_MFMA=0 the
+row-dot runs.  (test_gpu_wide_rows.py has the wider rows, which take the kernel
+that keeps the parts in LDS, or the row-dot.)
 """
 import os
 
