@@ -421,8 +421,9 @@ constexpr int kXP = 16;
 // union, in every block; block 0 also publishes both for the down and combine
 // launches.  Fills the member table, the token and gate lists and (slc not
 // NULL) the resident members' slices of kXP positions, (member << 8) | group,
-// their number to *nms; returns the number of members.  All threads; ends
-// with a barrier.
+// their number to *nms; returns the number of members.  SHARED: other blocks of
+// this launch read the pairs' places.  All threads; ends with a barrier.
+template <bool SHARED = false>
 __device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& tb,
                                            float (&z0)[2][4], int lane, int wave, int* absent,
                                            int32_t* slc = nullptr, int* nms = nullptr) {
@@ -541,8 +542,10 @@ __device__ __forceinline__ int route_lists(const GroupedArgs& a, const Tables& t
     if (out) {
       a.sel.tok_list[p] = t;
       a.sel.gate_list[p] = g;
-      // (Read by other blocks of the single-launch verify layer.)
-      __hip_atomic_store(a.sel.pair_pos + i, p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if constexpr (SHARED)
+        __hip_atomic_store(a.sel.pair_pos + i, p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        a.sel.pair_pos[i] = p;
     }
   }
   if (out) {

@@ -587,7 +587,7 @@ __device__ __forceinline__ float output_value(const Slice& c, const Tables& tb, 
 // blocks of this launch read them.  nan is set where one is NaN.
 template <typename WT, bool GATEUP, bool SHARED>
 __device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, int rpt, int r,
-                                             int lkw, const float* buf, bool& nan) {
+                                             int lkw, const float* buf, int& nan) {
   const int kw = 1 << lkw;
   constexpr int kWaveRed = kFrags<WT> * kRedTile;
   int tid = threadIdx.x;
@@ -605,7 +605,7 @@ __device__ __forceinline__ void tile_outputs(const Slice& c, const Tables& tb, i
       }
       const float val = output_value<GATEUP>(c, tb, pos, s, u);
       st_out<SHARED>(c.out + (size_t)(c.p0 + pos) * c.ostride + row, val);
-      nan = nan || !(val == val);
+      nan |= val == val ? 0 : 1;
     }
   }
 }
@@ -787,12 +787,11 @@ __device__ __forceinline__ void tile(Regs<WT, KS>& R, const Slice& c, const Lane
 }
 
 // The block's `count` > 0 tiles from tile r of slice v (then of every step-th
-// slice after it).
+// slice after it).  True where the thread wrote a NaN.
 template <typename WT, int KS, bool GATEUP, bool REREAD, bool SHARED>
-__device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r, int step,
+__device__ __forceinline__ bool stream(const Tiles<WT, GATEUP>& tl, int v, int r, int step,
                                        int count, int lkw, float* red, int lane, int wave) {
-  const int v0 = v, r0 = r;
-  bool nan = false;
+  int nan = 0;
   const int ks = wave & ((1 << lkw) - 1), rw = wave >> lkw, rpt = tl.a.geo.rpt;
   Slice c = tl.slice(v);
   Lanes<WT, KS> L = lanes_of<WT, KS>(c, tl.tb, ks, lkw, lane);
@@ -837,10 +836,7 @@ __device__ __forceinline__ void stream(const Tiles<WT, GATEUP>& tl, int v, int r
     L = N;
     r = nr;
   }
-  if constexpr (!kQ4<WT>) {
-    if (__builtin_amdgcn_ballot_w64(nan) != 0ull)
-      plain_outputs<WT, GATEUP, SHARED>(tl, v0, r0, step, count, lkw, lane);
-  }
+  return nan != 0;
 }
 
 // Room for the member slices: lists that share no entry need no more.
@@ -884,7 +880,7 @@ struct MfmaTables {
 // The block's tables: the lists (selected and united here in a gate/up launch
 // with fused routing, else read), the members and their slices.  absent and
 // nms are shared words.  Ends with a barrier.
-template <typename WT, int KS, bool GATEUP>
+template <typename WT, int KS, bool GATEUP, bool SHARED = false>
 __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane, int wave,
                                                   int* absent, int* nms) {
   MfmaTables mt;
@@ -899,7 +895,7 @@ __device__ __forceinline__ MfmaTables mfma_tables(const GroupedArgs& a, int lane
     float z0[2][4];
     first_logits(a, wave, z0);
     // (route_lists starts with a barrier: absent is initialised.)
-    mt.nu = uni(route_lists(a, mt.tb, z0, lane, wave, absent, slc, nms));
+    mt.nu = uni(route_lists<SHARED>(a, mt.tb, z0, lane, wave, absent, slc, nms));
   } else if (a.has_routed) {
     __syncthreads();
     mt.nu = uni(fill_tables(a, mt.tb, absent));
@@ -938,20 +934,31 @@ template <typename WT, int KS, bool GATEUP, bool REREAD = false, bool SHARED = f
 __device__ __forceinline__ void mfma_pass(const GroupedArgs& a, int arg, const Tables& tb,
                                           const int32_t* slc, int nms, int lane, int wave) {
   const Tiles<WT, GATEUP> tl{a, arg, tb, slc, nms};
-  int count, v, r, step = 1;
-  if constexpr (REREAD) {
-    const int G = a.geo.groups, run = gridDim.x / G, g = uni((int)blockIdx.x / run);
-    const int lo = share(a.geo.ndt / G, blockIdx.x - g * run, run, count);
-    const int chunk = uni(lo / a.geo.tiles[0]);
-    v = chunk * G + g;
-    r = lo - chunk * a.geo.tiles[0];
-    step = G;
-  } else {
-    const int lo = share(tl.total(), blockIdx.x, gridDim.x, count);
-    if (count > 0) tl.locate(lo, v, r);
+  const auto start = [&](int block, int& v, int& r, int& step, int& count) {
+    step = 1;
+    if constexpr (REREAD) {
+      const int G = a.geo.groups, run = gridDim.x / G, g = uni(block / run);
+      const int lo = share(a.geo.ndt / G, block - g * run, run, count);
+      const int chunk = uni(lo / a.geo.tiles[0]);
+      v = chunk * G + g;
+      r = lo - chunk * a.geo.tiles[0];
+      step = G;
+    } else {
+      const int lo = share(tl.total(), block, gridDim.x, count);
+      if (count > 0) tl.locate(lo, v, r);
+    }
+  };
+  int v, r, step, count, block = blockIdx.x;
+  start(block, v, r, step, count);
+  if (count <= 0) return;
+  const bool nan =
+      stream<WT, KS, GATEUP, REREAD, SHARED>(tl, v, r, step, count, a.lkw, s_dyn, lane, wave);
+  if constexpr (!kQ4<WT>) {
+    if (__builtin_amdgcn_ballot_w64(nan) == 0ull) return;
+    asm volatile("" : "+s"(block));  // computed again, not kept through the tiles
+    start(block, v, r, step, count);
+    plain_outputs<WT, GATEUP, SHARED>(tl, v, r, step, count, a.lkw, lane);
   }
-  if (count > 0)
-    stream<WT, KS, GATEUP, REREAD, SHARED>(tl, v, r, step, count, a.lkw, s_dyn, lane, wave);
 }
 
 // Host side: a with the geometry of its pass.

@@ -145,7 +145,8 @@ __global__ __launch_bounds__(kBlock, 2) void verify_fused_kernel(FusedArgs f) {
   __shared__ int s_abort, s_absent, s_nms;
   __shared__ float s_red[kCombThreads / kWave];
   if (threadIdx.x == 0) s_abort = 0;
-  const MfmaTables mt = mfma_tables<uint16_t, kFKS, true>(f.gu, lane, wave, &s_absent, &s_nms);
+  const MfmaTables mt =
+      mfma_tables<uint16_t, kFKS, true, true>(f.gu, lane, wave, &s_absent, &s_nms);
   mfma_pass<uint16_t, kFKS, true, false, true>(f.gu, offsetof(FusedArgs, gu), mt.tb, mt.slc, mt.nms,
                                                lane, wave);
   grid_point(f, 1, &s_abort);
