@@ -171,8 +171,8 @@ constexpr size_t kStatusOff = 256;
 // The single-launch verify layer's arrival flags: at an offset that does not
 // depend on the block length, which no other call writes (a call with
 // another block length lays its buffers out differently).
-constexpr size_t kPDFlagsOff = 1024;
-static_assert(kPDFlagsOff + (de::kPDMaxGrid + 32) * 8 <= kCtlBytes, "control area");
+constexpr size_t kFusedFlagsOff = 1024;
+static_assert(kFusedFlagsOff + (de::kPDMaxGrid + 32) * 8 <= kCtlBytes, "control area");
 
 
 struct Layout {
@@ -546,7 +546,7 @@ int run_grouped(const de_moe_desc& d, int T, const float* x, const de::RoutedSrc
   if (fused) {
     f.dn = g;
     f.c = c;
-    f.flags = at<uint64_t>(ws, kPDFlagsOff);
+    f.flags = at<uint64_t>(ws, kFusedFlagsOff);
     f.epoch = next_epoch();
     f.status = r.status;
     f.done = dev->done;

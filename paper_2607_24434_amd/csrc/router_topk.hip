@@ -26,7 +26,6 @@ constexpr int kMaxN = 256;
 // N <= 256).
 struct SelShared {
   int32_t idx[kMaxT * kMaxK];
-  float sc[kMaxT * kMaxK];
   float gate[kMaxT * kMaxK];
   unsigned long long mask[kMaxN];
   int32_t off[kMaxN];
@@ -35,7 +34,7 @@ struct SelShared {
 };
 
 __device__ inline SelView view_of(SelShared& s) {
-  return SelView{s.idx, s.sc, s.gate, s.mask, s.off, s.upos, s.misc};
+  return SelView{s.idx, s.gate, s.mask, s.off, s.upos, s.misc};
 }
 
 // Block (t, g) (see the index map below): router logits of position t
@@ -94,7 +93,7 @@ __global__ __launch_bounds__(kSelThreads) void union_kernel(TopkUnionArgs a) {
     sel.gate[i] = a.gate_in[i];
   }
   __syncthreads();
-  build_union(a, v, true, nullptr, nullptr);
+  build_union(a, v);
 }
 
 }  // namespace

@@ -24,10 +24,9 @@
 
 namespace de {
 
-// LDS arrays of the selection and union (sizes: T*k, T*k, T*k, N, N, N, 4).
+// LDS arrays of the selection and union (sizes: T*k, T*k, N, N, N, 4).
 struct SelView {
   int32_t* idx;              // ordered top-k ids [T, k]
-  float* sc;                 // their scores
   float* gate;               // their gates
   unsigned long long* mask;  // position mask per expert [N]
   int32_t* off;              // list offset per expert
@@ -37,16 +36,15 @@ struct SelView {
 
 __host__ __device__ inline size_t sel_view_bytes(int T, int k, int N) {
   const size_t tk = (size_t)T * k;
-  return ((tk * 12 + 7) & ~(size_t)7) + (size_t)N * 16 + 16;
+  return tk * 8 + (size_t)N * 16 + 16;
 }
 
 __device__ inline SelView sel_view_at(char* p, int T, int k, int N) {
   SelView v;
   const size_t tk = (size_t)T * k;
   v.idx = reinterpret_cast<int32_t*>(p);
-  v.sc = reinterpret_cast<float*>(v.idx + tk);
-  v.gate = v.sc + tk;
-  p += (tk * 12 + 7) & ~(size_t)7;
+  v.gate = reinterpret_cast<float*>(v.idx + tk);
+  p += tk * 8;
   v.mask = reinterpret_cast<unsigned long long*>(p);
   v.off = reinterpret_cast<int32_t*>(v.mask + N);
   v.upos = v.off + N;
@@ -231,12 +229,10 @@ __device__ __forceinline__ float topk_gate(const TopkUnionArgs& a, float sv) {
 
 // Union of the first a.ucols entries of every position's list in s.idx /
 // s.gate.  s.misc[1] receives n_union (-1 for an id outside [0, N) or an id
-// that repeats within a position) and s.misc[2] the number of pairs.  With
-// write_out the lists go to a.n_union / union_ids / offsets / tok_list /
-// gate_list / pair_pos; with ptok / pgate the per-pair positions and gates
-// also go to LDS.  All threads of the block; ends with a barrier.
-__device__ inline void build_union(const TopkUnionArgs& a, const SelView& s, bool write_out,
-                                   int32_t* ptok, float* pgate) {
+// that repeats within a position) and s.misc[2] the number of pairs; the lists go
+// to a.n_union / union_ids / offsets / tok_list / gate_list / pair_pos.  All
+// threads of the block; ends with a barrier.
+__device__ inline void build_union(const TopkUnionArgs& a, const SelView& s) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nthreads = blockDim.x;
   const int T = a.T, N = a.N, k = a.k, uc = a.ucols;
@@ -259,7 +255,7 @@ __device__ inline void build_union(const TopkUnionArgs& a, const SelView& s, boo
     if (tid == 0) {
       s.misc[1] = -1;
       s.misc[2] = 0;
-      if (write_out) *a.n_union = -1;
+      *a.n_union = -1;
     }
     __syncthreads();
     return;
@@ -304,32 +300,23 @@ __device__ inline void build_union(const TopkUnionArgs& a, const SelView& s, boo
   }
   __syncthreads();
   const int nu = s.misc[1], total = s.misc[2];
-  if (write_out) {
-    for (int e = tid; e < N; e += nthreads) {
-      if (s.mask[e] != 0ull) {
-        a.union_ids[s.upos[e]] = e;
-        a.offsets[s.upos[e]] = s.off[e];
-      }
+  for (int e = tid; e < N; e += nthreads) {
+    if (s.mask[e] != 0ull) {
+      a.union_ids[s.upos[e]] = e;
+      a.offsets[s.upos[e]] = s.off[e];
     }
-    for (int u = nu + tid; u < N; u += nthreads) a.union_ids[u] = -1;
-    for (int u = nu + tid; u <= N; u += nthreads) a.offsets[u] = total;
-    if (tid == 0) *a.n_union = nu;
   }
+  for (int u = nu + tid; u < N; u += nthreads) a.union_ids[u] = -1;
+  for (int u = nu + tid; u <= N; u += nthreads) a.offsets[u] = total;
+  if (tid == 0) *a.n_union = nu;
   for (int i = tid; i < T * uc; i += nthreads) {
     const int t = i / uc, j = i - t * uc;
     const int e = s.idx[t * k + j];
     const unsigned long long below = t == 0 ? 0ull : (s.mask[e] & (~0ull >> (64 - t)));
     const int p = s.off[e] + __popcll(below);
-    const float g = s.gate[t * k + j];
-    if (write_out) {
-      a.tok_list[p] = t;
-      a.gate_list[p] = g;
-      a.pair_pos[i] = p;
-    }
-    if (ptok != nullptr) {
-      ptok[p] = t;
-      pgate[p] = g;
-    }
+    a.tok_list[p] = t;
+    a.gate_list[p] = s.gate[t * k + j];
+    a.pair_pos[i] = p;
   }
   __syncthreads();
 }

@@ -64,7 +64,7 @@ def inputs(T, H, N, I, Is, seed):
 @pytest.mark.parametrize("T,H,N,k,I,Is", [
     (2, 8, 4, 2, 8, 8), (16, 72, 5, 3, 24, 40), (17, 264, 6, 6, 136, 0), (5, 520, 8, 2, 16, 296),
     (33, 1000, 3, 2, 72, 144), (64, 512, 4, 4, 128, 256), (9, 2048, 16, 6, 1408, 2816),
-    (32, 2048, 4, 1, 40, 2048 + 1032)])
+    (32, 2048, 4, 1, 40, 2048 + 1032), (64, 2048, 256, 32, 16, 0)])
 @pytest.mark.parametrize("kind", ["verify", "draft"])
 def test_layer_matches_the_vector_alu_path(T, H, N, k, I, Is, kind):
     x, w, router = inputs(T, H, N, I, Is, T + H)
