@@ -40,14 +40,15 @@ PEAK_HBM_GBS = 8000.0
 # factors in profiles/verify_layer_v2lite_T9.md).  Valid only for the kernel
 # sources they were measured on: reported as null once those change.
 PMC_TRAFFIC = {
-    "bytes_per_launch": 463.53e6,
-    "vs_algorithmic": 1.004,
+    "bytes_per_launch": 462.93e6,
+    "vs_algorithmic": 1.002,
     "union_mean": 38.0,
-    "sources": ["paper_2607_24434_amd/csrc/grouped_swiglu.hip",
+    "sources": ["paper_2607_24434_amd/csrc/grouped_mfma.hip",
+                "paper_2607_24434_amd/csrc/mfma_core.h",
                 "paper_2607_24434_amd/csrc/grouped_core.h",
                 "paper_2607_24434_amd/csrc/topk_union.h",
                 "paper_2607_24434_amd/csrc/de_common.h"],
-    "sha256": "87cb95446bf41797167802e6d934f5cf9c65f6a9e217c7886e25d26cd1eb4193",
+    "sha256": "4a63b0868ac66dbf177a747edb292bc1e2af4c22b04980ba47d6a667c248c3df",
 }
 
 
@@ -294,7 +295,7 @@ def main():
         "wall_s_timed": round(wall, 4),
         "hbm_read_ceiling_gbs": None if probe_gbs is None else round(probe_gbs, 1),
         "roofline": {
-            "kernel": "gateup_kernel (verify layer)",
+            "kernel": "grouped_mfma_kernel, gate/up (verify layer)",
             "bound": "hbm",
             "achieved": round(gu_gbs, 1),
             "peak": PEAK_HBM_GBS,

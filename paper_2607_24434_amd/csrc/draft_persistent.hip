@@ -30,7 +30,7 @@
 // bf16 and Q4_0 blocks; a hidden size of 512 to 2048 whose rows are whole
 // 16-byte units (lanes past a row's end add zeros).  A Q4_0 layer is 19.5 MB
 // and bound by the chain of latencies above: six V2-Lite layer calls 190 us
-// on four launches each, 128 in one each (bf16, 415 MB: 141).
+// on four launches each, 124 in one each (bf16, 415 MB: 139).
 //
 // The arithmetic is the one of the separate launches, operation for
 // operation (lane l owns the 16-byte weight units l, l + 64, ...; fp32 FMAs in
@@ -48,7 +48,9 @@
 // for the last layer's rows; and a wave that polls asks for no weights first
 // where it can.  In-kernel clock of a V2-Lite layer call: last rows written to
 // seen 4.2 us with every block polling, 1.2 with one.  Six calls 165 -> 141 us
-// (Q4_0 153 -> 128), a token through a four-layer stack and its head 204 -> 197.
+// (Q4_0 153 -> 128), a token through a four-layer stack and its head 204 -> 197;
+// with the words at fixed addresses of the device instead of a workspace's 139 (124)
+// and 195.
 // Every wait is bounded: a wait that runs out records kStatusSyncTimeout in the
 // status word, and every later wait of the block returns at once, so the launch
 // always ends.

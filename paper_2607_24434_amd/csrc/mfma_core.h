@@ -35,20 +35,21 @@
 // one fragment per wave (64 KB in flight per CU; two measured no faster) and
 // each is refilled from the next fragment as soon as it is stored, across
 // tiles and experts.  A block owns a contiguous range of the launch's tiles
-// and meets one or two experts.  In the steady state a bf16 gate/up tile
-// (128 KB) takes 4.5 us, 7.4 TB/s over the chip.
+// and meets one or two experts.  The bf16 gate/up launch of a V2-Lite layer at
+// T = 9 streams 460 MB in 79 us, 5.8 TB/s with its prologue and its tail (a linear
+// read of 4 GiB on the same card: 6.0).
 //
 // Q4_0: a fragment is a quarter of the bytes, so a tile is four fragments and
 // all four are in flight.  The codes become bf16 operands with one conversion
 // per two (the vector ALU needed one conversion and one FMA per weight and
-// position); V2-Lite layer at T = 9: gate/up 41 us (vector ALU 63), down 30
+// position); V2-Lite layer at T = 9: gate/up 42 us (vector ALU 63), down 30
 // (51), bound by the latency of a fragment's way through LDS, conversion and
 // matrix cores.
 //
-// Measured (rocprofv3, V2-Lite layer): T = 9 gate/up 82 us (vector ALU 88),
-// down 42 (47); T = 17 99 (131) and 50 (80); T = 64 163 (554) and 79 (248);
-// dense layer of 10944 at T = 9 21 and 15 (78 us with the combine before, 41
-// now); LM head of 102400 at T = 9 72 (101).
+// Measured (rocprofv3): V2-Lite layer T = 9 gate/up 79 us (vector ALU 88), down
+// 44 (47); T = 64 142 (554) and 82 (248); Moonlight layer T = 17 87 and 51; dense
+// layer of 10944 at T = 9 19 and 13 (78 us with the combine before, 39 now); LM head
+// of 102400 at T = 9 72 (101).
 //
 // More than 16 positions are several slices of 16 over the same rows.  Where
 // a launch has one dense source (a dense layer, the LM head) the blocks that

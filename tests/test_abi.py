@@ -75,13 +75,13 @@ def test_workspace_bytes():
     sizes = [de.de_workspace_bytes(d, T) for T in (1, 5, 9, 17, 64)]
     assert all(s > 0 for s in sizes)
     # Larger blocks need more, within the lengths the single launch serves
-    # (T = 2..14 at this shape) and beyond them.
+    # (T = 2..9) and beyond them.
     assert sizes[1] < sizes[2] and sizes[3] < sizes[4] and sizes[0] < sizes[3]
     assert de.de_workspace_bytes(d, 0) == 0 and de.de_workspace_bytes(d, 65) == 0
     assert de.de_workspace_bytes(cfg2_desc(n_experts=0), 9) == 0
     # A_r + P_r + shared/draft activations dominate: T*k*(I+H)*4 + T*(Is+Id+2H)*4,
-    # and for the single launch their (value, epoch) words: T*k*(I+H)*8 + T*Is*8
-    # + 3*T*H*8.
+    # and room of a (value, epoch) word for each value of the single launch, which
+    # stays part of the reported size: T*k*(I+H)*8 + T*Is*8 + 3*T*H*8.
     plain = 9 * 6 * (1408 + 2048) * 4 + 9 * (2816 + 1408 + 2 * 2048) * 4
     tagged = 9 * 6 * (1408 + 2048) * 8 + 9 * 2816 * 8 + 3 * 9 * 2048 * 8
     assert sizes[2] >= plain + tagged

@@ -1,16 +1,16 @@
 """The verify layer as one launch, on the GPU.
 
 de_verify_layer runs the layer of a bf16 block of 2..9 positions (V2-Lite
-and Moonlight shapes) as one launch whose blocks exchange the gate/up outputs
-and the down partials as (value, launch epoch) words.  Every value is computed
-by the same operations as in the separate launches, so each output must equal
+and Moonlight shapes) as one launch with two device-wide points, whose blocks
+hand on the gate/up outputs and the down partials past their caches.  Every value
+is computed by the same operations as in the separate launches, so each output must equal
 theirs bit for bit (DE_VERIFY_FUSED=1 selects the single launch, which is
 off by default, and 0 the separate launches); the
 oracle comparisons of the layer (test_gpu_layer.py) cover both paths at their
 shapes.  Covered here: the block lengths the launch serves at its edges, long
-runs of calls on one workspace (every call must see only its own words),
-alternating block lengths, the epilogue, a needed expert without a slot and
-the phase timer.
+runs of calls on one workspace (every call must wait for its own arrivals),
+alternating block lengths, the epilogue, a needed expert without a slot, the
+phase timer, calls on several streams at once and under capture.
 """
 import os
 
@@ -105,8 +105,8 @@ def test_off_by_default():
 
 
 def test_block_lengths_served():
-    """The single launch serves the V2-Lite layer at T = 2..9 (the staged
-    rows of a sweep fit a CU's LDS); other lengths use the separate launches."""
+    """The single launch serves the V2-Lite layer at T = 2..9; other lengths use
+    the separate launches."""
     _, dev = layer_pair(configs.CFG2)
     served = [T for T in range(1, 65) if de.de_verify_single_launch(dev.desc, T)]
     assert served == list(range(2, 10))
