@@ -5,6 +5,7 @@
 #include "de_common.h"
 
 #include <climits>
+#include <type_traits>
 
 namespace de {
 namespace {
@@ -28,10 +29,13 @@ __global__ __launch_bounds__(kResThreads) void residual_kernel(ResidualArgs a) {
 
 // Threads of a row's block, and the values of a row that a thread has in flight.
 // One value at a time on 256 threads, each with a load and an exponential behind
-// the last, 32 rows of 102400 logits took 318 us (the whole signals of a 32-position
-// block 1289 us, 1112 now).
+// the last, a row of 102400 logits took 253 us (now 91).
 constexpr int kKlWide = 1024, kKlNarrow = 256, kKlBatch = 8;
-constexpr int kKlNarrowN = 2048;  // router rows: one batch of the narrow block
+// The longest rows of the narrow block: the wide one has four times the waves but
+// four times the partial results to merge.  us, narrow and wide, a row of softmax
+// (three sums): 2048 11 and 22, 12288 28 and 30, 16384 35 and 32; of sigmoids (whose
+// logarithms weigh more): 2056 27 and 28, 3072 34 and 33, 8192 78 and 59.
+constexpr int kKlNarrowSoftmax = 12288, kKlNarrowSigmoid = 2560;
 
 // Running (max, sum exp(v - max)).
 struct Lse {
@@ -48,6 +52,13 @@ __device__ __forceinline__ Lse lse_add(Lse a, const float (&v)[kKlBatch]) {
   for (int j = 0; j < kKlBatch; ++j)
     s += v[j] == -INFINITY ? 0.f : (v[j] == m ? 1.f : expf(v[j] - m));
   return Lse{m, s};
+}
+// One value: one exponential.
+__device__ __forceinline__ Lse lse_add(Lse a, const float (&v)[1]) {
+  const float e = expf(-fabsf(v[0] - a.m));
+  if (v[0] > a.m) return Lse{v[0], a.s * e + 1.f};
+  if (v[0] != -INFINITY) a.s += v[0] == a.m ? 1.f : e;
+  return a;
 }
 
 __device__ __forceinline__ Lse lse_merge(Lse a, Lse b) {
@@ -128,37 +139,36 @@ __global__ __launch_bounds__(NTH) void rowkl_kernel(RowKlArgs a) {
   const float it = 1.f / a.tau;
   Lse la{-INFINITY, 0.f}, lb{-INFINITY, 0.f}, lb1{-INFINITY, 0.f};
   Best best{-INFINITY, __int_as_float(INT_MAX)};
-  // The batch from value i0 on: a + bias and b + bias (sigmoid: log sigmoid of
-  // a and b in x and y, and a + bias in c).  Loads are clamped; what lies past
-  // the row is -inf.
-  float x[kKlBatch], y[kKlBatch], c[kKlBatch];
-  const auto load = [&](int i0) {
+  // A thread's B values from i0 on: a + bias and b + bias (sigmoid: log sigmoid of a
+  // and b in x and y, and a + bias in c).  All of them exist.
+  const auto load = [&](auto& x, auto& y, auto& c, int i0) __attribute__((always_inline)) {
+    constexpr int B = sizeof(x) / sizeof(float);
 #pragma unroll
-    for (int j = 0; j < kKlBatch; ++j) {
-      const int i = min(i0 + j * NTH, a.n - 1);
+    for (int j = 0; j < B; ++j) {
+      const int i = i0 + j * NTH;
       c[j] = a.bias ? a.bias[i] : 0.f;
       x[j] = pa[i];
       y[j] = pb[i];
     }
 #pragma unroll
-    for (int j = 0; j < kKlBatch; ++j) {
-      const bool in = i0 + j * NTH < a.n;
+    for (int j = 0; j < B; ++j) {
       const float bias = c[j];
       c[j] = x[j] + bias;
-      x[j] = !in ? -INFINITY : (a.sigmoid ? log_sigmoid(x[j]) : c[j]);
-      y[j] = !in ? -INFINITY : (a.sigmoid ? log_sigmoid(y[j]) : y[j] + bias);
+      x[j] = a.sigmoid ? log_sigmoid(x[j]) : c[j];
+      y[j] = a.sigmoid ? log_sigmoid(y[j]) : y[j] + bias;
     }
   };
-  for (int i0 = threadIdx.x; i0 < a.n; i0 += NTH * kKlBatch) {
-    load(i0);
+  const auto add = [&](auto b, int i0) __attribute__((always_inline)) {
+    constexpr int B = decltype(b)::value;
+    float x[B], y[B], c[B];
+    load(x, y, c, i0);
     if (!a.sigmoid) lb1 = lse_add(lb1, y);
 #pragma unroll
-    for (int j = 0; j < kKlBatch; ++j) {
+    for (int j = 0; j < B; ++j) {
       // Argmax of a + bias; a NaN counts as -infinity, as in the argmax.
-      const int i = i0 + j * NTH;
       const float vc = c[j] == c[j] ? c[j] : -INFINITY;
-      if (i < a.n && (__float_as_int(best.i) == INT_MAX || vc > best.v))
-        best = Best{vc, __int_as_float(i)};
+      if (__float_as_int(best.i) == INT_MAX || vc > best.v)
+        best = Best{vc, __int_as_float(i0 + j * NTH)};
       if (!a.sigmoid) {
         x[j] *= it;
         y[j] *= it;
@@ -166,22 +176,38 @@ __global__ __launch_bounds__(NTH) void rowkl_kernel(RowKlArgs a) {
     }
     la = lse_add(la, x);
     lb = lse_add(lb, y);
-  }
+  };
+  float lsa = 0.f, lsb = 0.f, acc = 0.f;
+  const auto divergence = [&](auto b, int i0) __attribute__((always_inline)) {
+    constexpr int B = decltype(b)::value;
+    float x[B], y[B], c[B];
+    load(x, y, c, i0);
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const float xa = (a.sigmoid ? x[j] : x[j] * it) - lsa;
+      const float xb = (a.sigmoid ? y[j] : y[j] * it) - lsb;
+      acc += expf(xa) * (xa - xb);
+    }
+  };
+  // The row: whole batches of the block, then what is left value by value (a router's
+  // row is all of that: a padded batch, or code unrolled for one, costs it 1 to 10 us).
+  const auto sweep = [&](const auto& f) __attribute__((always_inline)) {
+    constexpr int kStep = NTH * kKlBatch;
+    const int whole = a.n / kStep * kStep;
+#pragma unroll 1
+    for (int i0 = threadIdx.x; i0 < whole; i0 += kStep)
+      f(std::integral_constant<int, kKlBatch>{}, i0);
+#pragma unroll 1
+    for (int i0 = whole + threadIdx.x; i0 < a.n; i0 += NTH) f(std::integral_constant<int, 1>{}, i0);
+  };
+  sweep(add);
   la = block_reduce<NTH>(la, rl, LseOp{}, Lse{-INFINITY, 0.f});
   lb = block_reduce<NTH>(lb, rl, LseOp{}, Lse{-INFINITY, 0.f});
   lb1 = block_reduce<NTH>(lb1, rl, LseOp{}, Lse{-INFINITY, 0.f});
   best = block_reduce<NTH>(best, rb, BestOp{}, Best{-INFINITY, __int_as_float(INT_MAX)});
-  const float lsa = lse_val(la), lsb = lse_val(lb);
-  float acc = 0.f;
-  for (int i0 = threadIdx.x; i0 < a.n; i0 += NTH * kKlBatch) {
-    load(i0);
-#pragma unroll
-    for (int j = 0; j < kKlBatch; ++j) {
-      const float xa = (a.sigmoid ? x[j] : x[j] * it) - lsa;
-      const float xb = (a.sigmoid ? y[j] : y[j] * it) - lsb;
-      if (i0 + j * NTH < a.n) acc += expf(xa) * (xa - xb);
-    }
-  }
+  lsa = lse_val(la);
+  lsb = lse_val(lb);
+  sweep(divergence);
   const Sum tot = block_reduce<NTH>(Sum{acc}, rs, SumOp{}, Sum{0.f});
   if (threadIdx.x == 0) {
     a.kl[blockIdx.x] = a.sigmoid ? tot.s : a.tau * a.tau * tot.s;
@@ -203,7 +229,7 @@ hipError_t launch_residual(const ResidualArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_rowkl(const RowKlArgs& a, hipStream_t s) {
-  if (a.n <= kKlNarrowN)
+  if (a.n <= (a.sigmoid ? kKlNarrowSigmoid : kKlNarrowSoftmax))
     hipLaunchKernelGGL(rowkl_kernel<kKlNarrow>, dim3(a.rows), dim3(kKlNarrow), 0, s, a);
   else
     hipLaunchKernelGGL(rowkl_kernel<kKlWide>, dim3(a.rows), dim3(kKlWide), 0, s, a);
