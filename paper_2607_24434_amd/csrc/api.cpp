@@ -130,16 +130,21 @@ int chunk_count(int K, int n, int align) {
 // Blocks of two positions or more whose sources' columns fit the waves'
 // registers.  V2-Lite layer, gate/up + down, us on the matrix cores against
 // the vector ALU: bf16 T = 2 54 against 57, T = 9 120 against 136, T = 64 234
-// against 802; Q4_0 T = 9 76 against 113, T = 1 31 against 26.  (One bf16
-// position is the same within the runs' spread, and the persistent draft pass
-// computes it in the vector ALU's order.)  The plan follows from the layer's
-// shape and the block alone, so that calls over parts of a layer (an expert
-// cache's chunks) sum in the same order.
+// against 802; Q4_0 T = 9 76 against 113.  (One bf16 position is the same within
+// the runs' spread, and the persistent draft pass computes it in the vector ALU's
+// order.)  Two Q4_0 positions of few experts stay on the vector ALU where a row of
+// codes fills its waves: there the layer is bound by a fragment's way to the matrix
+// cores.  Whole layer of 2048 columns (I = 1408, no shared block), us there and on
+// the vector ALU: one expert a position 30 and 23, three 35 and 30, six 42 and 37,
+// eight 45 and 45; 1024 columns: two experts 25 and 26, six 26 and 32.  The plan
+// follows from the layer's shape and the block alone, so that calls over parts of a
+// layer (an expert cache's chunks) sum in the same order.
 MfmaPlan mfma_plan(const de_moe_desc& d, int T, int kk, bool has_shared, bool has_draft) {
   MfmaPlan p{};
   const int Is = has_shared ? d.shared_inter : 0, Id = has_draft ? d.draft_inter : 0;
   if (d.wdtype == DE_F32 || T < 2 || d.hidden > de::kMfmaMaxK || d.inter > de::kMfmaMaxK ||
-      Id > de::kMfmaMaxK || !de::mfma_fits(d.wdtype, T, d.n_experts, d.top_k))
+      Id > de::kMfmaMaxK || !de::mfma_fits(d.wdtype, T, d.n_experts, d.top_k) ||
+      (d.wdtype == DE_Q4_0 && T == 2 && kk <= 6 && d.hidden > 1024))
     return p;
   if (Is > 0) {
     // No wider than the routed experts' rows where possible, so that every

@@ -92,7 +92,9 @@ def q4_blocks(w, n, inter, hidden):
 
 @pytest.mark.parametrize("T,H,N,k,I,Is", [
     (2, 32, 4, 2, 32, 32), (16, 96, 5, 3, 64, 160), (17, 288, 6, 6, 160, 0), (5, 544, 8, 2, 32, 608),
-    (64, 512, 4, 4, 128, 256), (9, 2048, 16, 6, 1408, 2816), (33, 1024, 3, 2, 64, 2048 + 1056)])
+    (64, 512, 4, 4, 128, 256), (9, 2048, 16, 6, 1408, 2816), (33, 1024, 3, 2, 64, 2048 + 1056),
+    (2, 2048, 16, 6, 1408, 2816), (2, 1056, 8, 1, 64, 0), (2, 2048, 8, 7, 96, 64),
+    (2, 1024, 8, 2, 96, 64)])
 @pytest.mark.parametrize("kind", ["verify", "draft"])
 def test_q4_layer_matches_the_vector_alu_path(T, H, N, k, I, Is, kind):
     x, w, router = inputs(T, H, N, I, Is, T + H)
