@@ -48,7 +48,7 @@ PMC_TRAFFIC = {
                 "paper_2607_24434_amd/csrc/grouped_core.h",
                 "paper_2607_24434_amd/csrc/topk_union.h",
                 "paper_2607_24434_amd/csrc/de_common.h"],
-    "sha256": "4a63b0868ac66dbf177a747edb292bc1e2af4c22b04980ba47d6a667c248c3df",
+    "sha256": "e9a743515992c8324da1c66ce5d40c3b65264b3e98ca593d77e656e251dfca60",
 }
 
 

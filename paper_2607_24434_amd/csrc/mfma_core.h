@@ -657,7 +657,12 @@ __device__ __forceinline__ void plain_outputs(const TL& tl, int v, int r, int st
       const bool mine = output_at<WT, GATEUP>(c, rpt, r, o, rr, i, rg, pos, row);
       float* const p = c.out + (size_t)(c.p0 + pos) * c.ostride + row;
       float val = 0.f;
-      if (mine) val = *(DE_GLOBAL float*)p;  // (its own store)
+      if (mine) {  // (its own store)
+        if constexpr (SHARED)
+          val = __hip_atomic_load((DE_GLOBAL float*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          val = *(DE_GLOBAL float*)p;
+      }
       unsigned long long bad = __builtin_amdgcn_ballot_w64(!(val == val));
       while (bad != 0ull) {
         const int l = (int)__builtin_ctzll(bad);

@@ -135,3 +135,21 @@ def test_a_position_with_a_nan_beside_infinite_weights(T, H, V):
     assert same_kind(out, want)
     fin = want.isfinite()
     assert torch.equal(out.double()[fin], want[fin])
+
+
+def test_the_single_launch_layer(monkeypatch):
+    """The same in the single-launch verify layer, whose blocks read each other's
+    outputs: the bits of the separate launches."""
+    T, H, N, k, I, Is = 9, 512, 8, 2, 136, 296
+    x, w, router = inputs(T, H, N, I, Is, 1)
+    x = bf16_exact(x)
+    w[0].view(N, 3, I * H)[1, 1, 5] = INF
+    w[0].view(N, 3, I * H)[2, 2, 7] = -INF
+    w[1].view(3, Is * H)[2, 9] = INF
+    out = []
+    for fused in ("0", "1"):
+        monkeypatch.setenv("DE_VERIFY_FUSED", fused)
+        out.append(layer(T, H, N, k, I, Is, x, w, router, de.DE_BF16))
+    assert out[0][0].isinf().any() and out[0][0].isfinite().any()
+    assert torch.equal(out[0][0].nan_to_num(1e30, 2e30, -2e30),
+                       out[1][0].nan_to_num(1e30, 2e30, -2e30))
