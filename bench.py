@@ -48,7 +48,7 @@ PMC_TRAFFIC = {
                 "paper_2607_24434_amd/csrc/grouped_core.h",
                 "paper_2607_24434_amd/csrc/topk_union.h",
                 "paper_2607_24434_amd/csrc/de_common.h"],
-    "sha256": "e9a743515992c8324da1c66ce5d40c3b65264b3e98ca593d77e656e251dfca60",
+    "sha256": "a5afbeabbdf2d47b4e421609d5516b4bda92f607ea5c6515bd0e4a7be394f927",
 }
 
 

@@ -24,7 +24,9 @@
 
 namespace de {
 
-// LDS arrays of the selection and union (sizes: T*k, T*k, N, N, N, 4).
+// LDS arrays of the selection and union (sizes: T*k, T*k, N, N, N, 4), the masks
+// first: behind the lists, at an odd multiple of 8 bytes, a layer of five positions and
+// 22 us took 0.1 us more.
 struct SelView {
   int32_t* idx;              // ordered top-k ids [T, k]
   float* gate;               // their gates
@@ -42,13 +44,12 @@ __host__ __device__ inline size_t sel_view_bytes(int T, int k, int N) {
 __device__ inline SelView sel_view_at(char* p, int T, int k, int N) {
   SelView v;
   const size_t tk = (size_t)T * k;
-  v.idx = reinterpret_cast<int32_t*>(p);
-  v.gate = reinterpret_cast<float*>(v.idx + tk);
-  p += tk * 8;
   v.mask = reinterpret_cast<unsigned long long*>(p);
   v.off = reinterpret_cast<int32_t*>(v.mask + N);
   v.upos = v.off + N;
   v.misc = v.upos + N;
+  v.idx = v.misc + 4;
+  v.gate = reinterpret_cast<float*>(v.idx + tk);
   return v;
 }
 
